@@ -55,6 +55,10 @@ struct lbm_handle {
   bool profiling = false;
   // two steps per bulk pass (float32, d = 3): scratch state for the wall rows
   int steps_per_pass = 1;
+  bool multi = false;           // passes of several steps wanted (lbm_params.steps_per_pass == 2)
+  MarchPlan plans[4] = {};      // passes of at most 1, 2, 4, 8 steps (d = 2)
+  double* wall_ws = nullptr;    // wall data of wall_ws_steps steps (marching passes)
+  int wall_ws_steps = 0;
   void* fuse_buf = nullptr;     // state_bytes: populations (+ phi in split mode)
   double* xdata2 = nullptr;     // split mode: x_1-face data of the second step
   int device = 0;               // current device at lbm_create
@@ -163,6 +167,8 @@ void release(lbm_handle* h) {
   dev_free(h, h->kp.xdata);
   dev_free(h, h->fuse_buf);
   dev_free(h, h->xdata2);
+  dev_free(h, h->wall_ws);
+  h->wall_ws = nullptr;
   h->partial = h->result = nullptr;
   h->kp.xdata = nullptr;
   h->fuse_buf = nullptr;
@@ -284,6 +290,11 @@ double* blob_phi(const lbm_handle* h, void* blob) {
              : nullptr;
 }
 
+// Marching passes (d = 2): several steps per launch, any storage but hi/lo.
+bool use_march(const lbm_handle* h) {
+  return h->multi && h->d == 2 && h->precision != LBM_FP32_HILO;
+}
+
 int tape_push(lbm_handle* h) {
   void* b = dev_alloc(h, state_bytes(h));
   if (!b) return fail(h, LBM_ENOMEM, "checkpoint allocation failed");
@@ -386,6 +397,7 @@ int lbm_create(int d, const int64_t* dims, double tau, const lbm_params* p, lbm_
   h->steps_per_pass =
       (p->steps_per_pass == 2 && (d == 3 || (d == 2 && !split_mode(p->precision)))) ? 2
                                                                                         : 1;
+  h->multi = p->steps_per_pass == 2;
   h->stream = static_cast<hipStream_t>(p->stream);
   if (hipGetDevice(&h->device) != hipSuccess) {
     (void)hipGetLastError();
@@ -471,6 +483,9 @@ int lbm_create(int d, const int64_t* dims, double tau, const lbm_params* p, lbm_
     delete h;
     return rc;
   }
+
+  if (use_march(h))
+    for (int i = 0; i < 4; ++i) h->plans[i] = march_plan(kp, h->precision, 1 << i);
 
   // device buffers
   const size_t pb = pop_bytes(h);
@@ -600,8 +615,39 @@ hipError_t check_nonfinite(lbm_handle* h) {
   return e;
 }
 
-int run_steps(lbm_handle* h, int64_t n, void* cbuf, double* xd2) {
-  const bool pairs = use_pairs(h);
+// Wall data of a marching pass: doubles per step, and the steps the workspace
+// holds: 64 (one launch of k_wall_data serves several passes), fewer where that
+// would exceed 1 MB and half the state.
+int64_t wall_doubles(const lbm_handle* h) {
+  return use_march(h) ? wall_data2_x(h->kp) + wall_data2_y(h->kp) : 0;
+}
+int wall_steps(const lbm_handle* h) {
+  const int64_t per = wall_doubles(h) * static_cast<int64_t>(sizeof(double));
+  const int64_t cap = std::max<int64_t>(1 << 20, static_cast<int64_t>(state_bytes(h)) / 2);
+  int s = 64;
+  while (s > 1 && s * per > cap) s /= 2;
+  return s;
+}
+
+// Steps of the next pass when `left` remain: none may pass over the tape's next
+// checkpoint, nor (where a pair of steps did not) the next non-finite check.
+int64_t pass_limit(const lbm_handle* h, int64_t left) {
+  if (h->tape_active)
+    left = std::min(left, h->tape_every - (h->step - h->tape_start) % h->tape_every);
+  if (h->check_every > 0) {
+    int64_t due = std::max<int64_t>(1, h->check_every - (h->step - h->last_check));
+    if (h->steps_per_pass == 2) due = (due + 1) / 2 * 2;
+    left = std::min(left, due);
+  }
+  return left;
+}
+
+int run_steps(lbm_handle* h, int64_t n, void* cbuf, double* xd2, double* wall_ws, int wall_cap) {
+  const bool pairs = use_pairs(h) && h->d == 3;
+  const bool march = use_march(h);
+  const int64_t wx_len = march ? wall_data2_x(h->kp) : 0;
+  const int64_t wy_len = march ? wall_data2_y(h->kp) : 0;
+  int64_t wall0 = 0, wall_n = 0;  // steps whose wall data the workspace holds
   bool checked = false;
   if (h->check_every > 0 && n > 0) {
     hipError_t e = launch_zero_count(h->nonfinite, h->stream);
@@ -611,7 +657,20 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, double* xd2) {
   while (i < n) {
     const int src = h->cur, dst = 1 - h->cur;
     const bool aligned = !h->tape_active || (h->step - h->tape_start) % 2 == 0;
-    const int64_t todo = (pairs && aligned && n - i >= 2) ? 2 : 1;
+    int64_t todo = (pairs && aligned && n - i >= 2) ? 2 : 1;
+    MarchPlan plan{1, 0};
+    if (march) {
+      const int64_t lim = std::min<int64_t>(pass_limit(h, n - i), wall_cap);
+      plan = h->plans[lim >= 8 ? 3 : lim >= 4 ? 2 : lim >= 2 ? 1 : 0];
+      todo = plan.nl;
+      if (todo > 1 && h->kp.scheme != kNoWall && h->step + todo > wall0 + wall_n) {
+        wall0 = h->step;
+        wall_n = std::min<int64_t>(n - i, wall_cap);
+        hipError_t e = launch_wall_data2(h->kp, wall_ws, wall_ws + wx_len * wall_cap, wall0,
+                                         static_cast<int>(wall_n), h->stream);
+        if (e != hipSuccess) return hip_fail(h, e, "wall data");
+      }
+    }
     hipEvent_t* ev = nullptr;
     if (h->profiling && h->prof_used < h->prof_cap) {
       ev = &h->prof_ev[3 * h->prof_used];
@@ -619,7 +678,20 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, double* xd2) {
       h->prof_steps += todo;
     }
     hipError_t e;
-    if (todo == 2) {
+    if (march && todo > 1) {
+      MarchParams mp = march_params(h->kp);
+      if (h->kp.scheme != kNoWall) {
+        mp.wx = wall_ws + wx_len * (h->step - wall0);
+        mp.wy = wall_ws + wx_len * wall_cap + wy_len * (h->step - wall0);
+      }
+      const MarchBufs mb{h->buf[src], h->buf[dst], h->phib[src], h->phib[dst]};
+      if (ev) (void)hipEventRecord(ev[0], h->stream);
+      e = launch_march2(mp, h->kp.scheme, h->precision, plan, mb, h->step, h->stream);
+      if (ev) {
+        (void)hipEventRecord(ev[1], h->stream);
+        (void)hipEventRecord(ev[2], h->stream);
+      }
+    } else if (todo == 2) {
       const FusedBufs fb{h->buf[src], h->buf[dst], cbuf, h->phib[src], h->phib[dst],
                          blob_phi(h, cbuf), xd2};
       e = launch_fused_pair(h->kp, h->precision, fb, h->step, h->stream, ev);
@@ -662,7 +734,13 @@ extern "C" {
 
 int lbm_step(lbm_handle* h, int64_t n) {
   if (int rc = step_checks(h, n); rc != LBM_OK) return rc;
-  if (use_pairs(h) && n >= 2) {
+  if (wall_doubles(h) > 0 && n >= 2 && !h->wall_ws) {
+    h->wall_ws_steps = wall_steps(h);
+    h->wall_ws = static_cast<double*>(
+        dev_alloc(h, sizeof(double) * wall_doubles(h) * h->wall_ws_steps));
+    if (!h->wall_ws) return fail(h, LBM_ENOMEM, "wall data of the marching passes");
+  }
+  if (h->d == 3 && use_pairs(h) && n >= 2) {
     if (pair_state_bytes(h) > 0 && !h->fuse_buf) {
       h->fuse_buf = dev_alloc(h, pair_state_bytes(h));
       if (!h->fuse_buf) return fail(h, LBM_ENOMEM, "scratch state for two-step passes");
@@ -672,7 +750,8 @@ int lbm_step(lbm_handle* h, int64_t n) {
       if (!h->xdata2) return fail(h, LBM_ENOMEM, "x-face data for two-step passes");
     }
   }
-  return run_steps(h, n, h->fuse_buf, h->xdata2);
+  return run_steps(h, n, h->fuse_buf, h->xdata2, h->wall_ws,
+                   wall_doubles(h) > 0 ? h->wall_ws_steps : kMarchMaxSteps);
 }
 
 int lbm_step_static(lbm_handle* h, int64_t n) {
@@ -697,7 +776,18 @@ int lbm_step_static(lbm_handle* h, int64_t n) {
       if (xdata_bytes(h) > 0) xd2 = reinterpret_cast<double*>(static_cast<char*>(base) + cb);
     }
   }
-  return run_steps(h, n, cbuf, xd2);
+  // the wall data of marching passes go to the same scratch
+  double* wall_ws = nullptr;
+  int wall_cap = kMarchMaxSteps;
+  if (wall_doubles(h) > 0) {
+    const int64_t per = wall_doubles(h) * static_cast<int64_t>(sizeof(double));
+    wall_cap = static_cast<int>(
+        std::min<int64_t>(wall_steps(h), static_cast<int64_t>(kStaticScratchBytes) / per));
+    hipError_t err = hipSuccess;
+    wall_ws = static_cast<double*>(static_scratch(h->device, &err));
+    if (!wall_ws) return hip_fail(h, err, "address of the static scratch");
+  }
+  return run_steps(h, n, cbuf, xd2, wall_ws, std::max(wall_cap, 1));
 }
 
 int lbm_moments(lbm_handle* h, uint32_t what, double* phi_out_dev, double* scalars_host) {

@@ -82,6 +82,49 @@ struct KParams {
   FieldDev field;
 };
 
+// What the marching passes of d = 2 (march.hpp) need of a lattice, by value: a
+// tenth of KParams, whose field table they do not read.
+struct MarchParams {
+  int n0, n1, bc0, bc1;
+  long long ps;              // elements between two population planes
+  double omega[9];
+  float omega_f[9];
+  float s_f;
+  double s, dt, R, dtR, phi_ref;
+  // wall data of the steps of a pass (l = 0, 1, ...):
+  // wx[((l * 2 + side) * 3 + slot) * n1 + row], wy[((l * 2 + side) * 3 + slot) * n0 + x]
+  const double* wx;
+  const double* wy;
+};
+struct MarchBufs {
+  const void* src;
+  void* dst;
+  const double* phi_src;     // split mode
+  double* phi_dst;
+};
+MarchParams march_params(const KParams& p);
+
+// Output columns of one wavefront's tile in a pass of nl steps: 64 lanes less a
+// halo of nl on either side, in whole 64-byte pieces of float64 rows.
+__host__ __device__ constexpr int march_width(int nl) { return (64 - 2 * nl) / 8 * 8; }
+constexpr int kMarchMaxSteps = 8, kMarchMaxWallSteps = 4;
+
+// Steps (nl: 1 for none, 2, 4 or 8) and rows per tile (yc) of a pass.
+struct MarchPlan {
+  int nl, yc;
+};
+MarchPlan march_plan(const KParams& p, int mode, int max_nl);
+// plan.nl steps of a d = 2 lattice (float64, float32 or split mode) in one
+// pass; p.wx / p.wy hold the wall data of those steps.
+hipError_t launch_march2(const MarchParams& p, int scheme, int mode, const MarchPlan& plan,
+                         const MarchBufs& b, long long n, hipStream_t stream);
+// Doubles of wall data per step (x_1 faces, then x_2 faces), and the wall data of
+// steps n .. n + nsteps - 1 into wx / wy in the layout of MarchParams.
+long long wall_data2_x(const KParams& p);
+long long wall_data2_y(const KParams& p);
+hipError_t launch_wall_data2(const KParams& p, double* wx, double* wy, long long n, int nsteps,
+                             hipStream_t stream);
+
 // One block of a batched launch: rows row0 .. row0 + blockDim.y - 1 of an
 // instance.
 struct BatchTile {

@@ -177,23 +177,4 @@ __device__ __forceinline__ int fuse_slot2(int it) {
   else return 15 + i;
 }
 
-// x_2 rows per block: 64, halved (down to 8) while the grid has fewer than
-// four blocks per CU
-__host__ __device__ constexpr int fuse_ychunk(int tiles_x, int n1) {
-  int yc = 64;
-  while (yc > 8 && tiles_x * ((n1 + yc - 1) / yc) < 4 * 256) yc /= 2;
-  return yc;
-}
-
-// tile of this block for d = 2, in the XCD-aware order of fuse_tile
-__device__ __forceinline__ void fuse_tile2(const KParams& p, int TX, int& bx, int& by) {
-  const int gx = (p.n[0] + TX - 1) / TX;
-  const int nb = static_cast<int>(gridDim.x);
-  const int per = nb / 8;
-  const int b = static_cast<int>(blockIdx.x);
-  const int t = (b < 8 * per) ? (b % 8) * per + b / 8 : b;
-  bx = t % gx;
-  by = t / gx;
-}
-
 }  // namespace lbm

@@ -270,68 +270,8 @@ static hipError_t fused_pair_m(const KParams& p, const FusedBufs& fb, long long 
               : fused_pair_t<T, false, false>(p, a, b, c, n, stream, ev);
 }
 
-template <class T, bool TAN, bool HALF>
-static hipError_t fused_pair2_t(const KParams& p, const T* A, T* B, T* C, long long n,
-                                hipStream_t stream, hipEvent_t* ev) {
-  using S = FuseShape2<T, HALF>;
-  constexpr size_t lds = sizeof(T) * S::SLOTS * (S::TX + 2);
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fused2_d2<T, HALF>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       static_cast<int>(lds));
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  constexpr int mode = std::is_same<T, float>::value ? kFP32 : kFP64;
-  const LaunchShape s = step_shape(p);
-  const dim3 block(s.tx, s.ty);
-  const dim3 wgrid(static_cast<unsigned>((p.wall_rows + s.ty - 1) / s.ty));
-  const double t0 = static_cast<double>(n) * p.dt, t1 = static_cast<double>(n + 1) * p.dt;
-  auto mark = [&](int i) {
-    if (ev) (void)hipEventRecord(ev[i], stream);
-  };
-  if (p.bc[0] != 0) {
-    const unsigned xb = static_cast<unsigned>((2 * p.rows + 255) / 256);
-    launch_xface<2, T, TAN>(xb, stream, const_cast<T*>(A), p, t0, mode);
-    launch_xface<2, T, TAN>(xb, stream, B, p, t1, mode);
-  }
-  if (p.wall_rows > 0)
-    launch_wall<2, T, TAN>(wgrid, block, stream, A, C, p, t0);
-  const int tiles_x = (p.n[0] + S::TX - 1) / S::TX;
-  const int yc = fuse_ychunk(tiles_x, p.n[1]);
-  const dim3 grid(static_cast<unsigned>(tiles_x * ((p.n[1] + yc - 1) / yc)));
-  mark(0);
-  hipLaunchKernelGGL((k_fused2_d2<T, HALF>), grid, dim3(S::NT), lds, stream, A, B, C, p, yc);
-  mark(1);
-  if (p.wall_rows > 0)
-    launch_wall<2, T, TAN>(wgrid, block, stream, C, B, p, t1);
-  mark(2);
-  return hipGetLastError();
-}
-
-template <class T>
-static hipError_t fused_pair2_m(const KParams& p, const FusedBufs& fb, long long n,
-                                hipStream_t stream, hipEvent_t* ev) {
-  auto* a = static_cast<const T*>(fb.A);
-  auto* b = static_cast<T*>(fb.B);
-  auto* c = static_cast<T*>(fb.C);
-  const bool half = p.scheme == kHalfWay;
-  if (p.wall_data) {
-    return half ? fused_pair2_t<T, true, true>(p, a, b, c, n, stream, ev)
-                : fused_pair2_t<T, true, false>(p, a, b, c, n, stream, ev);
-  }
-  return half ? fused_pair2_t<T, false, true>(p, a, b, c, n, stream, ev)
-              : fused_pair2_t<T, false, false>(p, a, b, c, n, stream, ev);
-}
-
 hipError_t launch_fused_pair(const KParams& p, int mode, const FusedBufs& fb, long long n,
                              hipStream_t stream, hipEvent_t* ev) {
-  if (p.d == 2) {
-    if (mode == kFP32) return fused_pair2_m<float>(p, fb, n, stream, ev);
-    if (mode == kFP64) return fused_pair2_m<double>(p, fb, n, stream, ev);
-    return hipErrorInvalidValue;
-  }
   if (p.d != 3) return hipErrorInvalidValue;
   if (mode == kFP32) return fused_pair_m<float>(p, fb, n, stream, ev);
   if (mode == kFP64) return fused_pair_m<double>(p, fb, n, stream, ev);

@@ -257,12 +257,17 @@ inline int wall_variant(const KParams& p) {
 //
 // wall_mode gives mode j's factor at the wall point (cos and sin of its phase,
 // or its exponential in C), wall_term the mode's contribution to population k,
-// wall_close the terms outside the mode sum.
+// wall_close the terms outside the mode sum.  These and the helpers below them
+// disable floating-point contraction: it works within one basic block, so with
+// it a wall value would depend on where a kernel's loops leave each product,
+// and the kernels that store wall values for later would differ in the last bit
+// from those that use them at once.
 
 // t: t_{n+1} full-way, t_n half-way
 template <int D, int V>
 __device__ __forceinline__ void wall_mode(const KParams& p, const double (&x)[kMaxDim], double t,
                                           int j, double& C, double& S) {
+#pragma clang fp contract(off)
   const FieldDev& F = p.field;
   double ph = 0.0;
 #pragma unroll
@@ -278,6 +283,7 @@ __device__ __forceinline__ void wall_mode(const KParams& p, const double (&x)[kM
 template <int D, bool TAN, int V, int k, class Axis>
 __device__ __forceinline__ double wall_term(const KParams& p, int j, double C, double S,
                                             Axis axis) {
+#pragma clang fp contract(off)
   const FieldDev& F = p.field;
   const double dt = p.dt;
   const double o2 = p.P >= 2 ? 1.0 : 0.0;
@@ -341,6 +347,7 @@ __device__ __forceinline__ double wall_term(const KParams& p, int j, double C, d
 
 template <int D, int V, int k>
 __device__ __forceinline__ double wall_close(const KParams& p, double v, double t_n) {
+#pragma clang fp contract(off)
   if (wall_full<V>(p)) return p.omega[k] * (v + p.R * (t_n + p.dt));
   constexpr int kb = opp_index(D, k);
   const double o2 = p.P >= 2 ? 1.0 : 0.0;
@@ -377,6 +384,25 @@ __device__ __forceinline__ void wall_analytic(const KParams& p, const double (&x
   });
 }
 
+// coordinate of axis a at index i
+__device__ __forceinline__ double wall_coord(const KParams& p, int a, int i) {
+#pragma clang fp contract(off)
+  return p.origin[a] + (i + p.shift[a]) * p.dx;
+}
+
+// absolute post-collision population of a stored value: the float32 deviations
+// are taken from omega_k ref
+__device__ __forceinline__ double wall_absolute(double stored, double omega, double ref) {
+#pragma clang fp contract(off)
+  return stored + omega * ref;
+}
+
+// deviation of an absolute value v from weight * ref
+__device__ __forceinline__ double wall_deviation(double v, double weight, double ref) {
+#pragma clang fp contract(off)
+  return v - weight * ref;
+}
+
 // Modes whose factors the half-way wall path of d = 3 keeps in registers
 constexpr int kWallModeCache = 4;
 
@@ -411,7 +437,7 @@ __device__ __forceinline__ void wall_values(A (&f)[q_of(D)], const KParams& p, c
                                             double t_n, double ref, FStarLocal fstar_local) {
   double x[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int a = 0; a < D; ++a) x[a] = p.origin[a] + (r.i[a] + p.shift[a]) * p.dx;
+  for (int a = 0; a < D; ++a) x[a] = wall_coord(p, a, r.i[a]);
   bool out[q_of(D)];
   static_for<0, q_of(D)>([&](auto K) {
     constexpr int k = decltype(K)::value;
@@ -444,7 +470,7 @@ __device__ __forceinline__ void wall_values(A (&f)[q_of(D)], const KParams& p, c
           if (j < p.field.nmodes)
             v += wall_term<D, TAN, V, k>(p, j, mc[j], ms[j], [&](int kk) { return ax[kk]; });
         v = wall_close<D, V, k>(p, v, t_n) - fstar_local(opp_index(D, k));
-        f[k] = static_cast<A>(v - p.omega[k] * ref);
+        f[k] = static_cast<A>(wall_deviation(v, p.omega[k], ref));
       });
       return;
     }
@@ -470,7 +496,7 @@ __device__ __forceinline__ void wall_values(A (&f)[q_of(D)], const KParams& p, c
       if (!out[k]) return;
       double v = val[k];
       if (half) v -= fstar_local(opp_index(D, k));
-      f[k] = static_cast<A>(v - p.omega[k] * ref);
+      f[k] = static_cast<A>(wall_deviation(v, p.omega[k], ref));
     });
   });
 }
@@ -495,13 +521,13 @@ __global__ void __launch_bounds__(256)
   const int side = idx >= p.rows ? 1 : 0;
   const int row = idx - side * p.rows;
   double x[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
-  x[0] = p.origin[0] + ((side ? p.n[0] - 1 : 0) + p.shift[0]) * p.dx;
+  x[0] = wall_coord(p, 0, side ? p.n[0] - 1 : 0);
   int rr = row;
 #pragma unroll
   for (int a = 1; a < D; ++a) {
     const int ia = rr % p.n[a];
     rr /= p.n[a];
-    x[a] = p.origin[a] + (ia + p.shift[a]) * p.dx;
+    x[a] = wall_coord(p, a, ia);
   }
   const double ref = (mode == kFP32) ? p.phi_ref + p.R * (t_n + p.dt) : 0.0;
   const bool half = !wall_full<V>(p);
@@ -521,8 +547,8 @@ __global__ void __launch_bounds__(256)
         p.xdata[((long long)side * S + xface_slot(D, k)) * p.rows + row] = val[k];
       } else {
         constexpr int kb = opp_index(D, k);
-        const double wref = (half ? p.omega[k] + p.omega[kb] : p.omega[k]) * ref;
-        buf[k * ps + p.xoff + row] = static_cast<T>(val[k] - wref);
+        const double w = half ? p.omega[k] + p.omega[kb] : p.omega[k];
+        buf[k * ps + p.xoff + row] = static_cast<T>(wall_deviation(val[k], w, ref));
       }
     }
   });
@@ -537,8 +563,8 @@ __global__ void __launch_bounds__(256)
 // float32 stores deviations from the uniform exact state omega_k (phi_ref + R t),
 // which is a fixed point of stream + collide, so the deviations follow the same
 // update without the source term; phi is summed with TwoSum compensation.
-template <int D, class T>
-__device__ __forceinline__ void collide_vals(T (&f)[q_of(D)], const KParams& p) {
+template <int D, class T, class Params>
+__device__ __forceinline__ void collide_vals(T (&f)[q_of(D)], const Params& p) {
   constexpr int Q = q_of(D);
   if constexpr (std::is_same<T, float>::value) {
     float sum = f[0], comp = 0.0f;
@@ -942,18 +968,6 @@ __device__ __forceinline__ void fused2_d2_tile(const T* __restrict__ A, T* __res
   }
 }
 
-template <class T, bool HALF>
-__global__ void __launch_bounds__(256)
-    k_fused2_d2(const T* __restrict__ A, T* __restrict__ B, T* __restrict__ C, const KParams p,
-                const int yc) {
-  extern __shared__ __align__(16) unsigned char fuse_lds[];
-  int tx_, ty_;
-  fuse_tile2(p, FuseShape2<T, HALF>::TX, tx_, ty_);
-  const int yc0 = ty_ * yc;
-  fused2_d2_tile<T, HALF>(A, B, C, p, reinterpret_cast<T*>(fuse_lds),
-                          tx_ * FuseShape2<T, HALF>::TX, yc0, min(yc0 + yc, p.n[1]));
-}
-
 // Two steps of many periodic d = 2 lattices in one launch: block b takes tile
 // tiles[b] (instance, x_1 start, row range) with the instance's parameter
 // block and buffers (cur selects the source).
@@ -1023,8 +1037,9 @@ __global__ void __launch_bounds__(256)
 // that keep phi of a plane in LDS keep t, formed once per node.
 __device__ __forceinline__ double split_src(double phi, const KParams& p) { return phi + p.dtR; }
 
+template <class Params>
 __device__ __forceinline__ double split_fstar_t(double omega, double t, float g,
-                                                const KParams& p) {
+                                                const Params& p) {
   return fma(omega, t, (1.0 - p.s) * static_cast<double>(g));
 }
 
@@ -1708,7 +1723,7 @@ __global__ void __launch_bounds__(256)
     const int node = r.rowbase + x;
     T f[Q];
     auto fstar = [&](int kb) {
-      return static_cast<double>(src[kb * ps + node]) + p.omega[kb] * ref;
+      return wall_absolute(static_cast<double>(src[kb * ps + node]), p.omega[kb], ref);
     };
     if constexpr (D == 4 && kF32) {
       // the wall values first, then the pulls of the populations that enter

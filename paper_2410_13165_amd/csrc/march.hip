@@ -1,0 +1,203 @@
+// Launches of the d = 2 marching passes (march.hpp) and of their wall data.
+#include <algorithm>
+
+#include "march.hpp"
+
+namespace lbm {
+
+// One tile per wavefront; kMarchWaves of them share a block, tiles next to each
+// other in x_1, whose halos read the same lines.  Walls take two per block, to
+// keep its wall data within 64 KB of LDS.
+template <int WALL>
+constexpr int kMarchWaves = WALL ? 2 : 4;
+
+template <int MODE, int NL, int WALL, int D>
+__global__ void __launch_bounds__(64 * kMarchWaves<WALL>)
+    k_march2(const MarchParams p, const MarchBufs b, const int yc, const int gx, const int ntiles,
+             const long long n) {
+  extern __shared__ __align__(16) unsigned char march_mem[];
+  const int wave = static_cast<int>(threadIdx.x) / 64;
+  const int w = static_cast<int>(blockIdx.x) * kMarchWaves<WALL> + wave;
+  if (w >= ntiles) return;
+  constexpr int W = march_width(NL);
+  const int y0 = (w / gx) * yc;
+  march2_tile<MODE, NL, WALL, D>(
+      p, b, (w % gx) * W, W, y0, min(y0 + yc, p.n1), n,
+      reinterpret_cast<double*>(march_mem + (WALL ? wave * march_lds(NL, yc) : 0)));
+}
+
+MarchParams march_params(const KParams& p) {
+  MarchParams m{};
+  m.n0 = p.n[0];
+  m.n1 = p.n[1];
+  m.bc0 = p.bc[0];
+  m.bc1 = p.bc[1];
+  m.ps = p.pstride;
+  for (int k = 0; k < 9; ++k) {
+    m.omega[k] = p.omega[k];
+    m.omega_f[k] = p.omega_f[k];
+  }
+  m.s_f = p.s_f;
+  m.s = p.s;
+  m.dt = p.dt;
+  m.R = p.R;
+  m.dtR = p.dtR;
+  m.phi_ref = p.phi_ref;
+  return m;
+}
+
+template <int MODE, int NL, int WALL, int D>
+static hipError_t march2_l(const MarchParams& p, const MarchBufs& b, long long n, int yc,
+                           hipStream_t stream) {
+  constexpr int W = march_width(NL), NW = kMarchWaves<WALL>;
+  const int gx = (p.n0 + W - 1) / W;
+  const int ntiles = gx * ((p.n1 + yc - 1) / yc);
+  const size_t lds = WALL ? NW * march_lds(NL, yc) : 0;
+  hipLaunchKernelGGL((k_march2<MODE, NL, WALL, D>), dim3((ntiles + NW - 1) / NW), dim3(64 * NW),
+                     lds, stream, p, b, yc, gx, ntiles, n);
+  return hipGetLastError();
+}
+
+// Source rows in flight: two hide more of the load latency than one (512^2,
+// 8 steps per pass, float64: 22 against 25 us); four cost registers (and are
+// slower on large lattices).  With walls one, beside the wall data.
+template <int MODE, int NL>
+static hipError_t march2_w(const MarchParams& p, int scheme, const MarchBufs& b, long long n,
+                           int yc, hipStream_t stream) {
+  if (scheme == kNoWall) return march2_l<MODE, NL, 0, 2>(p, b, n, yc, stream);
+  if constexpr (NL <= kMarchMaxWallSteps)
+    return scheme == kFullWay ? march2_l<MODE, NL, kFullWay, 1>(p, b, n, yc, stream)
+                              : march2_l<MODE, NL, kHalfWay, 1>(p, b, n, yc, stream);
+  return hipErrorInvalidValue;
+}
+
+// Steps and rows per tile of a pass of at most max_nl steps, by a model of its
+// time fitted to measured passes (64^2 to 2048^2, us): 4 for the launch, then
+// the largest of
+//   * one tile alone: c per row and stage (its instructions at one wavefront per
+//     SIMD: 0.115 in float64, 0.172 in float32 with its compensated sum, 0.177
+//     split) and 0.35 per source row (its load);
+//   * a SIMD's tiles one after another: c per row and stage of each;
+//   * the traffic at 5.2 TB/s, halo columns and rows read again.
+// The minimum is over time per step.  Large float32 lattices are bound by the
+// second (2048^2: 8 steps, 152 us), float64 ones by the third (149 us), small
+// ones by the first and the launch (64^2: 4 steps of one row per tile, 7.5 us).
+// 16 wall rows and columns per wavefront are more registers and instructions:
+// passes over walls stop at 4 steps and 32 rows.
+MarchPlan march_plan(const KParams& p, int mode, int max_nl) {
+  const bool walls = p.scheme != kNoWall;
+  const double c = mode == kFP64 ? 0.115 : mode == kFP32 ? 0.172 : 0.177;
+  const double node_bytes = mode == kFP64 ? 72.0 : mode == kFP32 ? 36.0 : 44.0;
+  const int simds = 4 * device_cus();
+  MarchPlan best{1, 0};
+  double best_t = 0.0;
+  for (int nl = 2; nl <= max_nl && nl <= (walls ? kMarchMaxWallSteps : kMarchMaxSteps); nl *= 2) {
+    const int w = march_width(nl);
+    const long long gx = (p.n[0] + w - 1) / w;
+    for (int yc = 1; yc <= (walls ? 32 : 128); ++yc) {
+      const long long tiles = gx * ((p.n[1] + yc - 1) / yc);
+      if (tiles > (1LL << 28)) continue;
+      const double rows = nl * yc + nl * (nl - 1);
+      const double alone = rows * c + (yc + 2 * nl) * 0.35;
+      const double issue = static_cast<double>((tiles + simds - 1) / simds) * rows * c;
+      const double bytes = p.nodes * node_bytes * ((1.0 + 2.0 * nl / yc) * 64.0 / w + 1.0);
+      const double t = (4.0 + std::max(std::max(alone, issue), bytes / 5.2e6)) / nl;
+      if (best.nl == 1 || t < best_t) {
+        best_t = t;
+        best = MarchPlan{nl, yc};
+      }
+      if (yc >= p.n[1]) break;
+    }
+  }
+  return best;
+}
+
+template <int MODE>
+static hipError_t march2_m(const MarchParams& p, int scheme, int nl, const MarchBufs& b,
+                           long long n, int yc, hipStream_t stream) {
+  switch (nl) {
+    case 2: return march2_w<MODE, 2>(p, scheme, b, n, yc, stream);
+    case 4: return march2_w<MODE, 4>(p, scheme, b, n, yc, stream);
+    case 8: return march2_w<MODE, 8>(p, scheme, b, n, yc, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_march2(const MarchParams& p, int scheme, int mode, const MarchPlan& plan,
+                         const MarchBufs& b, long long n, hipStream_t stream) {
+  if (plan.yc < 1) return hipErrorInvalidValue;
+  switch (mode) {
+    case kFP64: return march2_m<kFP64>(p, scheme, plan.nl, b, n, plan.yc, stream);
+    case kFP32: return march2_m<kFP32>(p, scheme, plan.nl, b, n, plan.yc, stream);
+    case kSplit: return march2_m<kSplit>(p, scheme, plan.nl, b, n, plan.yc, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// ---- wall data of several steps: one thread per (step, face, face node); the
+// values k_xface and k_wall compute, before their rounding to the storage type.
+template <bool TAN, int V>
+__global__ void __launch_bounds__(256)
+    k_wall_data2(double* __restrict__ wx, double* __restrict__ wy, const KParams p,
+                 const long long n, const int nsteps) {
+  const int fx = p.bc[0] != 0 ? 2 * p.n[1] : 0, fy = p.bc[1] != 0 ? 2 * p.n[0] : 0;
+  const int per = fx + fy;
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  if (idx >= per * nsteps) return;
+  const int l = idx / per;
+  int e = idx - l * per;
+  const double t_n = step_time(n + l, p.dt);
+  const bool onx = e < fx;
+  if (!onx) e -= fx;
+  const int len = onx ? p.n[1] : p.n[0];
+  const int side = e / len, pos = e - side * len;
+  const int ax = onx ? 0 : 1;
+  const int i0 = onx ? (side ? p.n[0] - 1 : 0) : pos;
+  const int i1 = onx ? pos : (side ? p.n[1] - 1 : 0);
+  double x[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
+  x[0] = wall_coord(p, 0, i0);
+  x[1] = wall_coord(p, 1, i1);
+  const int want = side ? -1 : 1;
+  double val[q_of(2)];
+  wall_analytic<2, TAN, V>(p, x, t_n, [&](int k) { return p.cv[k][ax] == want; },
+                           [&](int) { return ax; }, val);
+  double* out = (onx ? wx : wy) + static_cast<long long>((l * 2 + side) * 3) * len + pos;
+  static_for<0, q_of(2)>([&](auto K) {
+    constexpr int k = decltype(K)::value;
+    constexpr int cx = vel_comp(2, k, 0), cy = vel_comp(2, k, 1);
+    if (onx) {
+      if (cx == want) out[static_cast<long long>(xface_slot(2, k)) * len] = val[k];
+    } else {
+      if (cy == want) out[static_cast<long long>(march_slot(k)) * len] = val[k];
+    }
+  });
+}
+
+long long wall_data2_x(const KParams& p) { return p.bc[0] != 0 ? 6LL * p.n[1] : 0; }
+long long wall_data2_y(const KParams& p) { return p.bc[1] != 0 ? 6LL * p.n[0] : 0; }
+
+template <bool TAN>
+static void wall_data2_t(unsigned blocks, const KParams& p, double* wx, double* wy, long long n,
+                         int nsteps, hipStream_t stream) {
+  const dim3 g(blocks), b(256);
+  switch (wall_variant(p)) {
+    case 0: hipLaunchKernelGGL((k_wall_data2<TAN, 0>), g, b, 0, stream, wx, wy, p, n, nsteps); break;
+    case 1: hipLaunchKernelGGL((k_wall_data2<TAN, 1>), g, b, 0, stream, wx, wy, p, n, nsteps); break;
+    case 2: hipLaunchKernelGGL((k_wall_data2<TAN, 2>), g, b, 0, stream, wx, wy, p, n, nsteps); break;
+    default: hipLaunchKernelGGL((k_wall_data2<TAN, 3>), g, b, 0, stream, wx, wy, p, n, nsteps);
+  }
+}
+
+hipError_t launch_wall_data2(const KParams& p, double* wx, double* wy, long long n, int nsteps,
+                             hipStream_t stream) {
+  const long long per = (wall_data2_x(p) + wall_data2_y(p)) / 3;
+  const long long total = per * nsteps;
+  if (total <= 0) return hipSuccess;
+  if (total > (1LL << 30)) return hipErrorInvalidValue;
+  const unsigned blocks = static_cast<unsigned>((total + 255) / 256);
+  if (p.wall_data) wall_data2_t<true>(blocks, p, wx, wy, n, nsteps, stream);
+  else wall_data2_t<false>(blocks, p, wx, wy, n, nsteps, stream);
+  return hipGetLastError();
+}
+
+}  // namespace lbm
