@@ -367,19 +367,20 @@ int lbm_stability_map(int d, int64_t count, const double* sigma_dev, const doubl
    params[i] (periodic axes; one stream for all; the allocator of each
    instance serves its buffers, that of instance 0 the batch tables).
    lbm_batch_step advances every instance by n steps.  d = 2 batches (every
-   instance with steps_per_pass = 2) go two steps per pass over a table of
-   (instance, x_1 tile, chunk of rows) tiles, in one of two launch forms:
-     LBM_BATCH_PER_PAIR   one launch per pair of steps over every tile of every
+   instance with steps_per_pass = 2) go eight, four or two steps per pass over
+   a table of (instance, x_1 tile, chunk of rows) tiles, in one of two launch
+   forms:
+     LBM_BATCH_PER_PAIR   one launch per pass over every tile of every
                           instance (default);
-     LBM_BATCH_RESIDENT   one launch for all the pairs of the call, one block
-                          per instance: the block advances its instance pair
-                          after pair over the instance's tiles, so the
-                          per-instance barrier between pairs is the block's
+     LBM_BATCH_RESIDENT   one launch for all the passes of the call, one block
+                          per instance: the block advances its instance pass
+                          after pass over the instance's tiles, so the
+                          per-instance barrier between passes is the block's
                           own barrier and no block waits for another.
    Odd remainders, and batches without pairs, take one launch per step over a
    table of (instance, row) tiles.  Both forms give bitwise the same states.
    lbm_batch_set_launch(b, form, ychunk) selects the form and the rows per tile
-   (8..64, 0 = 64 halved down to 8 while there are fewer than four tiles per
+   (8..64, 0 = 64 halved down to 8 while there are fewer than eight tiles per
    CU); LBM_EUNSUPPORTED for batches without pairs.
    lbm_batch_tune times every launch the batch can use over trial_steps steps
    (the single-step block shapes 64x4, 128x2, 256x1; with pairs both forms at

@@ -572,6 +572,22 @@ int lbm_set_initial(lbm_handle* h, const double* phi0_dev, const double* grad_ph
 
 namespace {
 
+// lbm_moments' scalars from the reduced sums of a handle's state
+void scalar_moments(const lbm_handle* h, uint32_t what, const double* acc, double* scalars_host) {
+  const double nan = std::numeric_limits<double>::quiet_NaN();
+  const bool sums = what & LBM_MOM_SUMS;
+  const bool err = (what & LBM_MOM_RMSE) && h->kp.field.kind != kFieldNone;
+  const bool ent = (what & LBM_MOM_ENTROPY) && (split_mode(h->precision) || h->kp.s != 1.0);
+  scalars_host[0] = sums ? acc[0] : nan;
+  scalars_host[1] = sums ? acc[1] : nan;
+  scalars_host[2] = err ? acc[2] : nan;
+  scalars_host[3] = ent ? acc[3] : nan;
+  scalars_host[4] = sums ? acc[4] : nan;
+  scalars_host[5] = sums ? acc[5] : nan;
+  scalars_host[6] = err ? std::sqrt(acc[2] / static_cast<double>(h->nodes)) : nan;
+  scalars_host[7] = static_cast<double>(h->step) * h->kp.dt;
+}
+
 // Checks shared by the stepping entry points.
 int step_checks(lbm_handle* h, int64_t n) {
   if (!h) return fail(nullptr, LBM_EINVAL, "null handle");
@@ -808,18 +824,7 @@ int lbm_moments(lbm_handle* h, uint32_t what, double* phi_out_dev, double* scala
   double acc[kNumAcc];
   int rc = sync_result(h, acc);
   if (rc != LBM_OK) return rc;
-  const double nan = std::numeric_limits<double>::quiet_NaN();
-  const bool sums = what & LBM_MOM_SUMS;
-  const bool err = (what & LBM_MOM_RMSE) && h->kp.field.kind != kFieldNone;
-  const bool ent = (what & LBM_MOM_ENTROPY) && (split_mode(h->precision) || h->kp.s != 1.0);
-  scalars_host[0] = sums ? acc[0] : nan;
-  scalars_host[1] = sums ? acc[1] : nan;
-  scalars_host[2] = err ? acc[2] : nan;
-  scalars_host[3] = ent ? acc[3] : nan;
-  scalars_host[4] = sums ? acc[4] : nan;
-  scalars_host[5] = sums ? acc[5] : nan;
-  scalars_host[6] = err ? std::sqrt(acc[2] / static_cast<double>(h->nodes)) : nan;
-  scalars_host[7] = static_cast<double>(h->step) * h->kp.dt;
+  scalar_moments(h, what, acc, scalars_host);
   return LBM_OK;
 }
 
@@ -1201,24 +1206,40 @@ struct lbm_batch {
   hipStream_t stream = nullptr;
   lbm_handle* owner = nullptr;  // instance 0: its allocator serves the tables
   KParams* d_kps = nullptr;
+  MarchParams* d_mps = nullptr;  // the same for the marching passes
   void** d_bufs = nullptr;
   BatchTile* d_tiles = nullptr;
   int max_tiles = 0, ntiles = 0;
   int tx = 64, ty = 4;
-  // two-step passes (d = 2, every instance with steps_per_pass = 2)
+  // marching passes (d = 2, every instance with steps_per_pass = 2)
   bool pairs = false;
   BatchTile2* d_tiles2 = nullptr;
   int ntiles2 = 0, tiles2_cap = 0;
-  int ychunk = 0;                // rows per tile of the two-step passes
-  int form = LBM_BATCH_PER_PAIR;  // launch form of the two-step passes
+  int ychunk = 0;                // rows per tile of the marching passes
+  int form = LBM_BATCH_PER_PAIR;  // launch form of the marching passes
   int* d_first = nullptr;        // resident form: first tile of each instance (count + 1)
   int* d_order = nullptr;        // resident form: instances, largest first
+  // whole-batch initialisation and moments, allocated at their first use
+  BatchBlock* d_blocks = nullptr;
+  int nblocks = 0;
+  int* d_bfirst = nullptr;       // first block of each instance (count + 1)
+  long long* d_offset = nullptr;  // first element of each instance's phi0
+  double* d_bpartial = nullptr;  // nblocks x kNumAcc
+  double* d_bresult = nullptr;   // count x kNumAcc
   int cur = 0;
   int64_t step = 0;
   std::string err;
 };
 
 namespace {
+
+void batch_free_tables(lbm_batch* b) {
+  if (!b->owner) return;
+  void* tables[] = {b->d_kps,    b->d_mps,    b->d_bufs,     b->d_tiles,   b->d_tiles2, b->d_first,
+                    b->d_order,  b->d_blocks, b->d_bfirst,   b->d_offset,  b->d_bpartial,
+                    b->d_bresult};
+  for (void* t : tables) dev_free(b->owner, t);
+}
 
 int bfail(lbm_batch* b, int code, const std::string& msg) {
   if (b)
@@ -1243,9 +1264,10 @@ int batch_tiles(lbm_batch* b, int tx, int ty) {
   return LBM_OK;
 }
 
-// Tile table of the two-step passes (d = 2): every instance cut into x_1
-// tiles of the pass's width and chunks of yc rows; yc = 0 picks 64 rows,
-// halved (down to 8) while the table has fewer than four tiles per CU.  Also
+// Tile table of the marching passes (d = 2): every instance cut into x_1
+// tiles of the pass's width and chunks of yc rows; yc = 0 picks 64 rows (the
+// fewest rows computed twice), halved (down to 8) while the table has fewer than
+// two tiles per SIMD.  Also
 // each instance's first tile and the instances ordered by size, largest
 // first (resident form).  The tables are allocated for the largest table
 // (8 rows) on the first call.
@@ -1253,7 +1275,7 @@ int batch_pair_tiles(lbm_batch* b, int yc) {
   bool all = b->d == 2;
   for (lbm_handle* h : b->inst) all = all && h->steps_per_pass == 2;
   if (!all) return LBM_OK;
-  const int tw = batch_pair_tile_width(b->precision);
+  const int tw = kBatchTileWidth;
   auto count = [&](int c) {
     long long n = 0;
     for (lbm_handle* h : b->inst)
@@ -1262,7 +1284,7 @@ int batch_pair_tiles(lbm_batch* b, int yc) {
   };
   if (yc == 0) {
     yc = 64;
-    while (yc > 8 && count(yc) < 4 * device_cus()) yc /= 2;
+    while (yc > 8 && count(yc) < 8 * device_cus()) yc /= 2;
   }
   if (yc < 8 || yc > 64) return bfail(b, LBM_EINVAL, "row chunk must be in 8..64");
   const long long cap = count(8);
@@ -1309,19 +1331,80 @@ int batch_pair_tiles(lbm_batch* b, int yc) {
 
 int batch_upload(lbm_batch* b) {
   std::vector<KParams> kps(b->inst.size());
+  std::vector<MarchParams> mps(b->inst.size());
   std::vector<void*> bufs(2 * b->inst.size());
   for (size_t i = 0; i < b->inst.size(); ++i) {
     kps[i] = b->inst[i]->kp;
+    if (b->d == 2) mps[i] = march_params(kps[i]);
     bufs[2 * i] = b->inst[i]->buf[0];
     bufs[2 * i + 1] = b->inst[i]->buf[1];
   }
   hipError_t e = hipMemcpyAsync(b->d_kps, kps.data(), sizeof(KParams) * kps.size(),
                                 hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess && b->d == 2)
+    e = hipMemcpyAsync(b->d_mps, mps.data(), sizeof(MarchParams) * mps.size(),
+                       hipMemcpyHostToDevice, b->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(b->d_bufs, bufs.data(), sizeof(void*) * bufs.size(), hipMemcpyHostToDevice,
                        b->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) return bfail(b, LBM_EDEVICE, std::string("table upload: ") + hipGetErrorString(e));
+  return LBM_OK;
+}
+
+// Tables of the whole-batch initialisation and moments: each instance is cut into
+// the blocks its own reduction uses (at most kRedBlocks of kRedThreads nodes).
+int batch_blocks(lbm_batch* b) {
+  if (b->d_bresult) return LBM_OK;
+  const size_t cnt = b->inst.size();
+  std::vector<BatchBlock> blocks;
+  std::vector<int> first(cnt + 1, 0);
+  std::vector<long long> offset(cnt, 0);
+  long long off = 0;
+  for (size_t i = 0; i < cnt; ++i) {
+    first[i] = static_cast<int>(blocks.size());
+    offset[i] = off;
+    off += b->inst[i]->nodes;
+    const int64_t nb =
+        std::min<int64_t>(kRedBlocks, (b->inst[i]->nodes + kRedThreads - 1) / kRedThreads);
+    for (int k = 0; k < nb; ++k) blocks.push_back(BatchBlock{static_cast<int>(i), k});
+  }
+  first[cnt] = static_cast<int>(blocks.size());
+  if (!b->d_blocks) {
+    b->d_blocks = static_cast<BatchBlock*>(dev_alloc(b->owner, sizeof(BatchBlock) * blocks.size()));
+    b->nblocks = static_cast<int>(blocks.size());
+  }
+  if (!b->d_bfirst) b->d_bfirst = static_cast<int*>(dev_alloc(b->owner, sizeof(int) * (cnt + 1)));
+  if (!b->d_offset) b->d_offset = static_cast<long long*>(dev_alloc(b->owner, sizeof(long long) * cnt));
+  if (!b->d_bpartial)
+    b->d_bpartial =
+        static_cast<double*>(dev_alloc(b->owner, sizeof(double) * kNumAcc * blocks.size()));
+  if (!b->d_blocks || !b->d_bfirst || !b->d_offset || !b->d_bpartial)
+    return bfail(b, LBM_ENOMEM, "batch reduction tables");
+  hipError_t e = hipMemcpyAsync(b->d_blocks, blocks.data(), sizeof(BatchBlock) * blocks.size(),
+                                hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(b->d_bfirst, first.data(), sizeof(int) * first.size(),
+                       hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(b->d_offset, offset.data(), sizeof(long long) * cnt, hipMemcpyHostToDevice,
+                       b->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+  if (e != hipSuccess)
+    return bfail(b, LBM_EDEVICE, std::string("table upload: ") + hipGetErrorString(e));
+  b->d_bresult = static_cast<double*>(dev_alloc(b->owner, sizeof(double) * kNumAcc * cnt));
+  if (!b->d_bresult) return bfail(b, LBM_ENOMEM, "batch reduction tables");
+  return LBM_OK;
+}
+
+// the results of a whole-batch reduction, count x kNumAcc
+int batch_results(lbm_batch* b, std::vector<double>* host) {
+  host->resize(kNumAcc * b->inst.size());
+  hipError_t e = hipMemcpyAsync(host->data(), b->d_bresult, sizeof(double) * host->size(),
+                                hipMemcpyDeviceToHost, b->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+  if (e != hipSuccess)
+    return bfail(b, LBM_EDEVICE, std::string("batch reduction: ") + hipGetErrorString(e));
   return LBM_OK;
 }
 
@@ -1425,29 +1508,28 @@ void tune_cache_put(const std::string& key, const TuneEntry& e) {
 int batch_run(lbm_batch* b, int64_t n, bool allow_pairs = true) {
   if (n <= 0) return LBM_OK;
   int64_t done = 0;
-  if (allow_pairs && b->pairs && b->form == LBM_BATCH_RESIDENT && n >= 2) {
-    // every pair of steps of the call in one launch, one block per instance
-    for (int64_t np = n / 2; np > 0;) {
-      const int chunk = static_cast<int>(std::min<int64_t>(np, 1 << 30));
-      hipError_t e = launch_batch_resident(b->d_kps, b->d_bufs, b->d_tiles2, b->d_first,
+  if (allow_pairs && b->pairs && b->form == LBM_BATCH_RESIDENT) {
+    // every pass of the call in one launch, one block per instance
+    while (n - done >= 2) {
+      const int chunk = static_cast<int>(std::min<int64_t>((n - done) / 2 * 2, 1 << 30));
+      hipError_t e = launch_batch_resident(b->d_mps, b->d_bufs, b->d_tiles2, b->d_first,
                                            b->d_order, static_cast<int>(b->inst.size()),
                                            b->precision, b->cur, chunk, b->stream);
       if (e != hipSuccess)
         return bfail(b, LBM_EDEVICE, std::string("resident batch pass: ") + hipGetErrorString(e));
-      b->cur = (b->cur + chunk) & 1;
-      np -= chunk;
-      done += 2 * static_cast<int64_t>(chunk);
+      b->cur = b->cur ^ march_pass_parity(chunk);
+      done += chunk;
     }
   } else if (allow_pairs && b->pairs) {
-    for (int64_t np = n / 2; np > 0;) {
-      const int chunk = static_cast<int>(std::min<int64_t>(np, 1 << 20));
-      hipError_t e = launch_batch_pair(b->d_kps, b->d_bufs, b->d_tiles2, b->ntiles2,
-                                       b->precision, b->cur, chunk, b->stream);
-      if (e != hipSuccess)
-        return bfail(b, LBM_EDEVICE, std::string("batch two-step pass: ") + hipGetErrorString(e));
-      b->cur = (b->cur + chunk) & 1;
-      np -= chunk;
-      done += 2 * static_cast<int64_t>(chunk);
+    for (int nl = kMarchMaxSteps; nl >= 2; nl /= 2) {
+      while (n - done >= nl) {
+        hipError_t e = launch_batch_march(b->d_mps, b->d_bufs, b->d_tiles2, b->ntiles2,
+                                          b->precision, nl, b->cur, b->stream);
+        if (e != hipSuccess)
+          return bfail(b, LBM_EDEVICE, std::string("batch marching pass: ") + hipGetErrorString(e));
+        b->cur ^= 1;
+        done += nl;
+      }
     }
   }
   while (done < n) {
@@ -1483,14 +1565,7 @@ int lbm_batch_create(int count, int d, const int64_t* dims, const double* tau,
   auto abort_create = [&](int rc) {
     std::string msg = g_create_error;
     for (lbm_handle* h : b->inst) lbm_destroy(h);
-    if (b->owner) {
-      dev_free(b->owner, b->d_kps);
-      dev_free(b->owner, b->d_bufs);
-      dev_free(b->owner, b->d_tiles);
-      dev_free(b->owner, b->d_tiles2);
-      dev_free(b->owner, b->d_first);
-      dev_free(b->owner, b->d_order);
-    }
+    batch_free_tables(b);
     delete b;
     g_create_error = msg;
     return rc;
@@ -1518,7 +1593,8 @@ int lbm_batch_create(int count, int d, const int64_t* dims, const double* tau,
   b->d_kps = static_cast<KParams*>(dev_alloc(b->owner, sizeof(KParams) * count));
   b->d_bufs = static_cast<void**>(dev_alloc(b->owner, sizeof(void*) * 2 * count));
   b->d_tiles = static_cast<BatchTile*>(dev_alloc(b->owner, sizeof(BatchTile) * b->max_tiles));
-  if (!b->d_kps || !b->d_bufs || !b->d_tiles)
+  if (d == 2) b->d_mps = static_cast<MarchParams*>(dev_alloc(b->owner, sizeof(MarchParams) * count));
+  if (!b->d_kps || !b->d_bufs || !b->d_tiles || (d == 2 && !b->d_mps))
     return abort_create(bfail(nullptr, LBM_ENOMEM, "batch tables"));
   int rc = batch_upload(b);
   if (rc == LBM_OK) rc = batch_tiles(b, 64, 4);
@@ -1533,15 +1609,38 @@ int lbm_batch_create(int count, int d, const int64_t* dims, const double* tau,
 
 int lbm_batch_set_initial(lbm_batch* b, const double* phi0_dev, const double* grad_dev) {
   if (!b || !phi0_dev) return bfail(b, LBM_EINVAL, "null argument");
-  int64_t off = 0;
+  int rc = batch_blocks(b);
+  if (rc != LBM_OK) return rc;
+  const int count = static_cast<int>(b->inst.size());
+  hipError_t e = hipSuccess;
+  if (b->precision == LBM_FP32) {
+    // the mean of every phi0 (compute_reference), in one reduction
+    e = launch_batch_sum_phi0(b->d, b->d_kps, b->d_blocks, b->nblocks, b->d_bfirst, count,
+                              b->d_offset, phi0_dev, b->d_bpartial, b->d_bresult, b->stream);
+    if (e != hipSuccess)
+      return bfail(b, LBM_EDEVICE, std::string("sum of phi0: ") + hipGetErrorString(e));
+    std::vector<double> sums;
+    rc = batch_results(b, &sums);
+    if (rc != LBM_OK) return rc;
+    for (int i = 0; i < count; ++i)
+      b->inst[i]->kp.phi_ref = sums[kNumAcc * i] / static_cast<double>(b->inst[i]->nodes);
+    rc = batch_upload(b);
+    if (rc != LBM_OK) return rc;
+  }
+  e = launch_batch_init(b->d, b->d_kps, b->d_bufs, b->d_blocks, b->nblocks, b->d_offset,
+                        b->precision, phi0_dev, grad_dev, b->stream);
+  if (e != hipSuccess)
+    return bfail(b, LBM_EDEVICE, std::string("initialisation kernel: ") + hipGetErrorString(e));
   for (lbm_handle* h : b->inst) {
-    int rc = lbm_set_initial(h, phi0_dev + off, grad_dev ? grad_dev + off * b->d : nullptr);
-    if (rc != LBM_OK) return bfail(b, rc, h->err);
-    off += h->nodes;
+    h->cur = 0;
+    h->step = 0;
+    h->last_check = 0;
+    h->initialised = true;
+    h->init_kind = (h->kp.K == 1) ? 4 : (grad_dev ? 3 : 2);
   }
   b->cur = 0;
   b->step = 0;
-  return batch_upload(b);  // float32 references may have changed
+  return LBM_OK;
 }
 
 int lbm_batch_step(lbm_batch* b, int64_t n) {
@@ -1688,11 +1787,22 @@ lbm_handle* lbm_batch_instance(const lbm_batch* b, int i) {
 
 int lbm_batch_moments(lbm_batch* b, double* scalars_host) {
   if (!b || !scalars_host) return bfail(b, LBM_EINVAL, "null argument");
-  for (size_t i = 0; i < b->inst.size(); ++i) {
-    int rc = lbm_moments(b->inst[i], LBM_MOM_SUMS | LBM_MOM_RMSE | LBM_MOM_ENTROPY, nullptr,
-                         scalars_host + i * LBM_NSCALARS);
-    if (rc != LBM_OK) return bfail(b, rc, b->inst[i]->err);
-  }
+  for (lbm_handle* h : b->inst)
+    if (!h->initialised) return bfail(b, LBM_EINVAL, "no initial state");
+  int rc = batch_blocks(b);
+  if (rc != LBM_OK) return rc;
+  constexpr uint32_t what = LBM_MOM_SUMS | LBM_MOM_RMSE | LBM_MOM_ENTROPY;
+  hipError_t e = launch_batch_moments(b->d, b->d_kps, b->d_bufs, b->d_blocks, b->nblocks,
+                                      b->d_bfirst, static_cast<int>(b->inst.size()), b->precision,
+                                      b->cur, b->step, b->d_bpartial, b->d_bresult, what,
+                                      b->stream);
+  if (e != hipSuccess)
+    return bfail(b, LBM_EDEVICE, std::string("moments kernel: ") + hipGetErrorString(e));
+  std::vector<double> acc;
+  rc = batch_results(b, &acc);
+  if (rc != LBM_OK) return rc;
+  for (size_t i = 0; i < b->inst.size(); ++i)
+    scalar_moments(b->inst[i], what, &acc[kNumAcc * i], scalars_host + i * LBM_NSCALARS);
   return LBM_OK;
 }
 
@@ -1703,14 +1813,7 @@ const char* lbm_batch_last_error(const lbm_batch* b) {
 int lbm_batch_destroy(lbm_batch* b) {
   if (!b) return LBM_OK;
   (void)hipStreamSynchronize(b->stream);
-  if (b->owner) {
-    dev_free(b->owner, b->d_kps);
-    dev_free(b->owner, b->d_bufs);
-    dev_free(b->owner, b->d_tiles);
-    dev_free(b->owner, b->d_tiles2);
-    dev_free(b->owner, b->d_first);
-    dev_free(b->owner, b->d_order);
-  }
+  batch_free_tables(b);
   for (lbm_handle* h : b->inst) lbm_destroy(h);
   delete b;
   return LBM_OK;

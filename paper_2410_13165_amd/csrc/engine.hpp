@@ -125,6 +125,13 @@ long long wall_data2_y(const KParams& p);
 hipError_t launch_wall_data2(const KParams& p, double* wx, double* wy, long long n, int nsteps,
                              hipStream_t stream);
 
+// One block of a batched reduction or initialisation: block `block` of the
+// kRedBlocks that cover instance inst.
+struct BatchBlock {
+  int inst;
+  int block;
+};
+
 // One block of a batched launch: rows row0 .. row0 + blockDim.y - 1 of an
 // instance.
 struct BatchTile {
@@ -132,7 +139,7 @@ struct BatchTile {
   int row0;
 };
 
-// Tile of a batched two-step pass (d = 2): instance, first x_1 node, output
+// Tile of a batched marching pass (d = 2): instance, first x_1 node, output
 // rows y0 .. y1 - 1.
 struct BatchTile2 {
   int inst;
@@ -198,26 +205,48 @@ hipError_t launch_zero_count(unsigned* count, hipStream_t stream);
 hipError_t launch_sum_phi0(const KParams& p, const double* arr, double* partial,
                            double* out, hipStream_t stream);
 
+// Whole-batch forms of launch_moments (scalars only), launch_sum_phi0 and
+// launch_init: nblocks BatchBlocks, instance i's at first[i] .. first[i + 1); its
+// kNumAcc results go to out[i * kNumAcc ..].  offset[i]: instance i's first
+// element of the concatenated phi0 (d offset[i] of the gradients).
+hipError_t launch_batch_moments(int d, const KParams* kps, void* const* bufs,
+                                const BatchBlock* blocks, int nblocks, const int* first,
+                                int count, int mode, int cur, long long n, double* partial,
+                                double* out, unsigned what, hipStream_t stream);
+hipError_t launch_batch_sum_phi0(int d, const KParams* kps, const BatchBlock* blocks, int nblocks,
+                                 const int* first, int count, const long long* offset,
+                                 const double* phi0, double* partial, double* out,
+                                 hipStream_t stream);
+hipError_t launch_batch_init(int d, const KParams* kps, void* const* bufs,
+                             const BatchBlock* blocks, int nblocks, const long long* offset,
+                             int mode, const double* phi0, const double* grad0,
+                             hipStream_t stream);
+
 // nsteps steps of every instance of a batch (periodic lattices of one d and
 // precision), one launch per step over the tile table.
 hipError_t launch_batch(int d, const KParams* kps, void* const* bufs, const BatchTile* tiles,
                         int ntiles, int tx, int ty, int mode, int cur, int nsteps,
                         hipStream_t stream);
 
-// npairs two-step passes of every instance of a d = 2 batch (float32 or
-// float64), one launch per pair over the BatchTile2 table.
-hipError_t launch_batch_pair(const KParams* kps, void* const* bufs, const BatchTile2* tiles,
-                             int ntiles, int mode, int cur, int npairs, hipStream_t stream);
-// x_1 width of the tiles of launch_batch_pair
-int batch_pair_tile_width(int mode);
+// One marching pass of nl (2, 4 or 8) steps of every instance of a d = 2 batch
+// (float32 or float64) over the BatchTile2 table, whose tiles are kBatchTileWidth
+// wide.
+constexpr int kBatchTileWidth = march_width(kMarchMaxSteps);
+hipError_t launch_batch_march(const MarchParams* mps, void* const* bufs, const BatchTile2* tiles,
+                              int ntiles, int mode, int nl, int cur, hipStream_t stream);
 
-// npairs two-step passes of every instance of a d = 2 batch in one launch:
-// block b advances instance order[b] (largest first) through all the pairs,
-// over its tiles tiles[first[i] .. first[i + 1]) of launch_batch_pair's table;
-// the instances never share a block, so no block waits for another.
-hipError_t launch_batch_resident(const KParams* kps, void* const* bufs, const BatchTile2* tiles,
-                                 const int* first, const int* order, int count, int mode, int cur,
-                                 int npairs, hipStream_t stream);
+// nsteps (even) steps of every instance of a d = 2 batch in one launch: block b
+// advances instance order[b] (largest first) through all the passes, its
+// wavefronts sharing the instance's tiles tiles[first[i] .. first[i + 1]); the
+// instances never share a block, so no block waits for another.
+hipError_t launch_batch_resident(const MarchParams* mps, void* const* bufs,
+                                 const BatchTile2* tiles, const int* first, const int* order,
+                                 int count, int mode, int cur, int nsteps, hipStream_t stream);
+// Parity of the number of passes of nsteps (even) steps: as many of 8 as fit,
+// then one of 4 and one of 2.
+inline int march_pass_parity(long long nsteps) {
+  return static_cast<int>((nsteps / 8 + nsteps % 8 / 4 + nsteps % 4 / 2) & 1);
+}
 
 // Adjoint step lambda^{n+1} -> lambda^n (adjoint.hip).  g: forward state at
 // step n (nullable); when given, per-block partial sums of

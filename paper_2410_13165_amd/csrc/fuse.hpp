@@ -150,31 +150,4 @@ __device__ __forceinline__ int adj_slot(int it) {
   else return 33 + i;
 }
 
-// ---- d = 2: 1-D tiles along x_1 marching along x_2 (the same plan with
-// planes replaced by rows).  The c_2 classes of D2Q9 have three members each.
-template <class T, bool HALF>
-struct FuseShape2 {
-  // 256 outputs (lattice sizes are often multiples); threads 0 and 1 also
-  // take the two halo nodes of the step-1 row
-  static constexpr int TX = 256, NT = 256, SLOTS = HALF ? 21 : 18;
-};
-
-constexpr int cy_index(int k) {
-  const int cy = vel_comp(2, k, 1);
-  int idx = 0;
-  for (int m = 0; m < k; ++m)
-    if (vel_comp(2, m, 1) == cy) ++idx;
-  return idx;
-}
-
-template <bool HALF, int k>
-__device__ __forceinline__ int fuse_slot2(int it) {
-  constexpr int cy = vel_comp(2, k, 1);
-  constexpr int i = cy_index(k);
-  if constexpr (cy == 0) return 2 * i + (it & 1);
-  else if constexpr (cy == 1) return 6 + 3 * i + it % 3;
-  else if constexpr (HALF) return 15 + 2 * i + (it & 1);
-  else return 15 + i;
-}
-
 }  // namespace lbm

@@ -43,9 +43,8 @@
 
 namespace lbm {
 
-__global__ void __launch_bounds__(kRedThreads)
-    k_reduce_final(const double* __restrict__ partial, int nblocks, double* __restrict__ out) {
-  __shared__ double sh[kNumAcc * kRedThreads];
+__device__ __forceinline__ void reduce_final(const double* __restrict__ partial, int nblocks,
+                                             double* __restrict__ out, double* sh) {
   double acc[kNumAcc] = {0, 0, 0, 0, 0, 0};
   for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
 #pragma unroll
@@ -58,6 +57,42 @@ __global__ void __launch_bounds__(kRedThreads)
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int m = 0; m < kNumAcc; ++m) out[m] = acc[m];
+  }
+}
+
+__global__ void __launch_bounds__(kRedThreads)
+    k_reduce_final(const double* __restrict__ partial, int nblocks, double* __restrict__ out) {
+  __shared__ double sh[kNumAcc * kRedThreads];
+  reduce_final(partial, nblocks, out, sh);
+}
+
+__global__ void __launch_bounds__(kRedThreads)
+    k_batch_reduce(const double* __restrict__ partial, const int* __restrict__ first,
+                   double* __restrict__ out) {
+  __shared__ double sh[kNumAcc * kRedThreads];
+  const int b0 = first[blockIdx.x], b1 = first[blockIdx.x + 1];
+  reduce_final(partial + static_cast<long long>(b0) * kNumAcc, b1 - b0, out + blockIdx.x * kNumAcc,
+               sh);
+}
+
+// Sum of phi0 over every instance of a batch (arrays one after another), cut as
+// k_sum_phi0 cuts each.
+__global__ void __launch_bounds__(kRedThreads)
+    k_batch_sum_phi0(const KParams* __restrict__ kps, const BatchBlock* __restrict__ blocks,
+                     const long long* __restrict__ offset, const double* __restrict__ phi0,
+                     double* __restrict__ partial) {
+  __shared__ double sh[kNumAcc * kRedThreads];
+  double acc[kNumAcc] = {0, 0, 0, 0, 0, 0};
+  const BatchBlock b = blocks[blockIdx.x];
+  const int nodes = kps[b.inst].nodes;
+  const double* arr = phi0 + offset[b.inst];
+  for (int node = b.block * kRedThreads + threadIdx.x; node < nodes;
+       node += kRedBlocks * kRedThreads)
+    acc[0] += arr[node];
+  block_reduce(acc, sh);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int m = 0; m < kNumAcc; ++m) partial[blockIdx.x * kNumAcc + m] = acc[m];
   }
 }
 
@@ -336,6 +371,16 @@ static hipError_t moments_d(const KParams& p, int mode, const void* f, const dou
                             long long n, double* phi_out, double* partial, double* out,
                             unsigned what, hipStream_t stream) {
   const double t_n = static_cast<double>(n) * p.dt;
+  if (!(what & (kMomSums | kMomRmse | kMomEntropy))) {
+    const dim3 g(grid_for(p.nodes, 256)), b(256);
+    if (mode == kFP64)
+      hipLaunchKernelGGL((k_phi<D, double>), g, b, 0, stream, static_cast<const double*>(f), phi,
+                         p, mode, t_n, phi_out);
+    else
+      hipLaunchKernelGGL((k_phi<D, float>), g, b, 0, stream, static_cast<const float*>(f), phi, p,
+                         mode, t_n, phi_out);
+    return hipGetLastError();
+  }
   const dim3 block(kRedThreads), grid(kRedBlocks);
   if (mode == kFP64)
     hipLaunchKernelGGL((k_moments<D, double>), grid, block, 0, stream,
@@ -345,7 +390,6 @@ static hipError_t moments_d(const KParams& p, int mode, const void* f, const dou
                        static_cast<const float*>(f), phi, p, mode, t_n, phi_out, partial, what);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (!(what & (kMomSums | kMomRmse | kMomEntropy))) return hipSuccess;
   hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kRedThreads), 0, stream, partial, kRedBlocks,
                      out);
   return hipGetLastError();
@@ -414,6 +458,80 @@ hipError_t launch_sum_phi0(const KParams& p, const double* arr, double* partial,
   }
 }
 
+static hipError_t batch_reduce(const double* partial, const int* first, int count, double* out,
+                               hipStream_t stream) {
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_batch_reduce, dim3(count), dim3(kRedThreads), 0, stream, partial, first,
+                     out);
+  return hipGetLastError();
+}
+
+template <int D>
+static void batch_moments_d(const KParams* kps, void* const* bufs, const BatchBlock* blocks,
+                            int nblocks, int mode, int cur, long long n, double* partial,
+                            unsigned what, hipStream_t stream) {
+  const dim3 g(nblocks), b(kRedThreads);
+  if (mode == kFP64)
+    hipLaunchKernelGGL((k_batch_moments<D, double>), g, b, 0, stream, kps, bufs, blocks, cur, mode,
+                       n, partial, what);
+  else
+    hipLaunchKernelGGL((k_batch_moments<D, float>), g, b, 0, stream, kps, bufs, blocks, cur, mode,
+                       n, partial, what);
+}
+
+hipError_t launch_batch_moments(int d, const KParams* kps, void* const* bufs,
+                                const BatchBlock* blocks, int nblocks, const int* first,
+                                int count, int mode, int cur, long long n, double* partial,
+                                double* out, unsigned what, hipStream_t stream) {
+  switch (d) {
+    case 1: batch_moments_d<1>(kps, bufs, blocks, nblocks, mode, cur, n, partial, what, stream); break;
+    case 2: batch_moments_d<2>(kps, bufs, blocks, nblocks, mode, cur, n, partial, what, stream); break;
+    case 3: batch_moments_d<3>(kps, bufs, blocks, nblocks, mode, cur, n, partial, what, stream); break;
+    case 4: batch_moments_d<4>(kps, bufs, blocks, nblocks, mode, cur, n, partial, what, stream); break;
+    default: return hipErrorInvalidValue;
+  }
+  return batch_reduce(partial, first, count, out, stream);
+}
+
+hipError_t launch_batch_sum_phi0(int d, const KParams* kps, const BatchBlock* blocks, int nblocks,
+                                 const int* first, int count, const long long* offset,
+                                 const double* phi0, double* partial, double* out,
+                                 hipStream_t stream) {
+  const dim3 g(nblocks), b(kRedThreads);
+  if (d < 1 || d > kMaxDim) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_batch_sum_phi0, g, b, 0, stream, kps, blocks, offset, phi0, partial);
+  return batch_reduce(partial, first, count, out, stream);
+}
+
+template <int D>
+static hipError_t batch_init_d(const KParams* kps, void* const* bufs, const BatchBlock* blocks,
+                               int nblocks, const long long* offset, int mode, const double* phi0,
+                               const double* grad0, hipStream_t stream) {
+  const dim3 g(nblocks), b(256);
+  const BatchInit bi{kps, bufs, blocks, offset};
+  if (mode == kFP64)
+    hipLaunchKernelGGL((k_init<D, double, true>), g, b, 0, stream, nullptr, nullptr, phi0, grad0,
+                       bi, mode);
+  else
+    hipLaunchKernelGGL((k_init<D, float, true>), g, b, 0, stream, nullptr, nullptr, phi0, grad0,
+                       bi, mode);
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_init(int d, const KParams* kps, void* const* bufs,
+                             const BatchBlock* blocks, int nblocks, const long long* offset,
+                             int mode, const double* phi0, const double* grad0,
+                             hipStream_t stream) {
+  switch (d) {
+    case 1: return batch_init_d<1>(kps, bufs, blocks, nblocks, offset, mode, phi0, grad0, stream);
+    case 2: return batch_init_d<2>(kps, bufs, blocks, nblocks, offset, mode, phi0, grad0, stream);
+    case 3: return batch_init_d<3>(kps, bufs, blocks, nblocks, offset, mode, phi0, grad0, stream);
+    case 4: return batch_init_d<4>(kps, bufs, blocks, nblocks, offset, mode, phi0, grad0, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 template <int D>
 static hipError_t batch_d(const KParams* kps, void* const* bufs, const BatchTile* tiles,
                           int ntiles, int tx, int ty, int mode, int cur, int nsteps,
@@ -431,72 +549,6 @@ static hipError_t batch_d(const KParams* kps, void* const* bufs, const BatchTile
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
-}
-
-template <class T>
-static hipError_t batch_pair_t(const KParams* kps, void* const* bufs, const BatchTile2* tiles,
-                               int ntiles, int cur, int npairs, hipStream_t stream) {
-  using S = FuseShape2<T, false>;
-  constexpr size_t lds = sizeof(T) * S::SLOTS * (S::TX + 2);
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fused2_d2_batch<T>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       static_cast<int>(lds));
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  for (int i = 0; i < npairs; ++i) {
-    // a two-step pass reads buffer c and writes buffer 1 - c, as one step does
-    const int c = (cur + i) & 1;
-    hipLaunchKernelGGL((k_fused2_d2_batch<T>), dim3(ntiles), dim3(S::NT), lds, stream, kps,
-                       reinterpret_cast<T* const*>(bufs), tiles, c);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
-hipError_t launch_batch_pair(const KParams* kps, void* const* bufs, const BatchTile2* tiles,
-                             int ntiles, int mode, int cur, int npairs, hipStream_t stream) {
-  if (mode == kFP64) return batch_pair_t<double>(kps, bufs, tiles, ntiles, cur, npairs, stream);
-  if (mode == kFP32) return batch_pair_t<float>(kps, bufs, tiles, ntiles, cur, npairs, stream);
-  return hipErrorInvalidValue;
-}
-
-template <class T>
-static hipError_t batch_resident_t(const KParams* kps, void* const* bufs, const BatchTile2* tiles,
-                                   const int* first, const int* order, int count, int cur,
-                                   int npairs, hipStream_t stream) {
-  using S = FuseShape2<T, false>;
-  constexpr size_t lds = sizeof(T) * S::SLOTS * (S::TX + 2);
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fused2_d2_resident<T>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       static_cast<int>(lds));
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  hipLaunchKernelGGL((k_fused2_d2_resident<T>), dim3(static_cast<unsigned>(count)), dim3(S::NT),
-                     lds, stream, kps, reinterpret_cast<T* const*>(bufs), tiles, first, order,
-                     npairs, cur);
-  return hipGetLastError();
-}
-
-hipError_t launch_batch_resident(const KParams* kps, void* const* bufs, const BatchTile2* tiles,
-                                 const int* first, const int* order, int count, int mode, int cur,
-                                 int npairs, hipStream_t stream) {
-  if (npairs <= 0 || count <= 0) return hipSuccess;
-  if (mode == kFP64)
-    return batch_resident_t<double>(kps, bufs, tiles, first, order, count, cur, npairs, stream);
-  if (mode == kFP32)
-    return batch_resident_t<float>(kps, bufs, tiles, first, order, count, cur, npairs, stream);
-  return hipErrorInvalidValue;
-}
-
-int batch_pair_tile_width(int mode) {
-  return mode == kFP64 ? FuseShape2<double, false>::TX : FuseShape2<float, false>::TX;
 }
 
 hipError_t launch_batch(int d, const KParams* kps, void* const* bufs, const BatchTile* tiles,

@@ -130,6 +130,13 @@ __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e) {
   e = (a - (s - bp)) + (b - bp);
 }
 
+// t_n as the host forms it, n dt rounded before anything is added to it (a
+// contraction of the two would differ from the single steps in the last bit)
+__device__ __forceinline__ double step_time(long long n, double dt) {
+#pragma clang fp contract(off)
+  return static_cast<double>(n) * dt;
+}
+
 // -------------------------------------------------- analytic field values ---
 
 // phi*(x, t) for the RMSE reference and the analytic initial state.
@@ -257,21 +264,31 @@ inline int wall_variant(const KParams& p) {
 //
 // wall_mode gives mode j's factor at the wall point (cos and sin of its phase,
 // or its exponential in C), wall_term the mode's contribution to population k,
-// wall_close the terms outside the mode sum.  These and the helpers below them
-// disable floating-point contraction: it works within one basic block, so with
-// it a wall value would depend on where a kernel's loops leave each product,
-// and the kernels that store wall values for later would differ in the last bit
-// from those that use them at once.
+// wall_close the terms outside the mode sum.
+// Products that a kernel's loops may leave inside or outside the basic block of
+// the sum they enter are rounded by themselves where several kernels must agree
+// on them (d <= 2, whose wall data of several steps come from a kernel of their
+// own): floating-point contraction works within one block, so left to itself it
+// would make the last bit of a wall value depend on the kernel.
+template <int D>
+__device__ __forceinline__ double wall_product(double a, double b) {
+  if constexpr (D <= 2) {
+#pragma clang fp contract(off)
+    const double r = a * b;
+    return r;
+  } else {
+    return a * b;
+  }
+}
 
 // t: t_{n+1} full-way, t_n half-way
 template <int D, int V>
 __device__ __forceinline__ void wall_mode(const KParams& p, const double (&x)[kMaxDim], double t,
                                           int j, double& C, double& S) {
-#pragma clang fp contract(off)
   const FieldDev& F = p.field;
   double ph = 0.0;
 #pragma unroll
-  for (int a = 0; a < D; ++a) ph += F.kvec[j][a] * (x[a] - p.u[a] * t);
+  for (int a = 0; a < D; ++a) ph += F.kvec[j][a] * (x[a] - wall_product<D>(p.u[a], t));
   if (wall_cos<V>(p)) {
     sincos(ph + F.phase[j], &S, &C);
   } else {
@@ -283,7 +300,6 @@ __device__ __forceinline__ void wall_mode(const KParams& p, const double (&x)[kM
 template <int D, bool TAN, int V, int k, class Axis>
 __device__ __forceinline__ double wall_term(const KParams& p, int j, double C, double S,
                                             Axis axis) {
-#pragma clang fp contract(off)
   const FieldDev& F = p.field;
   const double dt = p.dt;
   const double o2 = p.P >= 2 ? 1.0 : 0.0;
@@ -347,12 +363,11 @@ __device__ __forceinline__ double wall_term(const KParams& p, int j, double C, d
 
 template <int D, int V, int k>
 __device__ __forceinline__ double wall_close(const KParams& p, double v, double t_n) {
-#pragma clang fp contract(off)
-  if (wall_full<V>(p)) return p.omega[k] * (v + p.R * (t_n + p.dt));
+  if (wall_full<V>(p)) return p.omega[k] * (v + wall_product<D>(p.R, t_n + p.dt));
   constexpr int kb = opp_index(D, k);
   const double o2 = p.P >= 2 ? 1.0 : 0.0;
   const double wp = p.omega[k] + p.omega[kb];
-  return v + wp * p.R * t_n + o2 * wp * p.R * p.dt;
+  return v + wall_product<D>(wp * p.R, t_n) + wall_product<D>(o2 * wp * p.R, p.dt);
 }
 
 // Only the populations K0 <= k < K1 are evaluated; each val[k] is the same sum
@@ -385,22 +400,22 @@ __device__ __forceinline__ void wall_analytic(const KParams& p, const double (&x
 }
 
 // coordinate of axis a at index i
+template <int D>
 __device__ __forceinline__ double wall_coord(const KParams& p, int a, int i) {
-#pragma clang fp contract(off)
-  return p.origin[a] + (i + p.shift[a]) * p.dx;
+  return p.origin[a] + wall_product<D>(i + p.shift[a], p.dx);
 }
 
 // absolute post-collision population of a stored value: the float32 deviations
 // are taken from omega_k ref
+template <int D>
 __device__ __forceinline__ double wall_absolute(double stored, double omega, double ref) {
-#pragma clang fp contract(off)
-  return stored + omega * ref;
+  return stored + wall_product<D>(omega, ref);
 }
 
 // deviation of an absolute value v from weight * ref
+template <int D>
 __device__ __forceinline__ double wall_deviation(double v, double weight, double ref) {
-#pragma clang fp contract(off)
-  return v - weight * ref;
+  return v - wall_product<D>(weight, ref);
 }
 
 // Modes whose factors the half-way wall path of d = 3 keeps in registers
@@ -437,7 +452,7 @@ __device__ __forceinline__ void wall_values(A (&f)[q_of(D)], const KParams& p, c
                                             double t_n, double ref, FStarLocal fstar_local) {
   double x[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int a = 0; a < D; ++a) x[a] = wall_coord(p, a, r.i[a]);
+  for (int a = 0; a < D; ++a) x[a] = wall_coord<D>(p, a, r.i[a]);
   bool out[q_of(D)];
   static_for<0, q_of(D)>([&](auto K) {
     constexpr int k = decltype(K)::value;
@@ -470,7 +485,7 @@ __device__ __forceinline__ void wall_values(A (&f)[q_of(D)], const KParams& p, c
           if (j < p.field.nmodes)
             v += wall_term<D, TAN, V, k>(p, j, mc[j], ms[j], [&](int kk) { return ax[kk]; });
         v = wall_close<D, V, k>(p, v, t_n) - fstar_local(opp_index(D, k));
-        f[k] = static_cast<A>(wall_deviation(v, p.omega[k], ref));
+        f[k] = static_cast<A>(wall_deviation<D>(v, p.omega[k], ref));
       });
       return;
     }
@@ -496,7 +511,7 @@ __device__ __forceinline__ void wall_values(A (&f)[q_of(D)], const KParams& p, c
       if (!out[k]) return;
       double v = val[k];
       if (half) v -= fstar_local(opp_index(D, k));
-      f[k] = static_cast<A>(wall_deviation(v, p.omega[k], ref));
+      f[k] = static_cast<A>(wall_deviation<D>(v, p.omega[k], ref));
     });
   });
 }
@@ -521,13 +536,13 @@ __global__ void __launch_bounds__(256)
   const int side = idx >= p.rows ? 1 : 0;
   const int row = idx - side * p.rows;
   double x[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
-  x[0] = wall_coord(p, 0, side ? p.n[0] - 1 : 0);
+  x[0] = wall_coord<D>(p, 0, side ? p.n[0] - 1 : 0);
   int rr = row;
 #pragma unroll
   for (int a = 1; a < D; ++a) {
     const int ia = rr % p.n[a];
     rr /= p.n[a];
-    x[a] = wall_coord(p, a, ia);
+    x[a] = wall_coord<D>(p, a, ia);
   }
   const double ref = (mode == kFP32) ? p.phi_ref + p.R * (t_n + p.dt) : 0.0;
   const bool half = !wall_full<V>(p);
@@ -548,7 +563,7 @@ __global__ void __launch_bounds__(256)
       } else {
         constexpr int kb = opp_index(D, k);
         const double w = half ? p.omega[k] + p.omega[kb] : p.omega[k];
-        buf[k * ps + p.xoff + row] = static_cast<T>(wall_deviation(val[k], w, ref));
+        buf[k * ps + p.xoff + row] = static_cast<T>(wall_deviation<D>(val[k], w, ref));
       }
     }
   });
@@ -838,179 +853,6 @@ __global__ void __launch_bounds__((FuseFwdShape<T, HALF>::NT))
       }
     }
     __syncthreads();
-  }
-}
-
-// The two-step pass for d = 2: a block owns TX nodes of x_1 and a chunk of
-// x_2 rows and marches along x_2 (rows play the part of the planes of
-// k_fused2, with no halo across x_2 besides the marching itself).  Rows on a
-// Dirichlet wall of x_2 go through C as in k_fused2.
-// One tile (x_1 nodes x0 .. x0 + TX - 1, output rows yc0 .. yend - 1) of the
-// d = 2 two-step pass; lds holds the block's SLOTS x (TX + 2) row-slots.
-template <class T, bool HALF>
-__device__ __forceinline__ void fused2_d2_tile(const T* __restrict__ A, T* __restrict__ B,
-                                               T* __restrict__ C, const KParams& p, T* lds,
-                                               const int x0, const int yc0, const int yend) {
-  using S = FuseShape2<T, HALF>;
-  constexpr int D = 2, Q = q_of(2), TX = S::TX, NT = S::NT;
-  constexpr int R = TX + 2;
-  static_assert(TX == NT, "one output node per thread");
-  const long long ps = p.pstride;
-  const int n0 = p.n[0], n1 = p.n[1];
-  const int iters = yend - yc0 + 2;
-  const int r = threadIdx.x;
-  for (int it = 0; it < iters; ++it) {
-    const int yp = yc0 - 1 + it;  // step-1 row of this iteration
-    // ---- step 1 on the tile and its halo of row yp
-    for (int rr = r; rr < R; rr += NT) {
-      int gx = x0 - 1 + rr, gy = yp;
-      bool skip = false;
-      if (gx < 0 || gx >= n0) {
-        if (p.bc[0] != 0) skip = true;
-        else gx = fuse_wrap(gx, n0);
-      }
-      if (gy < 0 || gy >= n1) {
-        if (p.bc[1] != 0) skip = true;
-        else gy = fuse_wrap(gy, n1);
-      }
-      if (!skip) {
-        const int row = gy;
-        RowInfo<D> ri;
-        row_setup<D>(p, row, ri);
-        col_setup<D>(p, gx, ri);
-        const int node = ri.rowbase + gx;
-        T f[Q];
-        if (ri.rowwall) {
-          static_for<0, Q>([&](auto K) {
-            constexpr int k = decltype(K)::value;
-            f[k] = C[k * ps + node];
-          });
-        } else {
-          static_for<0, Q>([&](auto K) {
-            constexpr int k = decltype(K)::value;
-            constexpr int cx = vel_comp(D, k, 0);
-            int idx = node + pull_offset<D, k>(ri);
-            if constexpr (cx != 0) {
-              if ((cx == 1) ? ri.lo[0] : ri.hi[0]) idx = p.xoff + row;
-            }
-            f[k] = A[k * ps + idx];
-          });
-          if (HALF && (ri.lo[0] || ri.hi[0])) {
-            static_for<0, Q>([&](auto K) {
-              constexpr int k = decltype(K)::value;
-              constexpr int cx = vel_comp(D, k, 0);
-              if constexpr (cx != 0) {
-                if ((cx == 1) ? ri.lo[0] : ri.hi[0]) f[k] -= A[opp_index(D, k) * ps + node];
-              }
-            });
-          }
-          collide_vals<D, T>(f, p);
-          // rows next to a wall of x_2, owned by this block: kept for the
-          // step-2 wall kernel
-          const bool own = rr >= 1 && rr <= TX && x0 - 1 + rr < n0 && yp >= yc0 && yp < yend;
-          const bool near = p.bc[1] != 0 && (ri.i[1] == 1 || ri.i[1] == n1 - 2);
-          if (own && near) {
-#pragma unroll
-            for (int k = 0; k < Q; ++k) __builtin_nontemporal_store(f[k], C + k * ps + node);
-          }
-        }
-        static_for<0, Q>([&](auto K) {
-          constexpr int k = decltype(K)::value;
-          lds[fuse_slot2<HALF, k>(it) * R + rr] = f[k];
-        });
-      }
-    }
-    __syncthreads();
-    // ---- step 2 on output row yp - 1
-    if (it >= 2 && r < TX) {
-      const int gy = yp - 1;
-      const int gx = x0 + r;
-      if (gx < n0) {
-        const int row = gy;
-        RowInfo<D> ri;
-        row_setup<D>(p, row, ri);
-        if (!ri.rowwall) {
-          col_setup<D>(p, gx, ri);
-          const int node = ri.rowbase + gx;
-          // pulls from LDS, x_1-face unknowns from B's row slots (as k_fused2)
-          T f[Q];
-          static_for<0, Q>([&](auto K) {
-            constexpr int k = decltype(K)::value;
-            constexpr Vec4i c = vel_vec(D, k);
-            constexpr int src_it = c.v[1] == 0 ? 1 : (c.v[1] == 1 ? 2 : 0);
-            f[k] = lds[fuse_slot2<HALF, k>(it - src_it) * R + (r + 1 - c.v[0])];
-          });
-          if (ri.lo[0] || ri.hi[0]) {
-            static_for<0, Q>([&](auto K) {
-              constexpr int k = decltype(K)::value;
-              constexpr int cx = vel_comp(D, k, 0);
-              if constexpr (cx != 0) {
-                if ((cx == 1) ? ri.lo[0] : ri.hi[0]) f[k] = B[k * ps + p.xoff + row];
-              }
-            });
-          }
-          if (HALF && (ri.lo[0] || ri.hi[0])) {
-            static_for<0, Q>([&](auto K) {
-              constexpr int k = decltype(K)::value;
-              constexpr int cx = vel_comp(D, k, 0);
-              if constexpr (cx != 0) {
-                constexpr int kb = opp_index(D, k);
-                if ((cx == 1) ? ri.lo[0] : ri.hi[0])
-                  f[k] -= lds[fuse_slot2<HALF, kb>(it - 1) * R + (r + 1)];
-              }
-            });
-          }
-          collide_store<D, T>(f, B, ps, node, p);
-        }
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// Two steps of many periodic d = 2 lattices in one launch: block b takes tile
-// tiles[b] (instance, x_1 start, row range) with the instance's parameter
-// block and buffers (cur selects the source).
-template <class T>
-__global__ void __launch_bounds__(256)
-    k_fused2_d2_batch(const KParams* __restrict__ kps, T* const* __restrict__ bufs,
-                      const BatchTile2* __restrict__ tiles, const int cur) {
-  extern __shared__ __align__(16) unsigned char fuse_lds[];
-  const BatchTile2 t = tiles[blockIdx.x];
-  fused2_d2_tile<T, false>(bufs[2 * t.inst + cur], bufs[2 * t.inst + 1 - cur], nullptr,
-                           kps[t.inst], reinterpret_cast<T*>(fuse_lds), t.x0, t.y0, t.y1);
-}
-
-// Every pair of steps of a call for a batch of d = 2 lattices in one launch,
-// one block per instance: block b takes instance order[b] and advances it
-// through all npairs pairs, tile after tile of the instance's table
-// (tiles[first[i] .. first[i + 1])), with the block barrier that ends each
-// tile body as the only synchronisation (the instance's state never leaves
-// its block, so no block waits for another).  Bitwise the result of the
-// per-pair launches: the same tile body on the same tiles.
-template <class T>
-__global__ void __launch_bounds__(256)
-    k_fused2_d2_resident(const KParams* __restrict__ kps, T* const* __restrict__ bufs,
-                         const BatchTile2* __restrict__ tiles, const int* __restrict__ first,
-                         const int* __restrict__ order, const int npairs, const int cur) {
-  extern __shared__ __align__(16) unsigned char fuse_lds[];
-  const int inst = order[blockIdx.x];
-  const KParams& p = kps[inst];
-  const int t0 = first[inst], t1 = first[inst + 1];
-  for (int pair = 0; pair < npairs; ++pair) {
-    const int c = (cur + pair) & 1;
-    const T* A = bufs[2 * inst + c];
-    T* B = bufs[2 * inst + 1 - c];
-    for (int t = t0; t < t1; ++t) {
-      const BatchTile2 tl = tiles[t];
-      fused2_d2_tile<T, false>(A, B, nullptr, p, reinterpret_cast<T*>(fuse_lds), tl.x0, tl.y0,
-                               tl.y1);
-    }
-    // this pair's output (B) is read by the next pair: the block's global
-    // stores must be visible to all of its threads
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   }
 }
 
@@ -1723,7 +1565,7 @@ __global__ void __launch_bounds__(256)
     const int node = r.rowbase + x;
     T f[Q];
     auto fstar = [&](int kb) {
-      return wall_absolute(static_cast<double>(src[kb * ps + node]), p.omega[kb], ref);
+      return wall_absolute<D>(static_cast<double>(src[kb * ps + node]), p.omega[kb], ref);
     };
     if constexpr (D == 4 && kF32) {
       // the wall values first, then the pulls of the populations that enter
@@ -1819,14 +1661,40 @@ __device__ double fd4_derivative(const double* phi, const KParams& p, const int 
   return (-at(2) + 8.0 * at(1) - 8.0 * at(-1) + at(-2)) / (12.0 * p.dx);
 }
 
-template <int D, class T>
+// What a whole-batch initialisation takes beside the concatenated arrays: the
+// instances' parameter blocks and buffers, the blocks, and each instance's first
+// element of phi0.
+struct BatchInit {
+  const KParams* kps;
+  void* const* bufs;
+  const BatchBlock* blocks;
+  const long long* offset;
+};
+
+// Initial state from the analytic field (phi0 == nullptr) or from device arrays;
+// BATCH: of every instance of a batch, one BatchBlock per block.
+template <int D, class T, bool BATCH = false>
 __global__ void __launch_bounds__(256)
     k_init(T* __restrict__ dst, double* __restrict__ phidst, const double* __restrict__ phi0,
-           const double* __restrict__ grad0, const KParams p, int mode) {
+           const double* __restrict__ grad0, const std::conditional_t<BATCH, BatchInit, KParams> pb,
+           int mode) {
+  const KParams& p = [&]() -> const KParams& {
+    if constexpr (BATCH) return pb.kps[pb.blocks[blockIdx.x].inst];
+    else return pb;
+  }();
+  int first = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+  if constexpr (BATCH) {
+    const BatchBlock b = pb.blocks[blockIdx.x];
+    dst = static_cast<T*>(pb.bufs[2 * b.inst]);
+    phi0 += pb.offset[b.inst];
+    if (grad0) grad0 += pb.offset[b.inst] * D;
+    first = b.block * 256 + threadIdx.x;
+    stride = kRedBlocks * 256;
+  }
   constexpr int Q = q_of(D);
   const long long ps = p.pstride;
-  for (int node = blockIdx.x * blockDim.x + threadIdx.x; node < p.nodes;
-       node += gridDim.x * blockDim.x) {
+  for (int node = first; node < p.nodes;
+       node += stride) {
     int i[D];
     node_index<D>(p, node, i);
     double phi, grad[D];
@@ -1903,21 +1771,23 @@ __device__ __forceinline__ void block_reduce(double (&v)[kNumAcc], double* sh) {
 // per-node analytic field is not evaluated, without kMomEntropy the
 // pre-collision populations are not rebuilt, and without any scalar bit no
 // partial sums are written.
+// One block's share of the reduction: nodes block * kRedThreads + thread, then
+// every `stride`; its sums go to partial[0 .. kNumAcc).
 template <int D, class T>
-__global__ void __launch_bounds__(kRedThreads)
-    k_moments(const T* __restrict__ f, const double* __restrict__ phis, const KParams p,
-              const int mode, const double t_n, double* __restrict__ phi_out,
-              double* __restrict__ partial, const unsigned what) {
+__device__ __forceinline__ void moments_block(const T* __restrict__ f,
+                                              const double* __restrict__ phis, const KParams& p,
+                                              const int mode, const double t_n,
+                                              double* __restrict__ phi_out,
+                                              double* __restrict__ partial, const unsigned what,
+                                              const int block, const int stride, double* sh) {
+#pragma clang fp contract(off)
   constexpr int Q = q_of(D);
-  __shared__ double sh[kNumAcc * kRedThreads];
   double acc[kNumAcc] = {0, 0, 0, 0, 0, 0};
   const long long ps = p.pstride;
   const bool want_err = (what & kMomRmse) && p.field.kind != kFieldNone;
   const bool want_ent = (what & kMomEntropy) != 0;
-  const bool want_red = (what & (kMomSums | kMomRmse | kMomEntropy)) != 0;
   const double ref = (mode == kFP32) ? p.phi_ref + p.R * (t_n + p.dt) : 0.0;
-  for (int node = blockIdx.x * blockDim.x + threadIdx.x; node < p.nodes;
-       node += gridDim.x * blockDim.x) {
+  for (int node = block * kRedThreads + threadIdx.x; node < p.nodes; node += stride) {
     double fk[Q];
     double phi;
     if (split_layout(mode)) {
@@ -1942,7 +1812,6 @@ __global__ void __launch_bounds__(kRedThreads)
       }
     }
     if (phi_out) phi_out[node] = phi;
-    if (!want_red) continue;
     if (want_ent) {
       double ent = 0.0;
 #pragma unroll
@@ -1962,11 +1831,59 @@ __global__ void __launch_bounds__(kRedThreads)
     acc[4] = fmax(acc[4], fabs(phi));
     acc[5] += isfinite(phi) ? 0.0 : 1.0;
   }
-  if (!want_red) return;  // uniform over the grid
   block_reduce(acc, sh);
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int m = 0; m < kNumAcc; ++m) partial[blockIdx.x * kNumAcc + m] = acc[m];
+    for (int m = 0; m < kNumAcc; ++m) partial[m] = acc[m];
+  }
+}
+
+template <int D, class T>
+__global__ void __launch_bounds__(kRedThreads)
+    k_moments(const T* __restrict__ f, const double* __restrict__ phis, const KParams p,
+              const int mode, const double t_n, double* __restrict__ phi_out,
+              double* __restrict__ partial, const unsigned what) {
+  __shared__ double sh[kNumAcc * kRedThreads];
+  moments_block<D, T>(f, phis, p, mode, t_n, phi_out, partial + blockIdx.x * kNumAcc, what,
+                      blockIdx.x, gridDim.x * kRedThreads, sh);
+}
+
+// The scalar moments of every instance of a batch at step n, each instance cut
+// as k_moments cuts it (the blocks past its nodes, which add zeros there, are
+// not launched), so the sums are the same numbers.
+template <int D, class T>
+__global__ void __launch_bounds__(kRedThreads)
+    k_batch_moments(const KParams* __restrict__ kps, void* const* __restrict__ bufs,
+                    const BatchBlock* __restrict__ blocks, const int cur, const int mode,
+                    const long long n, double* __restrict__ partial, const unsigned what) {
+  __shared__ double sh[kNumAcc * kRedThreads];
+  const BatchBlock b = blocks[blockIdx.x];
+  const KParams& p = kps[b.inst];
+  moments_block<D, T>(static_cast<const T*>(bufs[2 * b.inst + cur]), nullptr, p, mode,
+                      step_time(n, p.dt), nullptr, partial + static_cast<long long>(blockIdx.x) * kNumAcc,
+                      what, b.block, kRedBlocks * kRedThreads, sh);
+}
+
+// phi alone: no partial sums, and in the split layouts no populations either
+template <int D, class T>
+__global__ void __launch_bounds__(256)
+    k_phi(const T* __restrict__ f, const double* __restrict__ phis, const KParams p,
+          const int mode, const double t_n, double* __restrict__ phi_out) {
+#pragma clang fp contract(off)
+  const long long ps = p.pstride;
+  const double ref = (mode == kFP32) ? p.phi_ref + p.R * (t_n + p.dt) : 0.0;
+  for (int node = blockIdx.x * 256 + threadIdx.x; node < p.nodes; node += gridDim.x * 256) {
+    double phi;
+    if (split_layout(mode)) {
+      phi = mode == kHiLo ? phi_get(reinterpret_cast<const float2*>(phis), node) : phis[node];
+    } else {
+      double sum = 0.0;
+#pragma unroll
+      for (int k = 0; k < q_of(D); ++k)
+        sum += static_cast<double>(f[k * ps + node]) + p.omega[k] * ref;
+      phi = sum - p.dt * p.R;
+    }
+    __builtin_nontemporal_store(phi, phi_out + node);
   }
 }
 

@@ -134,6 +134,87 @@ hipError_t launch_march2(const MarchParams& p, int scheme, int mode, const March
   }
 }
 
+// ---- batches of periodic lattices: one tile of the table per wavefront
+template <int MODE, int NL>
+__global__ void __launch_bounds__(256)
+    k_march2_batch(const MarchParams* __restrict__ mps, void* const* __restrict__ bufs,
+                   const BatchTile2* __restrict__ tiles, const int ntiles, const int cur) {
+  const int w = static_cast<int>(blockIdx.x) * 4 + static_cast<int>(threadIdx.x) / 64;
+  if (w >= ntiles) return;
+  const BatchTile2 t = tiles[__builtin_amdgcn_readfirstlane(w)];
+  const MarchBufs b{bufs[2 * t.inst + cur], bufs[2 * t.inst + 1 - cur], nullptr, nullptr};
+  march2_tile<MODE, NL, 0, 2>(mps[t.inst], b, t.x0, kBatchTileWidth, t.y0, t.y1, 0, nullptr);
+}
+
+template <int MODE>
+static hipError_t batch_march_m(const MarchParams* mps, void* const* bufs,
+                                const BatchTile2* tiles, int ntiles, int nl, int cur,
+                                hipStream_t stream) {
+  const dim3 g((ntiles + 3) / 4), b(256);
+  switch (nl) {
+    case 2: hipLaunchKernelGGL((k_march2_batch<MODE, 2>), g, b, 0, stream, mps, bufs, tiles, ntiles, cur); break;
+    case 4: hipLaunchKernelGGL((k_march2_batch<MODE, 4>), g, b, 0, stream, mps, bufs, tiles, ntiles, cur); break;
+    case 8: hipLaunchKernelGGL((k_march2_batch<MODE, 8>), g, b, 0, stream, mps, bufs, tiles, ntiles, cur); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_march(const MarchParams* mps, void* const* bufs, const BatchTile2* tiles,
+                              int ntiles, int mode, int nl, int cur, hipStream_t stream) {
+  if (mode == kFP64) return batch_march_m<kFP64>(mps, bufs, tiles, ntiles, nl, cur, stream);
+  if (mode == kFP32) return batch_march_m<kFP32>(mps, bufs, tiles, ntiles, nl, cur, stream);
+  return hipErrorInvalidValue;
+}
+
+// Every pass of a call for one instance per block: its wavefronts take the
+// instance's tiles in turn, and the block's barrier ends each pass (the state
+// never leaves the block, so no block waits for another).  Bitwise the result of
+// the launches per pass: the same tile body on the same tiles.
+template <int MODE>
+__global__ void __launch_bounds__(256)
+    k_march2_resident(const MarchParams* __restrict__ mps, void* const* __restrict__ bufs,
+                      const BatchTile2* __restrict__ tiles, const int* __restrict__ first,
+                      const int* __restrict__ order, const int nsteps, const int cur) {
+  const int inst = order[blockIdx.x];
+  const int t0 = first[inst], t1 = first[inst + 1];
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
+  int c = cur;
+  auto pass = [&](auto Nl) {
+    constexpr int NL = decltype(Nl)::value;
+    const MarchBufs b{bufs[2 * inst + c], bufs[2 * inst + 1 - c], nullptr, nullptr};
+    for (int i = t0 + wave; i < t1; i += 4) {
+      const BatchTile2 t = tiles[i];
+      march2_tile<MODE, NL, 0, 2>(mps[inst], b, t.x0, kBatchTileWidth, t.y0, t.y1, 0, nullptr);
+    }
+    // this pass's output is read by the next: the block's global stores must
+    // be visible to all of its threads
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    c = 1 - c;
+  };
+  for (int s = 0; s < nsteps / 8; ++s) pass(std::integral_constant<int, 8>{});
+  if (nsteps & 4) pass(std::integral_constant<int, 4>{});
+  if (nsteps & 2) pass(std::integral_constant<int, 2>{});
+}
+
+hipError_t launch_batch_resident(const MarchParams* mps, void* const* bufs,
+                                 const BatchTile2* tiles, const int* first, const int* order,
+                                 int count, int mode, int cur, int nsteps, hipStream_t stream) {
+  if (nsteps <= 0 || count <= 0) return hipSuccess;
+  const dim3 g(static_cast<unsigned>(count)), b(256);
+  if (mode == kFP64)
+    hipLaunchKernelGGL((k_march2_resident<kFP64>), g, b, 0, stream, mps, bufs, tiles, first, order,
+                       nsteps, cur);
+  else if (mode == kFP32)
+    hipLaunchKernelGGL((k_march2_resident<kFP32>), g, b, 0, stream, mps, bufs, tiles, first, order,
+                       nsteps, cur);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 // ---- wall data of several steps: one thread per (step, face, face node); the
 // values k_xface and k_wall compute, before their rounding to the storage type.
 template <bool TAN, int V>
@@ -155,8 +236,8 @@ __global__ void __launch_bounds__(256)
   const int i0 = onx ? (side ? p.n[0] - 1 : 0) : pos;
   const int i1 = onx ? pos : (side ? p.n[1] - 1 : 0);
   double x[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
-  x[0] = wall_coord(p, 0, i0);
-  x[1] = wall_coord(p, 1, i1);
+  x[0] = wall_coord<2>(p, 0, i0);
+  x[1] = wall_coord<2>(p, 1, i1);
   const int want = side ? -1 : 1;
   double val[q_of(2)];
   wall_analytic<2, TAN, V>(p, x, t_n, [&](int k) { return p.cv[k][ax] == want; },

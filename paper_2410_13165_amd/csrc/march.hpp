@@ -43,13 +43,6 @@ __device__ __forceinline__ double lane_above(double v) {
   return __hiloint2double(lane_above(__double2hiint(v)), lane_above(__double2loint(v)));
 }
 
-// t_n as the host forms it, n dt rounded before anything is added to it (a
-// contraction of the two would differ from the single steps in the last bit)
-__device__ __forceinline__ double step_time(long long n, double dt) {
-#pragma clang fp contract(off)
-  return static_cast<double>(n) * dt;
-}
-
 // The populations of D2Q9 by their c_2: march_pop(cy, j) is the j-th
 // (j = 0..2) with c_2 = cy; march_slot(k) its j.
 constexpr int march_pop(int cy, int j) {
@@ -61,7 +54,13 @@ constexpr int march_pop(int cy, int j) {
   }
   return -1;
 }
-constexpr int march_slot(int k) { return cy_index(k); }
+constexpr int march_slot(int k) {
+  const int cy = vel_comp(2, k, 1);
+  int idx = 0;
+  for (int m = 0; m < k; ++m)
+    if (vel_comp(2, m, 1) == cy) ++idx;
+  return idx;
+}
 
 // Value of population k that enters a wall node from outside: v the analytic
 // wall value (wall_close included), own the node's own post-collision kbar
@@ -73,10 +72,10 @@ __device__ __forceinline__ A march_wall_value(double v, A own, bool rowwall, dou
                                               const MarchParams& p) {
   constexpr int kb = opp_index(2, k);
   if constexpr (MODE == kFP32) {
-    if constexpr (!HALF) return static_cast<A>(wall_deviation(v, p.omega[k], ref));
-    const double fs = wall_absolute(static_cast<double>(own), p.omega[kb], ref);
-    const A row = static_cast<A>(wall_deviation(v - fs, p.omega[k], ref));
-    const A face = static_cast<A>(wall_deviation(v, p.omega[k] + p.omega[kb], ref)) - own;
+    if constexpr (!HALF) return static_cast<A>(wall_deviation<2>(v, p.omega[k], ref));
+    const double fs = wall_absolute<2>(static_cast<double>(own), p.omega[kb], ref);
+    const A row = static_cast<A>(wall_deviation<2>(v - fs, p.omega[k], ref));
+    const A face = static_cast<A>(wall_deviation<2>(v, p.omega[k] + p.omega[kb], ref)) - own;
     return rowwall ? row : face;
   } else {
     return HALF ? v - own : v;

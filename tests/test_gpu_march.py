@@ -70,3 +70,38 @@ def test_march_passes_stop_at_checkpoints(precision):
     assert torch.equal(out[0][0], out[1][0])
     assert torch.equal(out[0][1]["phi0"], out[1][1]["phi0"])
     assert out[0][1]["tau"] == out[1][1]["tau"]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("d", [1, 2, 3])
+def test_batch_moments_and_initial_states_equal_per_instance(d, precision):
+    """Whole-batch moments against lbm_moments of each instance, bit for bit, and
+    whole-batch initialisation against lbm_set_initial of each lattice on its own:
+    one node, one reduction block exactly, and more nodes than one pass of the
+    reduction's blocks.  The two initialisations may fuse other products, one
+    rounding each of at most eight sums of values up to 4 max |phi0|; in float32
+    each stored deviation may then round the other way."""
+    import numpy as np
+    from paper_2410_13165_amd import Batch, Lattice
+    dims = {1: [(1,), (256,), (300001,)], 2: [(1, 1), (16, 16), (37, 29), (600, 500)],
+            3: [(1, 1, 1), (8, 8, 4), (9, 7, 5)]}[d]
+    u = [0.05, -0.1, 0.08][:d]
+    g = torch.Generator(device="cuda").manual_seed(12)
+    phi0 = [torch.randn(*reversed(n), generator=g, dtype=torch.float64, device="cuda") for n in dims]
+    specs = [{"dims": n, "tau": 0.6 + 0.1 * i, "dx": 1.0 / n[0], "u": u, "R": 0.3, "K": 3}
+             for i, n in enumerate(dims)]
+    eps = 2.0 ** -53 if precision == "fp64" else 2.0 ** -24
+    with Batch(d, specs, precision=precision) as b:
+        b.set_initial(torch.cat([p.reshape(-1) for p in phi0]))
+        for i, sp in enumerate(specs):
+            with Lattice(d, sp["dims"], sp["tau"], dx=sp["dx"], u=u, R=0.3, K=3,
+                         precision=precision) as lat:
+                lat.set_initial(phi0[i])
+                bound = 32 * eps * float(phi0[i].abs().max() + 1.0)
+                assert float((lat.phi() - b.instance(i).phi()).abs().max()) <= bound, i
+        for n in (0, 5):
+            b.step(n)
+            m = b.moments()
+            for i in range(len(specs)):
+                want = np.array(list(b.instance(i).diagnostics().values()))
+                assert np.array_equal(m[i], want, equal_nan=True), (n, i)
