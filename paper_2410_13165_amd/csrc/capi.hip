@@ -290,9 +290,9 @@ double* blob_phi(const lbm_handle* h, void* blob) {
              : nullptr;
 }
 
-// Marching passes (d = 2): several steps per launch, any storage but hi/lo.
+// Passes of several steps (d = 1 and 2): any storage but hi/lo.
 bool use_march(const lbm_handle* h) {
-  return h->multi && h->d == 2 && h->precision != LBM_FP32_HILO;
+  return h->multi && h->d <= 2 && h->precision != LBM_FP32_HILO;
 }
 
 int tape_push(lbm_handle* h) {
@@ -484,8 +484,7 @@ int lbm_create(int d, const int64_t* dims, double tau, const lbm_params* p, lbm_
     return rc;
   }
 
-  if (use_march(h))
-    for (int i = 0; i < 4; ++i) h->plans[i] = march_plan(kp, h->precision, 1 << i);
+  if (use_march(h) && d == 2) march_plans(kp, h->precision, h->plans);
 
   // device buffers
   const size_t pb = pop_bytes(h);
@@ -631,13 +630,20 @@ hipError_t check_nonfinite(lbm_handle* h) {
   return e;
 }
 
-// Wall data of a marching pass: doubles per step, and the steps the workspace
-// holds: 64 (one launch of k_wall_data serves several passes), fewer where that
-// would exceed 1 MB and half the state.
-int64_t wall_doubles(const lbm_handle* h) {
-  return use_march(h) ? wall_data2_x(h->kp) + wall_data2_y(h->kp) : 0;
+// Wall data of such passes: doubles per step (x_1 faces, x_2 faces), and the
+// steps the workspace holds: the longest pass (d = 1) or 64 (d = 2, one launch of
+// k_wall_data2 serves several passes), fewer where that would exceed 1 MB and half
+// the state.
+int64_t wall_x(const lbm_handle* h) {
+  if (!use_march(h) || h->kp.bc[0] == LBM_BC_PERIODIC) return 0;
+  return h->d == 1 ? 2 : wall_data2_x(h->kp);
 }
+int64_t wall_y(const lbm_handle* h) {
+  return use_march(h) && h->d == 2 ? wall_data2_y(h->kp) : 0;
+}
+int64_t wall_doubles(const lbm_handle* h) { return wall_x(h) + wall_y(h); }
 int wall_steps(const lbm_handle* h) {
+  if (h->d == 1) return line_steps(h->kp.n[0]);
   const int64_t per = wall_doubles(h) * static_cast<int64_t>(sizeof(double));
   const int64_t cap = std::max<int64_t>(1 << 20, static_cast<int64_t>(state_bytes(h)) / 2);
   int s = 64;
@@ -661,8 +667,7 @@ int64_t pass_limit(const lbm_handle* h, int64_t left) {
 int run_steps(lbm_handle* h, int64_t n, void* cbuf, double* xd2, double* wall_ws, int wall_cap) {
   const bool pairs = use_pairs(h) && h->d == 3;
   const bool march = use_march(h);
-  const int64_t wx_len = march ? wall_data2_x(h->kp) : 0;
-  const int64_t wy_len = march ? wall_data2_y(h->kp) : 0;
+  const int64_t wx_len = wall_x(h), wy_len = wall_y(h);
   int64_t wall0 = 0, wall_n = 0;  // steps whose wall data the workspace holds
   bool checked = false;
   if (h->check_every > 0 && n > 0) {
@@ -677,13 +682,19 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, double* xd2, double* wall_ws
     MarchPlan plan{1, 0};
     if (march) {
       const int64_t lim = std::min<int64_t>(pass_limit(h, n - i), wall_cap);
-      plan = h->plans[lim >= 8 ? 3 : lim >= 4 ? 2 : lim >= 2 ? 1 : 0];
-      todo = plan.nl;
+      if (h->d == 2) {
+        plan = h->plans[lim >= 8 ? 3 : lim >= 4 ? 2 : lim >= 2 ? 1 : 0];
+        todo = plan.nl;
+      } else {
+        todo = std::max<int64_t>(lim, 1);
+      }
       if (todo > 1 && h->kp.scheme != kNoWall && h->step + todo > wall0 + wall_n) {
         wall0 = h->step;
         wall_n = std::min<int64_t>(n - i, wall_cap);
-        hipError_t e = launch_wall_data2(h->kp, wall_ws, wall_ws + wx_len * wall_cap, wall0,
-                                         static_cast<int>(wall_n), h->stream);
+        const int m = static_cast<int>(wall_n);
+        hipError_t e = h->d == 1 ? launch_wall_data1(h->kp, wall_ws, wall0, m, h->stream)
+                                 : launch_wall_data2(h->kp, wall_ws, wall_ws + wx_len * wall_cap,
+                                                     wall0, m, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "wall data");
       }
     }
@@ -702,7 +713,9 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, double* xd2, double* wall_ws
       }
       const MarchBufs mb{h->buf[src], h->buf[dst], h->phib[src], h->phib[dst]};
       if (ev) (void)hipEventRecord(ev[0], h->stream);
-      e = launch_march2(mp, h->kp.scheme, h->precision, plan, mb, h->step, h->stream);
+      e = h->d == 1 ? launch_line(mp, h->kp.scheme, h->precision, static_cast<int>(todo), mb,
+                                  h->step, h->stream)
+                    : launch_march2(mp, h->kp.scheme, h->precision, plan, mb, h->step, h->stream);
       if (ev) {
         (void)hipEventRecord(ev[1], h->stream);
         (void)hipEventRecord(ev[2], h->stream);
@@ -767,7 +780,7 @@ int lbm_step(lbm_handle* h, int64_t n) {
     }
   }
   return run_steps(h, n, h->fuse_buf, h->xdata2, h->wall_ws,
-                   wall_doubles(h) > 0 ? h->wall_ws_steps : kMarchMaxSteps);
+                   wall_doubles(h) > 0 ? h->wall_ws_steps : wall_steps(h));
 }
 
 int lbm_step_static(lbm_handle* h, int64_t n) {
@@ -794,7 +807,7 @@ int lbm_step_static(lbm_handle* h, int64_t n) {
   }
   // the wall data of marching passes go to the same scratch
   double* wall_ws = nullptr;
-  int wall_cap = kMarchMaxSteps;
+  int wall_cap = wall_steps(h);
   if (wall_doubles(h) > 0) {
     const int64_t per = wall_doubles(h) * static_cast<int64_t>(sizeof(double));
     wall_cap = static_cast<int>(

@@ -113,12 +113,23 @@ constexpr int kMarchMaxSteps = 8, kMarchMaxWallSteps = 4;
 struct MarchPlan {
   int nl, yc;
 };
-MarchPlan march_plan(const KParams& p, int mode, int max_nl);
+void march_plans(const KParams& p, int mode, MarchPlan (&plans)[4]);
 // plan.nl steps of a d = 2 lattice (float64, float32 or split mode) in one
 // pass; p.wx / p.wy hold the wall data of those steps.
 hipError_t launch_march2(const MarchParams& p, int scheme, int mode, const MarchPlan& plan,
                          const MarchBufs& b, long long n, hipStream_t stream);
-// Doubles of wall data per step (x_1 faces, then x_2 faces), and the wall data of
+// nsteps (at most line_steps) steps of a d = 1 lattice in one launch; p.wx holds the
+// wall data of those steps (launch_wall_data1).  A lattice of at most kLineNodes
+// nodes is held by one block; longer ones take windows of kLineNodes nodes,
+// kLineCut per thread, whose halo is nsteps wide: 64 steps recompute an eighth of
+// the nodes.
+constexpr int kLineNodes = 1024, kLineCut = 4;
+constexpr int line_steps(int n0) { return n0 <= kLineNodes ? 1024 : 64; }
+hipError_t launch_line(const MarchParams& p, int scheme, int mode, int nsteps, const MarchBufs& b,
+                       long long n, hipStream_t stream);
+hipError_t launch_wall_data1(const KParams& p, double* wx, long long n, int nsteps,
+                             hipStream_t stream);
+// d = 2: doubles of wall data per step (x_1 faces, then x_2 faces), and the wall data of
 // steps n .. n + nsteps - 1 into wx / wy in the layout of MarchParams.
 long long wall_data2_x(const KParams& p);
 long long wall_data2_y(const KParams& p);

@@ -33,7 +33,7 @@ MarchParams march_params(const KParams& p) {
   m.bc0 = p.bc[0];
   m.bc1 = p.bc[1];
   m.ps = p.pstride;
-  for (int k = 0; k < 9; ++k) {
+  for (int k = 0; k < 9; ++k) {  // d = 1 uses the first three
     m.omega[k] = p.omega[k];
     m.omega_f[k] = p.omega_f[k];
   }
@@ -71,7 +71,7 @@ static hipError_t march2_w(const MarchParams& p, int scheme, const MarchBufs& b,
   return hipErrorInvalidValue;
 }
 
-// Steps and rows per tile of a pass of at most max_nl steps, by a model of its
+// Steps and rows per tile of passes of at most 1, 2, 4 and 8 steps, by a model of its
 // time fitted to measured passes (64^2 to 2048^2, us): 4 for the launch, then
 // the largest of
 //   * one tile alone: c per row and stage (its instructions at one wavefront per
@@ -84,14 +84,17 @@ static hipError_t march2_w(const MarchParams& p, int scheme, const MarchBufs& b,
 // ones by the first and the launch (64^2: 4 steps of one row per tile, 7.5 us).
 // 16 wall rows and columns per wavefront are more registers and instructions:
 // passes over walls stop at 4 steps and 32 rows.
-MarchPlan march_plan(const KParams& p, int mode, int max_nl) {
+void march_plans(const KParams& p, int mode, MarchPlan (&plans)[4]) {
   const bool walls = p.scheme != kNoWall;
   const double c = mode == kFP64 ? 0.115 : mode == kFP32 ? 0.172 : 0.177;
   const double node_bytes = mode == kFP64 ? 72.0 : mode == kFP32 ? 36.0 : 44.0;
   const int simds = 4 * device_cus();
   MarchPlan best{1, 0};
   double best_t = 0.0;
-  for (int nl = 2; nl <= max_nl && nl <= (walls ? kMarchMaxWallSteps : kMarchMaxSteps); nl *= 2) {
+  plans[0] = best;
+  for (int i = 1; i < 4; ++i, plans[i - 1] = best) {
+    const int nl = 1 << i;
+    if (nl > (walls ? kMarchMaxWallSteps : kMarchMaxSteps)) continue;
     const int w = march_width(nl);
     const long long gx = (p.n[0] + w - 1) / w;
     for (int yc = 1; yc <= (walls ? 32 : 128); ++yc) {
@@ -109,7 +112,6 @@ MarchPlan march_plan(const KParams& p, int mode, int max_nl) {
       if (yc >= p.n[1]) break;
     }
   }
-  return best;
 }
 
 template <int MODE>
@@ -215,7 +217,86 @@ hipError_t launch_batch_resident(const MarchParams* mps, void* const* bufs,
   return hipGetLastError();
 }
 
-// ---- wall data of several steps: one thread per (step, face, face node); the
+// ---- d = 1
+template <int MODE, int WALL, int M>
+__global__ void __launch_bounds__(M == 1 ? kLineNodes : kLineNodes / kLineCut)
+    k_line(const MarchParams p, const MarchBufs b, const int nsteps, const long long n) {
+  extern __shared__ __align__(16) unsigned char march_mem[];
+  if constexpr (M == 1) {
+    line_block<MODE, WALL, 1>(p, b, 0, p.n0, 0, p.n0, nsteps, n, march_mem);
+  } else {
+    const int out = kLineNodes - 2 * nsteps;
+    const long long o0 = static_cast<long long>(blockIdx.x) * out;
+    line_block<MODE, WALL, M>(p, b, static_cast<int>(o0) - nsteps, kLineNodes,
+                              static_cast<int>(o0),
+                              static_cast<int>(min(o0 + out, static_cast<long long>(p.n0))), nsteps,
+                              n, march_mem);
+  }
+}
+
+template <int MODE, int WALL, int M>
+static hipError_t line_m(const MarchParams& p, const MarchBufs& b, int nsteps, long long n,
+                         hipStream_t stream) {
+  constexpr size_t as = MODE == kFP32 ? sizeof(float) : sizeof(double);
+  const int nt = M == 1 ? (p.n0 + 63) / 64 * 64 : kLineNodes / kLineCut;
+  const int out = kLineNodes - 2 * nsteps;
+  const unsigned blocks = M == 1 ? 1 : static_cast<unsigned>((p.n0 + out - 1) / out);
+  const size_t lds = (WALL ? sizeof(double) * 2 * nsteps : 0) + as * 4 * nt;
+  hipLaunchKernelGGL((k_line<MODE, WALL, M>), dim3(blocks), dim3(nt), lds, stream, p, b, nsteps, n);
+  return hipGetLastError();
+}
+
+template <int MODE>
+static hipError_t line_w(const MarchParams& p, int scheme, const MarchBufs& b, int nsteps,
+                         long long n, hipStream_t stream) {
+  if (p.n0 <= kLineNodes) {
+    if (scheme == kFullWay) return line_m<MODE, kFullWay, 1>(p, b, nsteps, n, stream);
+    if (scheme == kHalfWay) return line_m<MODE, kHalfWay, 1>(p, b, nsteps, n, stream);
+    return line_m<MODE, 0, 1>(p, b, nsteps, n, stream);
+  }
+  if (scheme == kFullWay) return line_m<MODE, kFullWay, kLineCut>(p, b, nsteps, n, stream);
+  if (scheme == kHalfWay) return line_m<MODE, kHalfWay, kLineCut>(p, b, nsteps, n, stream);
+  return line_m<MODE, 0, kLineCut>(p, b, nsteps, n, stream);
+}
+
+hipError_t launch_line(const MarchParams& p, int scheme, int mode, int nsteps, const MarchBufs& b,
+                       long long n, hipStream_t stream) {
+  if (nsteps < 1 || nsteps > line_steps(p.n0)) return hipErrorInvalidValue;
+  switch (mode) {
+    case kFP64: return line_w<kFP64>(p, scheme, b, nsteps, n, stream);
+    case kFP32: return line_w<kFP32>(p, scheme, b, nsteps, n, stream);
+    case kSplit: return line_w<kSplit>(p, scheme, b, nsteps, n, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// one thread per (step, face): k_xface's values before their rounding
+template <bool TAN>
+__global__ void __launch_bounds__(256)
+    k_wall_data1(double* __restrict__ wx, const KParams p, const long long n, const int nsteps) {
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  if (idx >= 2 * nsteps) return;
+  const int side = idx & 1;
+  const double t_n = step_time(n + (idx >> 1), p.dt);
+  double x[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
+  x[0] = wall_coord<1>(p, 0, side ? p.n[0] - 1 : 0);
+  const int want = side ? 2 : 1;
+  double val[3];
+  wall_analytic<1, TAN, -1>(p, x, t_n, [&](int k) { return k == want; }, [](int) { return 0; }, val);
+  wx[idx] = side ? val[2] : val[1];
+}
+
+hipError_t launch_wall_data1(const KParams& p, double* wx, long long n, int nsteps,
+                             hipStream_t stream) {
+  const dim3 g(static_cast<unsigned>((2 * nsteps + 255) / 256)), b(256);
+  if (p.wall_data)
+    hipLaunchKernelGGL((k_wall_data1<true>), g, b, 0, stream, wx, p, n, nsteps);
+  else
+    hipLaunchKernelGGL((k_wall_data1<false>), g, b, 0, stream, wx, p, n, nsteps);
+  return hipGetLastError();
+}
+
+// ---- wall data of several steps of d = 2: one thread per (step, face, face node); the
 // values k_xface and k_wall compute, before their rounding to the storage type.
 template <bool TAN, int V>
 __global__ void __launch_bounds__(256)

@@ -1,6 +1,8 @@
-// Several time steps of a d = 2 lattice in one pass (k_march2), and the data of
-// the Dirichlet walls for the steps of a pass (k_wall_data).
+// Several time steps of a d = 2 lattice in one pass (k_march2) and of a d = 1
+// lattice (k_line), with the data of the Dirichlet walls for the steps of a pass
+// formed beforehand (k_wall_data2, k_wall_data1).
 //
+// d = 2.
 // One wavefront owns 64 consecutive columns of x_1 and marches along x_2.  Per
 // source row it loads the post-collision populations of its columns (stage 0)
 // and pushes them into stage 1, which thereby completes its row one behind,
@@ -67,10 +69,10 @@ constexpr int march_slot(int k) {
 // value (half-way walls), ref the float32 reference of the step.  The rows on
 // a wall of x_2 round as k_wall does, the x_1 faces of the other rows as
 // k_xface and k_step do (the two differ in float32 half-way lattices only).
-template <int MODE, bool HALF, int k, class A>
+template <int MODE, bool HALF, int k, class A, int D = 2>
 __device__ __forceinline__ A march_wall_value(double v, A own, bool rowwall, double ref,
                                               const MarchParams& p) {
-  constexpr int kb = opp_index(2, k);
+  constexpr int kb = opp_index(D, k);
   if constexpr (MODE == kFP32) {
     if constexpr (!HALF) return static_cast<A>(wall_deviation<2>(v, p.omega[k], ref));
     const double fs = wall_absolute<2>(static_cast<double>(own), p.omega[kb], ref);
@@ -329,6 +331,110 @@ __device__ __forceinline__ void march2_tile(const MarchParams& p, const MarchBuf
     static_for<0, D>([&](auto S) {
       if (i + decltype(S)::value < iters) iteration(i + decltype(S)::value, S);
     });
+}
+
+// nsteps steps of a d = 1 lattice in one launch.  A block keeps a window of nodes
+// in registers, M adjacent ones per thread, and only the two populations that
+// cross to a neighbouring thread go through LDS, double-buffered: one barrier per
+// step.  A lattice of at most kLineNodes nodes is one window (M = 1, nothing
+// computed twice, any number of steps); longer ones are cut into windows with a
+// halo of nsteps nodes on either side.  wx[l * 2 + side]: the wall data of step l.
+// Per node the arithmetic of k_step (k_step_split) with k_xface's data.
+template <int MODE, int WALL, int M>
+__device__ __forceinline__ void line_block(const MarchParams& p, const MarchBufs& b,
+                                           const int first, const int used, const int out0,
+                                           const int out1, const int nsteps,
+                                           const long long step, unsigned char* mem) {
+  using T = std::conditional_t<MODE == kFP64, double, float>;
+  using A = std::conditional_t<MODE == kFP32, float, double>;
+  constexpr bool HALF = WALL == kHalfWay;
+  const int tid = static_cast<int>(threadIdx.x), nt = static_cast<int>(blockDim.x);
+  double* wx = reinterpret_cast<double*>(mem);
+  A* edge = reinterpret_cast<A*>(mem + (WALL ? sizeof(double) * 2 * nsteps : 0));
+  const int n0 = p.n0;
+  const long long ps = p.ps;
+  const T* __restrict__ src = static_cast<const T*>(b.src);
+  T* __restrict__ dst = static_cast<T*>(b.dst);
+  if constexpr (WALL != 0)
+    for (int i = tid; i < 2 * nsteps; i += nt) wx[i] = p.wx[i];  // seen after the first barrier
+  // the window's nodes first .. first + used - 1; a window that is the whole
+  // periodic lattice closes on itself
+  const int left = tid == 0 ? (used - 1) / M : tid - 1;
+  const int right = (tid + 1) * M >= used ? 0 : tid + 1;
+  A g[M][3];
+  float gs[M][3];
+  double phi[M];
+#pragma unroll
+  for (int j = 0; j < M; ++j) {
+    int x = first + tid * M + j;
+    x = WALL != 0 ? min(max(x, 0), n0 - 1) : fuse_wrap(x, n0);
+    if constexpr (MODE == kSplit) {
+      phi[j] = b.phi_src[x];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) gs[j][k] = src[k * ps + x];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        g[j][k] = split_fstar_t(p.omega[k], phi[j] + p.dtR, gs[j][k], p);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) g[j][k] = src[k * ps + x];
+    }
+  }
+  for (int l = 0; l < nsteps; ++l) {
+    A* e = edge + (l & 1) * 2 * nt;
+    e[tid] = g[M - 1][1];
+    e[nt + tid] = g[0][2];
+    __syncthreads();
+    const A from_left = e[left], from_right = e[nt + right];
+    A f[M][3];
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      f[j][0] = g[j][0];
+      f[j][1] = j == 0 ? from_left : g[j - 1][1];
+      f[j][2] = j == M - 1 ? from_right : g[j + 1][2];
+    }
+    if constexpr (WALL != 0) {
+      const double ref =
+          MODE == kFP32 ? p.phi_ref + p.R * (step_time(step + l, p.dt) + p.dt) : 0.0;
+#pragma unroll
+      for (int j = 0; j < M; ++j) {
+        const int x = first + tid * M + j;
+        if (x == 0)
+          f[j][1] = march_wall_value<MODE, HALF, 1, A, 1>(wx[2 * l], g[j][2], false, ref, p);
+        if (x == n0 - 1)
+          f[j][2] = march_wall_value<MODE, HALF, 2, A, 1>(wx[2 * l + 1], g[j][1], false, ref, p);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      if constexpr (MODE == kSplit) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) s += f[j][k];
+        phi[j] = s;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) gs[j][k] = static_cast<float>(f[j][k] - p.omega[k] * s);
+        const double t = s + p.dtR;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) g[j][k] = split_fstar_t(p.omega[k], t, gs[j][k], p);
+      } else {
+        collide_vals<1, A>(f[j], p);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) g[j][k] = f[j][k];
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < M; ++j) {
+    const int x = first + tid * M + j;
+    if (x < out0 || x >= out1) continue;
+    if constexpr (MODE == kSplit) b.phi_dst[x] = phi[j];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if constexpr (MODE == kSplit) dst[k * ps + x] = gs[j][k];
+      else dst[k * ps + x] = static_cast<T>(g[j][k]);
+    }
+  }
 }
 
 }  // namespace lbm

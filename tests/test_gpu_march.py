@@ -1,10 +1,12 @@
-"""Passes of several steps of d = 2 lattices: bitwise the states of single steps.
+"""Passes of several steps of d = 1 and 2 lattices: bitwise the states of single
+steps.
 
 The single-step kernels are the reference (they are held to the oracle
 elsewhere), so no tolerance enters.  Sizes sit at the edges of the passes' tiles:
 output widths of 48 (8 steps) and 56 (2 and 4 steps) columns, one row, one
 column, row chunks that end unevenly; step counts take every pass length and the
-single-step remainder."""
+single-step remainder.  d = 1: one node, the largest lattice held by one block
+(1024 nodes) and the first two cut into windows."""
 import pytest
 
 from paper_2410_13165_amd import inputs
@@ -41,6 +43,30 @@ def test_march_passes_equal_single_steps_bitwise(dims, bc, wall_data, precision)
             a.step(n)
             b.step(n)
             assert torch.equal(_node_state(a), _node_state(b)), n
+    finally:
+        a.close()
+        b.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_split"])
+@pytest.mark.parametrize("n,bc,wall_data", [
+    (1, "periodic", "jets"), (255, "periodic", "jets"), (1024, "periodic", "jets"),
+    (1025, "periodic", "jets"), (5000, "periodic", "jets"), (2, "fullway", "jets"),
+    (1024, "halfway", "jets"), (1025, "fullway", "tangential"), (1930, "halfway", "jets"),
+])
+def test_line_passes_equal_single_steps_bitwise(n, bc, wall_data, precision):
+    from paper_2410_13165_amd import Lattice
+    spec = inputs.random_cosines(1, [0.15], 0.7, seed=74, kmax=1.0)
+    kw = dict(dx=1.0 / max(n - 1, 1), u=spec["u"], R=spec["R"], bc=[bc], precision=precision,
+              field=spec, wall_data=wall_data)
+    a = Lattice(1, (n,), 0.5, **kw)
+    b = Lattice(1, (n,), 0.5, steps_per_pass=1, **kw)
+    try:
+        print(f"[line] n={n} {bc} {wall_data} {precision}", flush=True)
+        for steps in (1, 63, 1100):  # 1100: more than one launch of either form
+            a.step(steps)
+            b.step(steps)
+            assert torch.equal(_node_state(a), _node_state(b)), steps
     finally:
         a.close()
         b.close()
