@@ -60,6 +60,7 @@ struct lbm_handle {
   double* wall_ws = nullptr;    // wall data of wall_ws_steps steps (marching passes)
   int wall_ws_steps = 0;
   void* fuse_buf = nullptr;     // state_bytes: populations (+ phi in split mode)
+  void* fuse_buf2 = nullptr;    // the same after the second step (three-step passes)
   double* xdata2 = nullptr;     // split mode: x_1-face data of the second step
   int device = 0;               // current device at lbm_create
   // non-finite checks every check_every steps (0: off)
@@ -166,6 +167,8 @@ void release(lbm_handle* h) {
   h->nonfinite = nullptr;
   dev_free(h, h->kp.xdata);
   dev_free(h, h->fuse_buf);
+  dev_free(h, h->fuse_buf2);
+  h->fuse_buf2 = nullptr;
   dev_free(h, h->xdata2);
   dev_free(h, h->wall_ws);
   h->wall_ws = nullptr;
@@ -596,13 +599,6 @@ int step_checks(lbm_handle* h, int64_t n) {
   return LBM_OK;
 }
 
-// Pairs of steps in one bulk pass where the lattice allows it; while a tape
-// records checkpoints every `every` steps, pairs only when every is even and
-// the pair starts on an even offset, so that no checkpoint falls inside one.
-bool use_pairs(const lbm_handle* h) {
-  return h->steps_per_pass == 2 && (!h->tape_active || h->tape_every % 2 == 0);
-}
-
 // Scratch state of a two-step pass: the rows on and next to the Dirichlet
 // walls of x_2 / x_3 pass through it, so lattices without such walls need none.
 size_t pair_state_bytes(const lbm_handle* h) {
@@ -664,8 +660,16 @@ int64_t pass_limit(const lbm_handle* h, int64_t left) {
   return left;
 }
 
-int run_steps(lbm_handle* h, int64_t n, void* cbuf, double* xd2, double* wall_ws, int wall_cap) {
-  const bool pairs = use_pairs(h) && h->d == 3;
+// Three-step passes, where the lattice takes them and (with wall rows) the second
+// scratch state is there.
+bool use_tri(const lbm_handle* h) {
+  return h->multi && h->d == 3 && tri_applies(h->kp, h->precision);
+}
+
+int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2, double* wall_ws,
+              int wall_cap) {
+  const bool pairs = h->steps_per_pass == 2 && h->d == 3;
+  const bool tri = use_tri(h) && (h->kp.wall_rows == 0 || cbuf2);
   const bool march = use_march(h);
   const int64_t wx_len = wall_x(h), wy_len = wall_y(h);
   int64_t wall0 = 0, wall_n = 0;  // steps whose wall data the workspace holds
@@ -677,8 +681,12 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, double* xd2, double* wall_ws
   int64_t i = 0;
   while (i < n) {
     const int src = h->cur, dst = 1 - h->cur;
-    const bool aligned = !h->tape_active || (h->step - h->tape_start) % 2 == 0;
-    int64_t todo = (pairs && aligned && n - i >= 2) ? 2 : 1;
+    int64_t todo = 1;
+    if (pairs) {
+      // threes, but four steps as two pairs
+      const int64_t lim = pass_limit(h, n - i);
+      todo = tri && lim >= 3 && lim != 4 ? 3 : std::min<int64_t>(lim, 2);
+    }
     MarchPlan plan{1, 0};
     if (march) {
       const int64_t lim = std::min<int64_t>(pass_limit(h, n - i), wall_cap);
@@ -720,6 +728,9 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, double* xd2, double* wall_ws
         (void)hipEventRecord(ev[1], h->stream);
         (void)hipEventRecord(ev[2], h->stream);
       }
+    } else if (todo == 3) {
+      const TriBufs tb{h->buf[src], h->buf[dst], cbuf, cbuf2};
+      e = launch_tri(h->kp, h->precision, tb, h->step, h->stream, ev);
     } else if (todo == 2) {
       const FusedBufs fb{h->buf[src], h->buf[dst], cbuf, h->phib[src], h->phib[dst],
                          blob_phi(h, cbuf), xd2};
@@ -769,17 +780,20 @@ int lbm_step(lbm_handle* h, int64_t n) {
         dev_alloc(h, sizeof(double) * wall_doubles(h) * h->wall_ws_steps));
     if (!h->wall_ws) return fail(h, LBM_ENOMEM, "wall data of the marching passes");
   }
-  if (h->d == 3 && use_pairs(h) && n >= 2) {
+  if (h->d == 3 && h->steps_per_pass == 2 && n >= 2) {
     if (pair_state_bytes(h) > 0 && !h->fuse_buf) {
       h->fuse_buf = dev_alloc(h, pair_state_bytes(h));
       if (!h->fuse_buf) return fail(h, LBM_ENOMEM, "scratch state for two-step passes");
     }
+    // without room for the second scratch state the pairs go on
+    if (use_tri(h) && n >= 3 && pair_state_bytes(h) > 0 && !h->fuse_buf2)
+      h->fuse_buf2 = dev_alloc(h, pair_state_bytes(h));
     if (xdata_bytes(h) > 0 && !h->xdata2) {
       h->xdata2 = static_cast<double*>(dev_alloc(h, xdata_bytes(h)));
       if (!h->xdata2) return fail(h, LBM_ENOMEM, "x-face data for two-step passes");
     }
   }
-  return run_steps(h, n, h->fuse_buf, h->xdata2, h->wall_ws,
+  return run_steps(h, n, h->fuse_buf, h->fuse_buf2, h->xdata2, h->wall_ws,
                    wall_doubles(h) > 0 ? h->wall_ws_steps : wall_steps(h));
 }
 
@@ -787,9 +801,9 @@ int lbm_step_static(lbm_handle* h, int64_t n) {
   if (int rc = step_checks(h, n); rc != LBM_OK) return rc;
   if (h->tape_active)
     return fail(h, LBM_EINVAL, "lbm_step_static cannot record a tape (checkpoints are allocated)");
-  void* cbuf = nullptr;
+  void *cbuf = nullptr, *cbuf2 = nullptr;
   double* xd2 = nullptr;
-  if (use_pairs(h) && n >= 2) {
+  if (h->steps_per_pass == 2 && n >= 2) {
     const size_t cb = (pair_state_bytes(h) + 255) / 256 * 256;
     const size_t need = cb + xdata_bytes(h);
     if (need > kStaticScratchBytes)
@@ -802,6 +816,9 @@ int lbm_step_static(lbm_handle* h, int64_t n) {
       void* base = static_scratch(h->device, &err);
       if (!base) return hip_fail(h, err, "address of the static scratch");
       if (pair_state_bytes(h) > 0) cbuf = base;
+      // three-step passes take a second scratch state, where it fits
+      if (pair_state_bytes(h) > 0 && (need + 255) / 256 * 256 + cb <= kStaticScratchBytes)
+        cbuf2 = static_cast<char*>(base) + (need + 255) / 256 * 256;
       if (xdata_bytes(h) > 0) xd2 = reinterpret_cast<double*>(static_cast<char*>(base) + cb);
     }
   }
@@ -816,7 +833,7 @@ int lbm_step_static(lbm_handle* h, int64_t n) {
     wall_ws = static_cast<double*>(static_scratch(h->device, &err));
     if (!wall_ws) return hip_fail(h, err, "address of the static scratch");
   }
-  return run_steps(h, n, cbuf, xd2, wall_ws, std::max(wall_cap, 1));
+  return run_steps(h, n, cbuf, cbuf2, xd2, wall_ws, std::max(wall_cap, 1));
 }
 
 int lbm_moments(lbm_handle* h, uint32_t what, double* phi_out_dev, double* scalars_host) {

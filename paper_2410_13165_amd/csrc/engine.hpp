@@ -193,6 +193,23 @@ struct FusedBufs {
 hipError_t launch_fused_pair(const KParams& p, int mode, const FusedBufs& fb, long long n,
                              hipStream_t stream, hipEvent_t* ev = nullptr);
 
+// Buffers of a three-step pass: A at t_n, B at t_{n+3}, and with wall rows the
+// scratch states C1 and C2 for the rows on and next to the walls of x_2 / x_3 after
+// one and two steps (C1 also holds the second step's x_1-face data).
+struct TriBufs {
+  const void* A;
+  void* B;
+  void* C1;
+  void* C2;
+};
+// Three steps of a d = 3 lattice in one pass (tri.hpp); bitwise three
+// launch_step calls.  tri_applies: whether the pass takes the lattice (a plane of
+// x_3 under 4 GiB; x_1 walls only together with wall rows, whose scratch state
+// holds their data).
+bool tri_applies(const KParams& p, int mode);
+hipError_t launch_tri(const KParams& p, int mode, const TriBufs& tb, long long n,
+                      hipStream_t stream, hipEvent_t* ev = nullptr);
+
 // Initial state from the analytic field (phi0 == nullptr) or from device
 // arrays (grad0 == nullptr: fourth-order central differences).
 hipError_t launch_init(const KParams& p, int mode, void* dst, double* phi_dst,
