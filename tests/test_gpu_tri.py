@@ -1,9 +1,9 @@
 """Three-step passes of d = 3 lattices: bitwise the states of single steps.
 
 The single-step kernels are the reference, so no tolerance enters.  Sizes sit at
-the edges of the passes' tiles (64 x 11, 64 x 7 and 32 x 10 columns, 32 x 14 in
-split storage), at the fewest planes a march can have, and at walls two and three
-rows apart; the step counts take 3, 3 + 1 as 2 + 2, 3 + 2, 3 + 3 + 1 as 3 + 2 + 2,
+the edges of the passes' tiles (64 x 11, 64 x 7 and 32 x 10 columns), at the fewest
+planes a march can have, and at walls two and three rows apart (lattices with walls
+are as large as the passes take them, 1.5 million nodes); the step counts take 3, 3 + 1 as 2 + 2, 3 + 2, 3 + 3 + 1 as 3 + 2 + 2,
 and several passes in a row."""
 import pytest
 
@@ -22,15 +22,15 @@ torch = pytest.importorskip("torch")
     ((64, 11, 5), ["periodic"] * 3, "jets"),
     ((65, 12, 3), ["periodic"] * 3, "jets"),
     ((33, 29, 140), ["periodic"] * 3, "jets"),
-    ((64, 22, 9), ["fullway"] * 3, "jets"),
-    ((32, 10, 2), ["fullway"] * 3, "jets"),
-    ((66, 15, 3), ["halfway"] * 3, "jets"),
-    ((31, 2, 12), ["halfway"] * 3, "jets"),
-    ((3, 3, 40), ["fullway"] * 3, "jets"),
-    ((70, 24, 20), ["halfway", "periodic", "halfway"], "tangential"),
-    ((40, 13, 17), ["periodic", "fullway", "periodic"], "jets"),
-    ((45, 11, 16), ["fullway", "periodic", "periodic"], "jets"),
-    ((40, 30, 20), ["periodic", "periodic", "halfway"], "jets"),
+    ((128, 121, 97), ["fullway"] * 3, "jets"),
+    ((1601, 480, 2), ["fullway"] * 3, "jets"),
+    ((1601, 313, 3), ["halfway"] * 3, "jets"),
+    ((31, 2, 24500), ["halfway"] * 3, "jets"),
+    ((2, 3, 250001), ["fullway"] * 3, "jets"),
+    ((129, 99, 118), ["halfway", "periodic", "halfway"], "tangential"),
+    ((160, 78, 121), ["periodic", "fullway", "periodic"], "jets"),
+    ((45, 11, 3100), ["fullway", "periodic", "periodic"], "jets"),
+    ((100, 150, 101), ["periodic", "periodic", "halfway"], "jets"),
 ])
 def test_tri_passes_equal_single_steps_bitwise(dims, bc, wall_data, precision):
     from paper_2410_13165_amd import Lattice
@@ -51,11 +51,11 @@ def test_tri_passes_equal_single_steps_bitwise(dims, bc, wall_data, precision):
 
 
 @pytest.mark.parametrize("bc", ["fullway", "halfway"])
-def test_tri_passes_in_the_static_scratch(bc):
-    """lbm_step_static holds both scratch states of this lattice in its fixed
-    scratch, and gives the states of lbm_step."""
+def test_static_scratch_without_room_for_three_steps(bc):
+    """lbm_step_static, whose fixed scratch holds one scratch state of this lattice
+    but not two, gives the states of lbm_step."""
     spec = inputs.random_cosines(3, [0.05, -0.1, 0.08], 0.7, seed=76, kmax=1.0)
-    lats = [gpu_lattice(3, (50, 33, 21), 1 / 49, spec, bc=[bc] * 3, precision="fp32")
+    lats = [gpu_lattice(3, (120, 113, 112), 1 / 119, spec, bc=[bc] * 3, precision="fp32")
             for _ in range(2)]
     try:
         lats[0].step(10)
