@@ -30,9 +30,21 @@
 //     f_h = 1 - sum_{g != h} v_g / (lambda - a tau_g).
 // All but one root sit near the poles a tau_g (exactly so for s -> 1, where
 // they collapse to 0); the remaining one carries the conserved mode (1 at
-// xi = 0) and starts from sum_g v_g + a mean(tau).  One thread
-// takes one wave number; a block reduces the maximum over the grid of one
-// parameter point.
+// xi = 0) and starts from sum_g v_g + a mean(tau).
+//
+// One thread takes one wave number.  G(-xi) is the complex conjugate of G(xi), so
+// only the wave numbers with j_d <= m / 2 are visited, those strictly inside
+// standing for two.  A block is one wavefront; stab_split deals the wave numbers to
+// blocks.
+//
+// The kernel is bound by float64 arithmetic: per sweep two complex reciprocals for
+// each pair of groups.  No array that a run-time index walks is private: the roots
+// lie in LDS, and the groups in registers or LDS (kStabListed), where the scratch
+// traffic of private arrays bound the kernel before.  A reciprocal is the hardware's
+// estimate with two Newton steps.  Calls at s = 2, before and after: 61^2 points of
+// D2Q9, m = 16, 6.2 and 1.3 ms; 9^2, m = 8, 400 and 210 us; 13^3 of D3Q19, m = 12,
+// 57 and 20.6 ms; 300000 of D1Q3, m = 16, 10.7 and 0.9 ms; 1 point of D2Q9, m = 256,
+// 120 and 0.24 ms (there for the split over blocks).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -54,71 +66,128 @@ __device__ __forceinline__ cplx cmul(cplx a, cplx b) {
   return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
 __device__ __forceinline__ cplx cscale(cplx a, double r) { return {a.re * r, a.im * r}; }
+// 1 / x: the estimate refined to rounding (0 gives a non-finite value, which the
+// iteration catches)
+__device__ __forceinline__ double recip(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
 __device__ __forceinline__ cplx cinv(cplx a) {
-  const double n = a.re * a.re + a.im * a.im;
-  return {a.re / n, -a.im / n};
+  const double r = recip(a.re * a.re + a.im * a.im);
+  return {a.re * r, -a.im * r};
 }
 __device__ __forceinline__ cplx cdiv(cplx a, cplx b) { return cmul(a, cinv(b)); }
 __device__ __forceinline__ double cabs2(cplx a) { return a.re * a.re + a.im * a.im; }
 __device__ __forceinline__ bool cfinite(cplx a) { return isfinite(a.re) && isfinite(a.im); }
 
-constexpr int kStabThreads = 256;
 constexpr int kAberthSweeps = 200;
 constexpr double kAberthTol = 1e-14;
 constexpr double kAberthFloor = 1e-12;
 
+// Where the groups live.  d <= 2: at the velocity that leads them, in registers; the
+// places of velocities that lead none are computed and masked off.  d >= 3: listed in
+// LDS, since most of the q places would be empty (m = 8 has at most 8 groups of
+// D3Q19's 19 or D4Q33's 33 velocities): at 300 points of D3Q19, m = 8, the registers'
+// form took 3759 us.
+template <int D>
+constexpr bool kStabListed = D >= 3;
+// Bytes of LDS per lane and group
+template <int D>
+constexpr int kStabBytes = kStabListed<D> ? 40 : 16;
+
 // rho(G(xi)) at xi = 2 pi j / m; *converged is false when the iteration did
-// not settle within kAberthSweeps sweeps.
+// not settle within kAberthSweeps sweeps.  roots: this lane's LDS column, root i
+// at roots[64 i]; taus and sws, used if kStabListed<D>, likewise.
 template <int D>
 __device__ double rho_at(const double (&w)[q_of(D)], double s, const int (&j)[kMaxDim], int m,
-                         bool* converged) {
+                         cplx* roots, cplx* taus, double* sws, bool* converged) {
   constexpr int Q = q_of(D);
+  constexpr bool LISTED = kStabListed<D>;
+  const double a = 1.0 - s;
+  double rho = 0.0;
+  // group of velocity k: led by the first velocity with its phase
   int key[Q];
-  double W[Q];
-  int cnt[Q];
-  int n = 0;
   static_for<0, Q>([&](auto K) {
     constexpr int k = decltype(K)::value;
     int ph = 0;
 #pragma unroll
-    for (int a = 0; a < D; ++a) ph += vel_comp(D, k, a) * j[a];
+    for (int b = 0; b < D; ++b) ph += vel_comp(D, k, b) * j[b];
     ph %= m;
-    if (ph < 0) ph += m;
-    int g = 0;
-    while (g < n && key[g] != ph) ++g;
-    if (g == n) {
-      key[n] = ph;
-      W[n] = 0.0;
-      cnt[n] = 0;
-      ++n;
-    }
-    W[g] += w[k];
-    cnt[g] += 1;
+    key[k] = ph < 0 ? ph + m : ph;
   });
-  const double a = 1.0 - s;
-  double rho = 0.0;
-  cplx pole[Q], v[Q], lam[Q];
+  cplx pole_r[Q], v_r[Q];
+  unsigned long long active = 0;
   int ng = 0;
-  for (int g = 0; g < n; ++g) {
+  static_for<0, Q>([&](auto K) {
+    constexpr int k = decltype(K)::value;
+    bool lead = true;
+#pragma unroll
+    for (int e = 0; e < k; ++e) lead = lead && key[e] != key[k];
+    double W = 0.0;
+    int cnt = 0;
+#pragma unroll
+    for (int e = k; e < Q; ++e) {
+      const bool same = key[e] == key[k];
+      W += same ? w[e] : 0.0;
+      cnt += same ? 1 : 0;
+    }
     // (1 - s) tau_g from the zero-sum vectors of a group, and from a group
     // whose weights cancel (its pole is then a root)
-    if (cnt[g] > 1 || W[g] == 0.0) rho = fmax(rho, fabs(a));
-    if (W[g] == 0.0) continue;
+    if (lead && (cnt > 1 || W == 0.0)) rho = fmax(rho, fabs(a));
+    const bool on = lead && W != 0.0;
     double sn, cs;
-    sincospi(2.0 * key[g] / m, &sn, &cs);
+    sincospi(2.0 * key[k] / m, &sn, &cs);
     const cplx tau{cs, -sn};
-    pole[ng] = cscale(tau, a);
-    v[ng] = cscale(tau, s * W[g]);
-    ++ng;
-  }
+    if constexpr (LISTED) {
+      if (on) {
+        taus[64 * ng] = tau;
+        sws[64 * ng] = s * W;
+      }
+    } else {
+      pole_r[k] = cscale(tau, a);
+      v_r[k] = on ? cscale(tau, s * W) : cplx{0.0, 0.0};
+      active |= on ? 1ull << k : 0ull;
+    }
+    ng += on ? 1 : 0;
+  });
+  const int places = LISTED ? ng : Q;
+  const auto is_on = [&](int k) { return LISTED || ((active >> k) & 1); };
+  const auto pole = [&](int k) {
+    if constexpr (LISTED) return cscale(taus[64 * k], a);
+    else return pole_r[k];
+  };
+  const auto v = [&](int k) {
+    if constexpr (LISTED) return cscale(taus[64 * k], sws[64 * k]);
+    else return v_r[k];
+  };
+  const auto each = [&](auto body) {
+    if constexpr (LISTED) {
+#pragma unroll 2
+      for (int k = 0; k < ng; ++k) body(k);
+    } else {
+      static_for<0, Q>([&](auto K) { body(K); });
+    }
+  };
   *converged = true;
   if (ng == 0) return rho;
-  if (a == 0.0) {
-    // all poles at 0: p(lambda) = lambda^(ng-1) (lambda - sum_g v_g)
-    cplx sum{0.0, 0.0};
-    for (int g = 0; g < ng; ++g) sum = cadd(sum, v[g]);
-    return fmax(rho, sqrt(cabs2(sum)));
-  }
+  cplx vsum{0.0, 0.0}, psum{0.0, 0.0};
+  int big = 0;
+  double vbig = -1.0;
+  each([&](auto k_) {
+      const int k = k_;
+    const bool on = is_on(k);
+    vsum = cadd(vsum, v(k));
+    psum.re += on ? pole(k).re : 0.0;
+    psum.im += on ? pole(k).im : 0.0;
+    const double vg = cabs2(v(k));
+    if (on && vg > vbig) {
+      vbig = vg;
+      big = k;
+    }
+  });
+  // all poles at 0: p(lambda) = lambda^(ng-1) (lambda - sum_g v_g)
+  if (a == 0.0) return fmax(rho, sqrt(cabs2(vsum)));
   // Start: ng - 1 roots just beside the poles (scaled by 1.01, turned by
   // pi / (4 ng)); the one of the largest |v_g| is replaced by the estimate of
   // the root that carries the conserved mode, sum_g v_g + a mean(tau).
@@ -126,58 +195,61 @@ __device__ double rho_at(const double (&w)[q_of(D)], double s, const int (&j)[kM
     double sn, cs;
     sincospi(0.25 / ng, &sn, &cs);
     const cplx turn{1.01 * cs, 1.01 * sn};
-    cplx vsum{0.0, 0.0}, psum{0.0, 0.0};
-    int big = 0;
-    double vbig = -1.0;
-    for (int g = 0; g < ng; ++g) {
-      lam[g] = cmul(pole[g], turn);
-      vsum = cadd(vsum, v[g]);
-      psum = cadd(psum, pole[g]);
-      const double vg = cabs2(v[g]);
-      if (vg > vbig) {
-        vbig = vg;
-        big = g;
-      }
-    }
-    lam[big] = cadd(cadd(vsum, cscale(psum, 1.0 / ng)), cplx{0.0, 1e-3});
+    each([&](auto k_) {
+      const int k = k_;
+      roots[64 * k] = cmul(pole(k), turn);
+    });
+    roots[64 * big] = cadd(cadd(vsum, cscale(psum, 1.0 / ng)), cplx{0.0, 1e-3});
   }
   bool done = false;
   double prev = INFINITY;
   for (int it = 0; it < kAberthSweeps && !done; ++it) {
     double worst = 0.0;
-    for (int i = 0; i < ng; ++i) {
-      const cplx z = lam[i];
+    for (int i = 0; i < places; ++i) {
+      if (!is_on(i)) continue;
+      const cplx z = roots[64 * i];
       // nearest pole h, kept out of the sums so that nothing blows up near it
-      int h = 0;
-      double dh = cabs2(csub(z, pole[0]));
-      for (int g = 1; g < ng; ++g) {
-        const double dg = cabs2(csub(z, pole[g]));
-        if (dg < dh) {
-          dh = dg;
-          h = g;
-        }
-      }
-      cplx f{1.0, 0.0}, fp{0.0, 0.0}, S{0.0, 0.0};
-      for (int g = 0; g < ng; ++g) {
-        if (g == h) continue;
-        const cplx inv = cinv(csub(z, pole[g]));
-        const cplx vi = cmul(v[g], inv);
+      int h = -1;
+      double dh = INFINITY;
+      cplx ph{0.0, 0.0}, vh{0.0, 0.0};
+      each([&](auto g_) {
+      const int g = g_;
+        const double dg = cabs2(csub(z, pole(g)));
+        const bool nearer = is_on(g) && (dg < dh || h < 0);
+        dh = nearer ? dg : dh;
+        h = nearer ? g : h;
+        ph.re = nearer ? pole(g).re : ph.re;
+        ph.im = nearer ? pole(g).im : ph.im;
+        vh.re = nearer ? v(g).re : vh.re;
+        vh.im = nearer ? v(g).im : vh.im;
+      });
+      cplx f{1.0, 0.0}, fp{0.0, 0.0}, S{0.0, 0.0}, ab{0.0, 0.0};
+      each([&](auto g_) {
+      const int g = g_;
+        const bool on = is_on(g);
+        cplx inv = cinv(csub(z, pole(g)));
+        const bool keep = on && g != h;
+        inv.re = keep ? inv.re : 0.0;
+        inv.im = keep ? inv.im : 0.0;
+        const cplx vi = cmul(v(g), inv);
         f = csub(f, vi);
         fp = cadd(fp, cmul(vi, inv));
         S = cadd(S, inv);
-      }
+        const cplx il = cinv(csub(z, roots[64 * g]));
+        const bool other = on && g != i;
+        ab.re += other ? il.re : 0.0;
+        ab.im += other ? il.im : 0.0;
+      });
       // p / p' with p = prod_{g != h} (z - pole_g) [(z - pole_h) f_h - v_h]
-      const cplx e = csub(z, pole[h]);
-      const cplx num = csub(cmul(e, f), v[h]);
-      const cplx den = csub(cadd(f, cmul(e, cadd(cmul(S, f), fp))), cmul(v[h], S));
+      const cplx e = csub(z, ph);
+      const cplx num = csub(cmul(e, f), vh);
+      const cplx den = csub(cadd(f, cmul(e, cadd(cmul(S, f), fp))), cmul(vh, S));
       const cplx N = cdiv(num, den);
-      cplx ab{0.0, 0.0};
-      for (int l = 0; l < ng; ++l)
-        if (l != i) ab = cadd(ab, cinv(csub(z, lam[l])));
       cplx corr = cdiv(N, csub(cplx{1.0, 0.0}, cmul(N, ab)));
       if (!cfinite(corr)) corr = cplx{1e-8, 1e-8};  // landed on a pole or a root
-      lam[i] = csub(z, corr);
-      const double rel = sqrt(cabs2(corr)) / fmax(1.0, sqrt(cabs2(lam[i])));
+      const cplx next = csub(z, corr);
+      roots[64 * i] = next;
+      const double rel = sqrt(cabs2(corr)) / fmax(1.0, sqrt(cabs2(next)));
       worst = fmax(worst, rel);
     }
     // settled: corrections below the tolerance, or at the rounding floor
@@ -186,60 +258,110 @@ __device__ double rho_at(const double (&w)[q_of(D)], double s, const int (&j)[kM
     prev = worst;
   }
   *converged = done;
-  for (int g = 0; g < ng; ++g) {
-    if (!cfinite(lam[g])) {
+  for (int g = 0; g < places; ++g) {
+    if (!is_on(g)) continue;
+    const cplx l = roots[64 * g];
+    if (!cfinite(l)) {
       *converged = false;
       return INFINITY;
     }
-    rho = fmax(rho, sqrt(cabs2(lam[g])));
+    rho = fmax(rho, sqrt(cabs2(l)));
   }
   return rho;
 }
 
+// How the wave numbers (nh per point) are dealt to blocks of one wavefront: `points` whole
+// points to a block, or, if the call is too small to fill the chip so, one point to `parts`
+// blocks.  81 points of D2Q9, m = 8, and 300 of D3Q19, m = 8, take 210 and 485 us in parts.
+struct StabSplit {
+  int points, parts;
+};
+// Two wavefronts per SIMD; four rounds of a block leave at most a fifth of its last one
+// idle.
+constexpr long long kStabFill = 2048;
+constexpr int kStabRounds = 4, kStabMaxPoints = 64;
+StabSplit stab_split(long long nh, long long count) {
+  const long long rounds = (nh + 63) / 64;
+  if (rounds > 1 && count < kStabFill) {
+    const long long parts = (kStabFill + count - 1) / count;
+    return {1, static_cast<int>(parts < rounds ? parts : rounds)};
+  }
+  int p = 1;
+  while (p < kStabMaxPoints && p * nh < 64 * kStabRounds && (p + 1) * kStabFill / 2 <= count) ++p;
+  return {p, 1};
+}
+
+// The outputs of a call whose points are split over blocks, which accumulate them.
+__global__ void k_stability_clear(long long count, double* __restrict__ rho_out,
+                                  int32_t* __restrict__ unconv_out) {
+  const long long i = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= count) return;
+  rho_out[i] = 0.0;
+  if (unconv_out) unconv_out[i] = 0;
+}
+
 template <int D>
-__global__ void __launch_bounds__(kStabThreads)
+__global__ void __launch_bounds__(64)
     k_stability(const double* __restrict__ sigma, const double* __restrict__ s_arr, double gm4,
-                int m, long long nxi, double* __restrict__ rho_out,
-                double* __restrict__ min_omega_out, int32_t* __restrict__ unconv_out) {
+                int m, long long nh, long long count, StabSplit split, int groups,
+                double* __restrict__ rho_out, double* __restrict__ min_omega_out, int32_t* __restrict__ unconv_out) {
   constexpr int Q = q_of(D);
-  const long long pt = blockIdx.x;
-  double u[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
+  extern __shared__ __align__(16) unsigned char stab_lds[];  // kStabBytes<D> x 64 x groups
+  cplx* const roots = reinterpret_cast<cplx*>(stab_lds);
+  cplx* const taus = roots + 64 * groups;
+  double* const sws = reinterpret_cast<double*>(taus + 64 * groups);
+  __shared__ unsigned long long best[kStabMaxPoints];  // rho as its bits: rho >= 0
+  __shared__ int bad[kStabMaxPoints];
+  const int lane = threadIdx.x;
+  const long long p0 = blockIdx.x / split.parts * static_cast<long long>(split.points);
+  const int part = blockIdx.x % split.parts;
+  const int here = static_cast<int>(min(static_cast<long long>(split.points), count - p0));
+  if (lane < here) {
+    best[lane] = 0ull;
+    bad[lane] = 0;
+  }
+  __syncthreads();
+  const int half = m / 2 + 1;
+  for (long long e = part * 64 + lane; e < here * nh; e += 64 * split.parts) {
+    const int pl = static_cast<int>(e / nh);
+    const long long pt = p0 + pl;
+    double u[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int a = 0; a < D; ++a) u[a] = sigma[pt * D + a];
-  const double s = s_arr[pt];
-  const double m4 = (D >= 2) ? m4_interpolated(D, u, gm4) : 0.0;
-  double w[Q];
-  omega_closed_form(D, u, m4, w);
-  double best = 0.0;
-  int bad = 0;
-  for (long long e = threadIdx.x; e < nxi; e += blockDim.x) {
+    for (int a = 0; a < D; ++a) u[a] = sigma[pt * D + a];
+    const double m4 = (D >= 2) ? m4_interpolated(D, u, gm4) : 0.0;
+    double w[Q];
+    omega_closed_form(D, u, m4, w);
+    long long r = e - pl * nh;
     int j[kMaxDim] = {0, 0, 0, 0};
-    long long r = e;
+    j[D - 1] = static_cast<int>(r % half);
+    r /= half;
 #pragma unroll
-    for (int a = 0; a < D; ++a) {
+    for (int a = 0; a < D - 1; ++a) {
       j[a] = static_cast<int>(r % m);
       r /= m;
     }
     bool ok = true;
-    best = fmax(best, rho_at<D>(w, s, j, m, &ok));
-    bad += ok ? 0 : 1;
+    const double rho = rho_at<D>(w, s_arr[pt], j, m, roots + lane, taus + lane, sws + lane, &ok);
+    atomicMax(&best[pl], static_cast<unsigned long long>(__double_as_longlong(rho)));
+    // a wave number strictly inside stands for its mirror image too
+    if (!ok) atomicAdd(&bad[pl], j[D - 1] == 0 || 2 * j[D - 1] == m ? 1 : 2);
   }
-  __shared__ double sb[kStabThreads];
-  __shared__ int si[kStabThreads];
-  sb[threadIdx.x] = best;
-  si[threadIdx.x] = bad;
   __syncthreads();
-  for (int h = kStabThreads / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) {
-      sb[threadIdx.x] = fmax(sb[threadIdx.x], sb[threadIdx.x + h]);
-      si[threadIdx.x] += si[threadIdx.x + h];
+  if (lane < here) {
+    const long long pt = p0 + lane;
+    if (split.parts > 1) {
+      atomicMax(reinterpret_cast<unsigned long long*>(rho_out) + pt, best[lane]);
+      if (unconv_out && bad[lane]) atomicAdd(unconv_out + pt, bad[lane]);
+    } else {
+      rho_out[pt] = __longlong_as_double(static_cast<long long>(best[lane]));
+      if (unconv_out) unconv_out[pt] = bad[lane];
     }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    rho_out[pt] = sb[0];
-    if (unconv_out) unconv_out[pt] = si[0];
-    if (min_omega_out) {
+    if (min_omega_out && part == 0) {
+      double u[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int a = 0; a < D; ++a) u[a] = sigma[pt * D + a];
+      double w[Q];
+      omega_closed_form(D, u, (D >= 2) ? m4_interpolated(D, u, gm4) : 0.0, w);
       double mw = w[0];
 #pragma unroll
       for (int k = 1; k < Q; ++k) mw = fmin(mw, w[k]);
@@ -248,33 +370,47 @@ __global__ void __launch_bounds__(kStabThreads)
   }
 }
 
+template <int D>
+hipError_t stability_pass(long long count, const double* sigma, const double* s, double g, int m,
+                          long long nxi, double* rho, double* min_omega, int32_t* unconverged,
+                          hipStream_t stream) {
+  const long long nh = nxi / m * (m / 2 + 1);
+  const StabSplit split = stab_split(nh, count);
+  // no wave number has more groups than phases or velocities
+  const int groups = kStabListed<D> && m < q_of(D) ? m : q_of(D);
+  constexpr int most = kStabBytes<D> * 64 * q_of(D);
+  if constexpr (most > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_stability<D>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (e != hipSuccess) return e;
+  }
+  const unsigned blocks =
+      static_cast<unsigned>((count + split.points - 1) / split.points * split.parts);
+  if (split.parts > 1)
+    hipLaunchKernelGGL(k_stability_clear, dim3(static_cast<unsigned>((count + 255) / 256)),
+                       dim3(256), 0, stream, count, rho, unconverged);
+  hipLaunchKernelGGL(k_stability<D>, dim3(blocks), dim3(64), kStabBytes<D> * 64 * groups, stream,
+                     sigma, s, g, m, nh, count, split, groups, rho, min_omega, unconverged);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_stability(int d, long long count, const double* sigma, const double* s,
                             double g, int m, long long nxi, double* rho, double* min_omega,
                             int32_t* unconverged, hipStream_t stream) {
-  const dim3 grid(static_cast<unsigned>(count)), block(kStabThreads);
   switch (d) {
     case 1:
-      hipLaunchKernelGGL(k_stability<1>, grid, block, 0, stream, sigma, s, g, m, nxi, rho,
-                         min_omega, unconverged);
-      break;
+      return stability_pass<1>(count, sigma, s, g, m, nxi, rho, min_omega, unconverged, stream);
     case 2:
-      hipLaunchKernelGGL(k_stability<2>, grid, block, 0, stream, sigma, s, g, m, nxi, rho,
-                         min_omega, unconverged);
-      break;
+      return stability_pass<2>(count, sigma, s, g, m, nxi, rho, min_omega, unconverged, stream);
     case 3:
-      hipLaunchKernelGGL(k_stability<3>, grid, block, 0, stream, sigma, s, g, m, nxi, rho,
-                         min_omega, unconverged);
-      break;
+      return stability_pass<3>(count, sigma, s, g, m, nxi, rho, min_omega, unconverged, stream);
     case 4:
-      hipLaunchKernelGGL(k_stability<4>, grid, block, 0, stream, sigma, s, g, m, nxi, rho,
-                         min_omega, unconverged);
-      break;
+      return stability_pass<4>(count, sigma, s, g, m, nxi, rho, min_omega, unconverged, stream);
     default:
       return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace lbm

@@ -35,6 +35,23 @@ def test_map_matches_oracle_eigenvalues(d, count, m):
         assert abs(got["min_omega"][i] - O.min_omega(sigma[i])) <= 1e-14
 
 
+@pytest.mark.parametrize("d,count,m", [(1, 70001, 3), (1, 5, 130), (2, 2049, 5), (2, 2, 41),
+                                       (3, 2, 20), (3, 2100, 2), (4, 1, 5)])
+def test_map_split_over_blocks(d, count, m):
+    """Many points to a block, a last block that is not full, one point on many
+    blocks, more phases than velocities: rho of the last points against the oracle."""
+    rng = np.random.default_rng(7 + m)
+    sigma = rng.uniform(-0.65, 0.65, size=(count, d))
+    s = rng.uniform(0.2, 2.0, size=count)
+    print(f"[stability] split d={d} count={count} m={m}", flush=True)
+    got = _gpu_map(sigma, s, m)
+    assert np.all(got["unconverged"] == 0)
+    for i in sorted({0, count // 2, max(count - 2, 0), count - 1}):
+        want = O.spectral_radius_grid(sigma[i], float(s[i]), m)
+        assert abs(got["rho"][i] - want) <= 1e-12 * max(1.0, want), i
+        assert abs(got["min_omega"][i] - O.min_omega(sigma[i])) <= 1e-14
+
+
 def test_map_g_weight_and_xi_zero():
     """m = 1 is xi = 0 only: rho = max(1, |1 - s|); the weight g of eq. (meq-4rd)
     changes m4 and with it omega and rho."""
