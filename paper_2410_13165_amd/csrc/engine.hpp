@@ -186,6 +186,16 @@ struct FusedBufs {
   double* xdata2;
 };
 
+// The x_1-face data of up to three steps, one launch of k_xface (blockIdx.y = step):
+// step i's go to the row slots of buf[i] or (split layout) to xdata[i], for the step
+// that starts at t[i].
+struct XfaceSteps {
+  int count = 1;
+  void* buf[3] = {};
+  double* xdata[3] = {};
+  double t[3] = {};
+};
+
 // Two steps t_n -> t_{n+2} of a lattice with d = 3 (any mode) in one pass of
 // the bulk kernel (k_fused2, k_fused2_split).  Bitwise equal to two
 // launch_step calls.  ev (nullable): three events around the fused kernel and

@@ -119,8 +119,7 @@ static unsigned grid_for(long long nodes, int threads) {
 // Launches of the wall kernels (defined in walls.hpp, instantiated in
 // walls_d*.hip, translation units of their own).
 template <int D, class T, bool TAN>
-void launch_xface(unsigned blocks, hipStream_t stream, T* buf, const KParams& p, double t,
-                  int mode);
+void launch_xface(hipStream_t stream, const XfaceSteps& xs, const KParams& p, int mode);
 template <int D, class T, bool TAN>
 void launch_wall(dim3 g, dim3 b, hipStream_t stream, const T* src, T* dst, const KParams& p,
                  double t);
@@ -140,13 +139,11 @@ static hipError_t step_dt(const KParams& p, int mode, const void* src, void* dst
     if (ev) (void)hipEventRecord(ev[i], stream);
   };
   if (p.bc[0] != 0) {
-    const unsigned xb = static_cast<unsigned>((2 * p.rows + 255) / 256);
+    const XfaceSteps xs{1, {const_cast<void*>(src)}, {p.xdata}, {t_n}};
     if (mode == kFP64)
-      launch_xface<D, double, TAN>(xb, stream, static_cast<double*>(const_cast<void*>(src)), p,
-                                   t_n, mode);
+      launch_xface<D, double, TAN>(stream, xs, p, mode);
     else
-      launch_xface<D, float, TAN>(xb, stream, static_cast<float*>(const_cast<void*>(src)), p,
-                                  t_n, mode);
+      launch_xface<D, float, TAN>(stream, xs, p, mode);
   }
   mark(0);
   if (mode == kFP64) {
@@ -216,11 +213,8 @@ static hipError_t fused_pair_t(const KParams& p, const T* A, T* B, T* C, long lo
   auto mark = [&](int i) {
     if (ev) (void)hipEventRecord(ev[i], stream);
   };
-  if (p.bc[0] != 0) {
-    const unsigned xb = static_cast<unsigned>((2 * p.rows + 255) / 256);
-    launch_xface<3, T, TAN>(xb, stream, const_cast<T*>(A), p, t0, mode);
-    launch_xface<3, T, TAN>(xb, stream, B, p, t1, mode);
-  }
+  if (p.bc[0] != 0)
+    launch_xface<3, T, TAN>(stream, XfaceSteps{2, {const_cast<T*>(A), B}, {}, {t0, t1}}, p, mode);
   if (p.wall_rows > 0)
     launch_wall<3, T, TAN>(wgrid, block, stream, A, C, p, t0);
   const int tiles_xy = ((p.n[0] + S::TX - 1) / S::TX) * ((p.n[1] + S::TY - 1) / S::TY);
@@ -265,16 +259,11 @@ static hipError_t fused_pair_split(const KParams& p, const FusedBufs& fb, long l
   auto mark = [&](int i) {
     if (ev) (void)hipEventRecord(ev[i], stream);
   };
-  if (p.bc[0] != 0) {
-    // the x_1-face data of the split mode live in p.xdata; the second step's
-    // go to the second array
-    KParams p2 = p;
-    p2.xdata = fb.xdata2;
-    const unsigned xb = static_cast<unsigned>((2 * p.rows + 255) / 256);
-    launch_xface<3, float, TAN>(xb, stream, const_cast<float*>(gA), p, t0,
+  // the x_1-face data of the split mode live in p.xdata; the second step's go to the
+  // second array
+  if (p.bc[0] != 0)
+    launch_xface<3, float, TAN>(stream, XfaceSteps{2, {}, {p.xdata, fb.xdata2}, {t0, t1}}, p,
                                 static_cast<int>(kSplit));
-    launch_xface<3, float, TAN>(xb, stream, gB, p2, t1, static_cast<int>(kSplit));
-  }
   if (p.wall_rows > 0)
     launch_wall_split<3, TAN, PT>(wgrid, block, stream, gA, gC, pA, pC, p, t0);
   const int tiles_xy = ((p.n[0] + S::TX - 1) / S::TX) * ((p.n[1] + S::TY - 1) / S::TY);

@@ -529,7 +529,10 @@ __device__ __forceinline__ void wall_values(A (&f)[q_of(D)], const KParams& p, c
 // mode keeps float64 values in p.xdata[(side * (2D-1) + slot) * rows + row].
 template <int D, class T, bool TAN, int V>
 __global__ void __launch_bounds__(256)
-    k_xface(T* __restrict__ buf, const KParams p, const double t_n, const int mode) {
+    k_xface(const XfaceSteps xs, const KParams p, const int mode) {
+  T* __restrict__ const buf = static_cast<T*>(xs.buf[blockIdx.y]);
+  double* __restrict__ const xdata = xs.xdata[blockIdx.y];
+  const double t_n = xs.t[blockIdx.y];
   constexpr int S = 2 * D - 1;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= 2 * p.rows) return;
@@ -559,7 +562,7 @@ __global__ void __launch_bounds__(256)
     } else {
       if (cx != want) return;
       if (split_layout(mode)) {
-        p.xdata[((long long)side * S + xface_slot(D, k)) * p.rows + row] = val[k];
+        xdata[((long long)side * S + xface_slot(D, k)) * p.rows + row] = val[k];
       } else {
         constexpr int kb = opp_index(D, k);
         const double w = half ? p.omega[k] + p.omega[kb] : p.omega[k];

@@ -7,8 +7,7 @@ namespace lbm {
 
 // wall-row and x_1-face launches (walls.hpp, instantiated in walls_d*.hip)
 template <int D, class T, bool TAN>
-void launch_xface(unsigned blocks, hipStream_t stream, T* buf, const KParams& p, double t,
-                  int mode);
+void launch_xface(hipStream_t stream, const XfaceSteps& xs, const KParams& p, int mode);
 template <int D, class T, bool TAN>
 void launch_wall(dim3 g, dim3 b, hipStream_t stream, const T* src, T* dst, const KParams& p,
                  double t);
@@ -80,12 +79,8 @@ static hipError_t tri_t(const KParams& p, const TriBufs& tb, long long n, hipStr
   const dim3 block(s.tx, s.ty);
   const dim3 wgrid(static_cast<unsigned>((p.wall_rows + s.ty - 1) / s.ty));
   auto t = [&](int i) { return static_cast<double>(n + i) * p.dt; };
-  if (p.bc[0] != 0) {
-    const unsigned xb = static_cast<unsigned>((2 * p.rows + 255) / 256);
-    launch_xface<3, T, TAN>(xb, stream, A, p, t(0), mode);
-    launch_xface<3, T, TAN>(xb, stream, C1, p, t(1), mode);
-    launch_xface<3, T, TAN>(xb, stream, B, p, t(2), mode);
-  }
+  if (p.bc[0] != 0)
+    launch_xface<3, T, TAN>(stream, XfaceSteps{3, {A, C1, B}, {}, {t(0), t(1), t(2)}}, p, mode);
   if (p.wall_rows > 0) {
     launch_wall<3, T, TAN>(wgrid, block, stream, A, C1, p, t(0));
     const int near = (p.bc[1] != 0 ? 2 * p.n[2] : 0) + (p.bc[2] != 0 ? 2 * p.n[1] : 0);

@@ -12,17 +12,16 @@ namespace lbm {
 // Per-variant launches of the wall kernels (d = 2 and 3; d = 1 and 4 take the
 // run-time variant).
 template <int D, class T, bool TAN>
-void launch_xface(unsigned blocks, hipStream_t stream, T* buf, const KParams& p, double t,
-                  int mode) {
-  const dim3 g(blocks), b(256);
+void launch_xface(hipStream_t stream, const XfaceSteps& xs, const KParams& p, int mode) {
+  const dim3 g(static_cast<unsigned>((2 * p.rows + 255) / 256), xs.count), b(256);
   if constexpr (D == 1 || D == 4) {
-    hipLaunchKernelGGL((k_xface<D, T, TAN, -1>), g, b, 0, stream, buf, p, t, mode);
+    hipLaunchKernelGGL((k_xface<D, T, TAN, -1>), g, b, 0, stream, xs, p, mode);
   } else {
     switch (wall_variant(p)) {
-      case 0: hipLaunchKernelGGL((k_xface<D, T, TAN, 0>), g, b, 0, stream, buf, p, t, mode); break;
-      case 1: hipLaunchKernelGGL((k_xface<D, T, TAN, 1>), g, b, 0, stream, buf, p, t, mode); break;
-      case 2: hipLaunchKernelGGL((k_xface<D, T, TAN, 2>), g, b, 0, stream, buf, p, t, mode); break;
-      default: hipLaunchKernelGGL((k_xface<D, T, TAN, 3>), g, b, 0, stream, buf, p, t, mode);
+      case 0: hipLaunchKernelGGL((k_xface<D, T, TAN, 0>), g, b, 0, stream, xs, p, mode); break;
+      case 1: hipLaunchKernelGGL((k_xface<D, T, TAN, 1>), g, b, 0, stream, xs, p, mode); break;
+      case 2: hipLaunchKernelGGL((k_xface<D, T, TAN, 2>), g, b, 0, stream, xs, p, mode); break;
+      default: hipLaunchKernelGGL((k_xface<D, T, TAN, 3>), g, b, 0, stream, xs, p, mode);
     }
   }
 }
@@ -75,10 +74,10 @@ void launch_wall_split(dim3 g, dim3 b, hipStream_t stream, const float* gs, floa
 }
 
 #define LBM_WALL_INST(D, TAN)                                                        \
-  template void launch_xface<D, float, TAN>(unsigned, hipStream_t, float*, const KParams&,  \
-                                            double, int);                              \
-  template void launch_xface<D, double, TAN>(unsigned, hipStream_t, double*,             \
-                                             const KParams&, double, int);             \
+  template void launch_xface<D, float, TAN>(hipStream_t, const XfaceSteps&, const KParams&, \
+                                            int);                                      \
+  template void launch_xface<D, double, TAN>(hipStream_t, const XfaceSteps&,             \
+                                             const KParams&, int);                     \
   template void launch_wall<D, float, TAN>(dim3, dim3, hipStream_t, const float*, float*,  \
                                            const KParams&, double);                    \
   template void launch_wall<D, double, TAN>(dim3, dim3, hipStream_t, const double*,       \
