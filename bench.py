@@ -14,13 +14,14 @@ arithmetic, phi as a float32 pair) are measured on the same workload for the
 precision comparison.
 
 The roofline entry is for the dominant kernel (the bulk stream-collide; it
-advances two time steps per launch, keeping the intermediate state in LDS):
+advances two time steps per launch, three in plain float32 and float64,
+keeping the intermediate states in LDS and registers):
 its algorithmic bytes per launch (per node of the (n-2)^2 rows off the y/z
 walls: 2 q sizeof(float) plus 16 B of phi in the split modes, times the steps
 per launch) divided by its
 average duration from HIP events recorded around every launch on the
-library's stream during the timed region.  Because the two-step kernel moves
-fewer bytes than two single steps, the measured HBM traffic (from the
+library's stream during the timed region.  Because such a kernel moves
+fewer bytes than its single steps, the measured HBM traffic (from the
 committed counter profile) is reported beside it, with the bandwidth of a plain
 device copy measured in the same run.  The CPU baseline is the
 float64 oracle on a bounded sample of the same workload.
@@ -44,10 +45,10 @@ if ROOT not in sys.path:
 
 METRIC = "D3Q19 MLUPS & % HBM peak, FP32 vs FP64 at fixed L2 error; adjoint/fwd ratio"
 HBM_PEAK_GBS = 8000.0
-PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "k_fused2_d3q19_512_{mode}_traffic.md")
+PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "bulk_d3q19_512_{mode}_traffic.md")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2410_13165_amd", "csrc", f)
-                  for f in ("kernels.hip", "kernels.hpp", "fuse.hpp", "engine.hpp",
-                            "lattice.hpp")]
+                  for f in ("kernels.hip", "kernels.hpp", "fuse.hpp", "tri.hip", "tri.hpp",
+                            "engine.hpp", "lattice.hpp")]
 
 
 def kernel_source_hash() -> str:
@@ -691,11 +692,11 @@ def main(argv=None):
                   f"{a['backward_s']:.3f} s, ratio {a['ratio']:.3f}", file=sys.stderr, flush=True)
 
     traffic = head["traffic_bytes_per_launch"]
-    kname = {"fp32": "k_fused2<float, false>", "fp64": "k_fused2<double, false>",
+    kname = {"fp32": "k_tri<float, false>", "fp64": "k_tri<double, false>",
              "fp32_split": "k_fused2_split<false, false>",
              "fp32_hilo": "k_fused2_split<false, true>"}[modes[0]]
-    if head["steps_per_launch"] == 2:
-        kernel = f"{kname} (two stream-collide steps per pass)"
+    if head["steps_per_launch"] > 1:
+        kernel = f"{kname} ({head['steps_per_launch']:.2f} stream-collide steps per pass)"
     else:
         kernel = f"k_step<3,{'float' if modes[0] != 'fp64' else 'double'}> (bulk stream-collide)"
     roofline = {

@@ -150,11 +150,12 @@ typedef struct {
   void* alloc_ctx;
   void* stream;                 /* hipStream_t used for all work, borrowed            */
   int32_t wall_data;            /* lbm_wall_data; default LBM_WALL_JETS               */
-  int32_t steps_per_pass;       /* 2 (default): lattices with d = 3 (every storage
-                                   mode) or d = 2 (LBM_FP32, LBM_FP64) advance two
-                                   time steps per pass of the bulk kernel (bitwise the
-                                   same result, about half the HBM traffic); 1: one
-                                   step per pass.  Other lattices always use 1.        */
+  int32_t steps_per_pass;       /* 2 (default): lattices with d <= 3 (d <= 2: any
+                                   storage mode but LBM_FP32_HILO) advance several time
+                                   steps per pass of the bulk kernel, the intermediate
+                                   states kept on the chip (bitwise the same result):
+                                   up to 1024 (d = 1), 8, 4 or 2 (d = 2), 3 or 2 (d = 3);
+                                   1: one step per pass.  Other lattices always use 1. */
   int32_t check_every;          /* M > 0: every M steps lbm_step counts the non-finite
                                    values of one population plane (split mode: phi),
                                    which any non-finite population of a node reaches
@@ -175,7 +176,7 @@ typedef struct {
   double s, dt;
   double phi_ref;               /* LBM_FP32: phi_mean of the deviation reference      */
   int32_t bytes_per_lu;         /* algorithmic HBM bytes per lattice update of a step */
-  int32_t steps_per_pass;       /* time steps per bulk-kernel pass lbm_step uses      */
+  int32_t steps_per_pass;       /* 2: lbm_step pairs steps (d = 2 and 3), 1: it does not */
   int64_t pstride;              /* elements between population planes in the state
                                    blob of lbm_get_state (nodes first, then padding) */
 } lbm_info_t;
@@ -208,20 +209,22 @@ int lbm_set_initial(lbm_handle* h, const double* phi0_dev, const double* grad_ph
 
 /* Advance n >= 0 time steps of the fused pull-stream + collide kernel with
    the wall schemes applied inline.  With steps_per_pass = 2 (see lbm_params)
-   the steps go in pairs through one bulk pass that keeps the intermediate
-   state in LDS, plus one single step when n is odd; while a tape is recording
-   (lbm_tape_begin) pairs are used only with an even checkpoint interval, never
-   across a checkpoint.  The first paired call allocates, through the
-   allocator, a scratch state (lbm_state_bytes) when the lattice has Dirichlet
-   walls on x_2 or x_3, and in split mode with x_1 walls the x_1-face data of a
-   second step (LBM_ENOMEM if that fails).  Asynchronous on the stream. */
+   the steps go through bulk passes of several steps that keep the intermediate
+   states on the chip, as few passes as n allows, plus a single step where one
+   is left; while a tape is recording (lbm_tape_begin) no pass crosses a
+   checkpoint.  The first such call allocates, through the allocator: for d = 3
+   a scratch state (lbm_state_bytes) when the lattice has Dirichlet walls on x_2
+   or x_3 (LBM_ENOMEM if that fails), and a second one if passes of three steps
+   pay on the lattice (without room for it, two steps go per pass); in split mode
+   with x_1 walls the x_1-face data of a second step; for d = 1 and 2 the wall
+   data of coming steps.  Asynchronous on the stream. */
 int lbm_step(lbm_handle* h, int64_t n);
 
 /* lbm_step for callers that cannot allocate device memory (code under HIP
    graph capture, tight serving loops, hosts that forbid hipMalloc): the same
    kernels and bitwise the same result as lbm_step, but the scratch of the
-   two-step passes (the scratch state of lattices with walls on x_2 or x_3,
-   the second x_1-face array in split mode) lives in a fixed device array of
+   passes (the scratch states of lattices with walls on x_2 or x_3, the second
+   x_1-face array in split mode, wall data) lives in a fixed device array of
    the library, 128 MiB per GPU, held from the first lbm_create on that GPU
    until the process ends.  This call allocates nothing and calls no
    allocator.  Every lbm_step_static on one GPU uses that same array and
@@ -272,7 +275,7 @@ int lbm_set_state(lbm_handle* h, const void* src_dev, int64_t step);
 
 /* Kernel timing with HIP events recorded on the lattice's stream, for
    benchmarks.  After lbm_profile_begin, each of the next max_launches bulk
-   passes (one step, or two with steps_per_pass = 2) records events before the
+   passes (one step, or several with steps_per_pass = 2) records events before the
    bulk kernel, after it, and after the wall kernel of its last step.
    lbm_profile_end synchronises the stream and returns the summed durations in
    milliseconds of the bulk passes (bulk_ms) and of the wall kernels after them

@@ -111,13 +111,17 @@ static hipError_t tri_m(const KParams& p, const TriBufs& tb, long long n, hipStr
 }
 
 // Periodic lattices gain at every size (24^3: 11.7 against 12.7 us per step in
-// float32, 160^3: 72 against 92).  With wall rows the pass has eight launches for
-// three steps against five for two, and small lattices are bound by those: 64^3
-// full-way 32.7 against 30.8 us, 112^3 50.5 against 49.7 (float64 76 against 80),
-// 128^3 61.6 against 65.2 (109 against 126).
+// float32, 160^3: 72 against 92).  With wall rows the pass has six launches for
+// three steps against four for two, and small lattices are bound by those: 64^3
+// full-way 27.9 against 27.4 us, 112^3 45.8 against 45.6 (float64 71.9 against 79.2);
+// with the x_1-face data in a launch per step, 128^3 61.6 against 65.2 (109 against 126).
+//
+// The split mode keeps its two-step pass: in this layout (32 x 14 columns, rings of
+// three planes of t in LDS) three steps of 512^3 took 9.2 ms full-way and 8.4 ms periodic,
+// against 5.95 ms for two.
 bool tri_applies(const KParams& p, int mode) {
   if (p.d != 3 || (mode != kFP64 && mode != kFP32)) return false;
-  if (p.wall_rows > 0 && p.nodes < 1500000) return false;
+  if (p.wall_rows > 0 && p.nodes < 1400000) return false;
   const long long plane = static_cast<long long>(p.n[0]) * p.n[1];
   if (plane * 8 >= (1LL << 32)) return false;
   return p.bc[0] == 0 || p.wall_rows > 0;

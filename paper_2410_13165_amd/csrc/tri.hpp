@@ -1,4 +1,4 @@
-// Three time steps of a d = 3 lattice in one pass (k_tri, k_tri_split).
+// Three time steps of a d = 3 lattice in one pass (k_tri).
 //
 // A block owns an x_1-x_2 tile and marches along x_3.  Each thread owns one
 // column of the tile and its halo of two, for all three steps: per source plane it
@@ -17,8 +17,8 @@
 // next to a wall k_step_near has updated), and k_wall on C2 updates them for step
 // 3 afterwards; for that launch this kernel stores its two-step values of the rows
 // next to those walls in C2.  The x_1-face data of the three steps lie in the row
-// slots of A, C1 and B.  Every node goes through the arithmetic of k_step
-// (k_step_split), so a pass is bitwise three single steps.
+// slots of A, C1 and B.  Every node goes through the arithmetic of k_step,
+// so a pass is bitwise three single steps.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -506,7 +506,7 @@ class Batch:
     """Independent periodic lattices of one d and precision advanced together.
 
     specs: list of dicts with keys dims, tau, dx, u and optional R, m4, g, K and
-    steps_per_pass (2 by default: d = 2 batches advance two steps per pass).
+    steps_per_pass (2 by default: d = 2 batches advance eight, four or two steps per pass).
     """
 
     def __init__(self, d: int, specs, precision: str = "fp32", device=None):
