@@ -1676,8 +1676,14 @@ struct BatchInit {
 
 // Initial state from the analytic field (phi0 == nullptr) or from device arrays;
 // BATCH: of every instance of a batch, one BatchBlock per block.
+//
+// d = 3 asks for two wavefronts per SIMD: left alone it takes 260 registers, most of
+// them products of the parameters kept through the loop, and one.  512^3 with four
+// modes 4.5 -> 3.2 ms in split storage and 4.5 -> 3.3 in float32 (three wavefronts: 3.6
+// and 11, spilled registers), 256^3 in float64 0.92 -> 0.64.  d = 4 would spill 144 for
+// two: 96^4 4.2 against 13.9 ms.
 template <int D, class T, bool BATCH = false>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, D == 3 && !BATCH ? 2 : 1)
     k_init(T* __restrict__ dst, double* __restrict__ phidst, const double* __restrict__ phi0,
            const double* __restrict__ grad0, const std::conditional_t<BATCH, BatchInit, KParams> pb,
            int mode) {
@@ -1841,8 +1847,11 @@ __device__ __forceinline__ void moments_block(const T* __restrict__ f,
   }
 }
 
+// (d = 3 in float32 storage: two wavefronts per SIMD, as for k_init; 512^3 with the
+// entropy 19.0 -> 10.1 ms in split storage, 7.0 -> 6.9 in float32.  Float64 loses: 256^3
+// 0.96 against 1.06.)
 template <int D, class T>
-__global__ void __launch_bounds__(kRedThreads)
+__global__ void __launch_bounds__(kRedThreads, D == 3 && sizeof(T) == 4 ? 2 : 1)
     k_moments(const T* __restrict__ f, const double* __restrict__ phis, const KParams p,
               const int mode, const double t_n, double* __restrict__ phi_out,
               double* __restrict__ partial, const unsigned what) {
