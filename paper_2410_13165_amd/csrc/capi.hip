@@ -41,6 +41,7 @@ struct lbm_handle {
   int64_t step = 0;
   bool initialised = false;
   bool batch_member = false;  // stepped only through its lbm_batch
+  bool set_alone = false;     // a batch member's lbm_set_initial since the batch's last upload
   std::string err;
   // how the current state was initialised (gradients w.r.t. phi0 need it)
   int init_kind = 0;  // 0 unknown, 1 analytic field, 2 device phi0 + FD gradient,
@@ -559,10 +560,12 @@ int lbm_set_initial(lbm_handle* h, const double* phi0_dev, const double* grad_ph
   tape_clear(h);
   int rc = compute_reference(h, phi0_dev);
   if (rc != LBM_OK) return rc;
-  hipError_t e = launch_init(h->kp, h->precision, h->buf[0], h->phib[0], phi0_dev, grad_phi0_dev,
-                             h->stream);
+  // an instance of a batch stays in the buffer that the batch steps from
+  if (h->batch_member) h->set_alone = true;
+  else h->cur = 0;
+  hipError_t e = launch_init(h->kp, h->precision, h->buf[h->cur], h->phib[h->cur], phi0_dev,
+                             grad_phi0_dev, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "initialisation kernel");
-  h->cur = 0;
   h->step = 0;
   h->last_check = 0;
   h->initialised = true;
@@ -1379,6 +1382,7 @@ int batch_upload(lbm_batch* b) {
                        b->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) return bfail(b, LBM_EDEVICE, std::string("table upload: ") + hipGetErrorString(e));
+  for (lbm_handle* h : b->inst) h->set_alone = false;
   return LBM_OK;
 }
 
@@ -1817,11 +1821,26 @@ lbm_handle* lbm_batch_instance(const lbm_batch* b, int i) {
 
 int lbm_batch_moments(lbm_batch* b, double* scalars_host) {
   if (!b || !scalars_host) return bfail(b, LBM_EINVAL, "null argument");
-  for (lbm_handle* h : b->inst)
-    if (!h->initialised) return bfail(b, LBM_EINVAL, "no initial state");
-  int rc = batch_blocks(b);
-  if (rc != LBM_OK) return rc;
   constexpr uint32_t what = LBM_MOM_SUMS | LBM_MOM_RMSE | LBM_MOM_ENTROPY;
+  bool one_step = true, alone = false;
+  for (lbm_handle* h : b->inst) {
+    if (!h->initialised) return bfail(b, LBM_EINVAL, "no initial state");
+    one_step = one_step && h->step == b->step;
+    alone = alone || h->set_alone;
+  }
+  int rc = LBM_OK;
+  if (!one_step) {
+    // instances initialised by themselves since the batch's last step
+    for (size_t i = 0; i < b->inst.size(); ++i) {
+      rc = lbm_moments(b->inst[i], what, nullptr, scalars_host + i * LBM_NSCALARS);
+      if (rc != LBM_OK) return bfail(b, rc, b->inst[i]->err);
+    }
+    return LBM_OK;
+  }
+  // their float32 references
+  if (alone && (rc = batch_upload(b)) != LBM_OK) return rc;
+  rc = batch_blocks(b);
+  if (rc != LBM_OK) return rc;
   hipError_t e = launch_batch_moments(b->d, b->d_kps, b->d_bufs, b->d_blocks, b->nblocks,
                                       b->d_bfirst, static_cast<int>(b->inst.size()), b->precision,
                                       b->cur, b->step, b->d_bpartial, b->d_bresult, what,
