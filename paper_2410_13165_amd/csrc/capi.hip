@@ -62,6 +62,7 @@ struct lbm_handle {
   int wall_ws_steps = 0;
   void* fuse_buf = nullptr;     // state_bytes: populations (+ phi in split mode)
   void* fuse_buf2 = nullptr;    // the same after the second step (three-step passes)
+  bool fuse_buf2_refused = false;  // no room for it: not asked for again
   double* xdata2 = nullptr;     // split mode: x_1-face data of the second step
   int device = 0;               // current device at lbm_create
   // non-finite checks every check_every steps (0: off)
@@ -129,7 +130,11 @@ void* dev_alloc(lbm_handle* h, size_t bytes) {
   if (bytes == 0) bytes = 256;
   if (h->alloc) return h->alloc(bytes, h->alloc_ctx);
   void* p = nullptr;
-  if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+  if (hipMalloc(&p, bytes) != hipSuccess) {
+    // or the next launch check would report it
+    (void)hipGetLastError();
+    return nullptr;
+  }
   return p;
 }
 
@@ -789,8 +794,11 @@ int lbm_step(lbm_handle* h, int64_t n) {
       if (!h->fuse_buf) return fail(h, LBM_ENOMEM, "scratch state for two-step passes");
     }
     // without room for the second scratch state the pairs go on
-    if (use_tri(h) && n >= 3 && pair_state_bytes(h) > 0 && !h->fuse_buf2)
+    if (use_tri(h) && n >= 3 && pair_state_bytes(h) > 0 && !h->fuse_buf2 &&
+        !h->fuse_buf2_refused) {
       h->fuse_buf2 = dev_alloc(h, pair_state_bytes(h));
+      h->fuse_buf2_refused = !h->fuse_buf2;
+    }
     if (xdata_bytes(h) > 0 && !h->xdata2) {
       h->xdata2 = static_cast<double*>(dev_alloc(h, xdata_bytes(h)));
       if (!h->xdata2) return fail(h, LBM_ENOMEM, "x-face data for two-step passes");

@@ -1,0 +1,99 @@
+"""Lattices whose memory runs short: a refused allocation that the library can do
+without changes no result and leaves no error behind for the launches after it."""
+import ctypes as C
+
+import pytest
+
+from paper_2410_13165_amd import inputs
+from paper_2410_13165_amd import lbm as B
+from tests.pairs import gpu_lattice
+from tests.test_zz_no_alloc import _node_state
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _limited_lattice(limit, d, dims, spec, bc, precision):
+    """A lattice whose allocator refuses what would exceed `limit(state_bytes)` bytes
+    in all, and the list of the sizes it refused."""
+    from paper_2410_13165_amd import Lattice
+    kw = dict(dx=1.0 / (dims[0] - 1), u=spec["u"], R=spec["R"], bc=bc, precision=precision,
+              field=spec)
+    lat = Lattice(d, dims, 0.5, **kw)
+    p, lib = lat._params, lat.lib
+    state = lat.state_bytes()
+    lib.lbm_destroy(lat._h)
+    bufs, refused = {}, []
+
+    def alloc(nbytes, ctx):
+        if sum(t.numel() for t in bufs.values()) + nbytes > limit(state):
+            refused.append(nbytes)
+            return None
+        t = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
+        bufs[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def free(ptr, ctx):
+        bufs.pop(ptr, None)
+
+    lat._limited = (B._ALLOC(alloc), B._FREE(free), bufs)
+    p.alloc, p.free_fn = lat._limited[0], lat._limited[1]
+    h = C.c_void_p()
+    dims_arr = (C.c_int64 * B.MAX_DIM)(*(list(dims) + [1] * (B.MAX_DIM - d)))
+    rc = lib.lbm_create(d, dims_arr, 0.5, C.byref(p), C.byref(h))
+    assert rc == B.OK, lib.lbm_last_error(None).decode()
+    lat._h = h
+    return lat, refused
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_second_scratch_state_refused(precision):
+    """Walled d = 3 lattices without room for a fourth state: the states of a lattice
+    with room, and the allocation is asked for once."""
+    dims, bc = (120, 113, 112), ["fullway"] * 3
+    spec = inputs.random_cosines(3, [0.05, -0.1, 0.08], 0.7, seed=81, kmax=1.0)
+    lat, refused = _limited_lattice(lambda s: 3.5 * s, 3, dims, spec, bc, precision)
+    ref = gpu_lattice(3, dims, 1.0 / 119, spec, bc=bc, precision=precision)
+    try:
+        for n in (6, 3, 4):
+            lat.step(n)
+            ref.step(n)
+            assert torch.equal(_node_state(lat), _node_state(ref)), n
+        assert refused == [lat.state_bytes()]
+    finally:
+        lat.close()
+        ref.close()
+
+
+def _default_allocator(p):
+    p.alloc = C.cast(None, B._ALLOC)
+    p.free_fn = C.cast(None, B._FREE)
+
+
+def test_failed_device_allocation_leaves_no_error():
+    """The library's own hipMalloc refuses a lattice larger than the memory of the
+    device (2 states of 300 GB); the next lattice steps all the same."""
+    lib = B.load_library()
+    torch.zeros(1, device="cuda")
+    p = B.LbmParams()
+    lib.lbm_params_default(C.byref(p))
+    _default_allocator(p)
+    p.dx = 0.1
+    h = C.c_void_p()
+    dims = (C.c_int64 * B.MAX_DIM)(1024, 1024, 2000, 1)
+    assert 19 * 8 * 1024 * 1024 * 2000 > torch.cuda.get_device_properties(0).total_memory
+    assert lib.lbm_create(3, dims, 0.5, C.byref(p), C.byref(h)) == B.ENOMEM
+    assert not h.value
+    dims = (C.c_int64 * B.MAX_DIM)(16, 12, 8, 1)
+    phi0 = torch.randn(8, 12, 16, dtype=torch.float64, device="cuda")
+    p.init_order = 1
+    assert lib.lbm_create(3, dims, 0.5, C.byref(p), C.byref(h)) == B.OK
+    try:
+        rc = lib.lbm_set_initial(h, C.c_void_p(phi0.data_ptr()), None)
+        assert rc == B.OK, lib.lbm_last_error(h).decode()
+        rc = lib.lbm_step(h, 6)
+        assert rc == B.OK, lib.lbm_last_error(h).decode()
+        torch.cuda.synchronize()
+    finally:
+        lib.lbm_destroy(h)
