@@ -695,7 +695,7 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2, do
       const int64_t lim = pass_limit(h, n - i);
       todo = tri && lim >= 3 && lim != 4 ? 3 : std::min<int64_t>(lim, 2);
     }
-    MarchPlan plan{1, 0};
+    MarchPlan plan{1, 0, false};
     if (march) {
       const int64_t lim = std::min<int64_t>(pass_limit(h, n - i), wall_cap);
       if (h->d == 2) {

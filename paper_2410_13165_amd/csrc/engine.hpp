@@ -109,9 +109,12 @@ MarchParams march_params(const KParams& p);
 __host__ __device__ constexpr int march_width(int nl) { return (64 - 2 * nl) / 8 * 8; }
 constexpr int kMarchMaxSteps = 8, kMarchMaxWallSteps = 4;
 
-// Steps (nl: 1 for none, 2, 4 or 8) and rows per tile (yc) of a pass.
+// Steps (nl: 1 for none, 2, 4 or 8) and rows per tile (yc) of a pass.  block: two
+// steps with one tile per block and the state between them in LDS (periodic
+// lattices) instead of one per wavefront.
 struct MarchPlan {
   int nl, yc;
+  bool block;
 };
 void march_plans(const KParams& p, int mode, MarchPlan (&plans)[4]);
 // plan.nl steps of a d = 2 lattice (float64, float32 or split mode) in one

@@ -26,6 +26,28 @@ __global__ void __launch_bounds__(64 * kMarchWaves<WALL>)
       reinterpret_cast<double*>(march_mem + (WALL ? wave * march_lds(NL, yc) : 0)));
 }
 
+// Tiles next to each other go to one XCD in turn (as fuse_tile orders them), so that
+// the rows they share are read through one L2.
+template <class T>
+__global__ void __launch_bounds__(kPairWidth)
+    k_pair2(const MarchParams p, const T* __restrict__ src, T* __restrict__ dst, const int yc,
+            const int gx) {
+  __shared__ T lds[kPairSlots * (kPairWidth + 2)];
+  const int nb = static_cast<int>(gridDim.x), per = nb / 8, b = static_cast<int>(blockIdx.x);
+  const int t = b < 8 * per ? (b % 8) * per + b / 8 : b;
+  const int y0 = t / gx * yc;
+  pair2_tile<T>(p, src, dst, lds, t % gx * kPairWidth, y0, min(y0 + yc, p.n1));
+}
+
+template <class T>
+static hipError_t pair2_t(const MarchParams& p, const MarchBufs& b, int yc, hipStream_t stream) {
+  const int gx = (p.n0 + kPairWidth - 1) / kPairWidth;
+  const dim3 grid(static_cast<unsigned>(gx * ((p.n1 + yc - 1) / yc)));
+  hipLaunchKernelGGL((k_pair2<T>), grid, dim3(kPairWidth), 0, stream, p,
+                     static_cast<const T*>(b.src), static_cast<T*>(b.dst), yc, gx);
+  return hipGetLastError();
+}
+
 MarchParams march_params(const KParams& p) {
   MarchParams m{};
   m.n0 = p.n[0];
@@ -83,13 +105,17 @@ static hipError_t march2_w(const MarchParams& p, int scheme, const MarchBufs& b,
 // second (2048^2: 8 steps, 152 us), float64 ones by the third (149 us), small
 // ones by the first and the launch (64^2: 4 steps of one row per tile, 7.5 us).
 // 16 wall rows and columns per wavefront are more registers and instructions:
-// passes over walls stop at 4 steps and 32 rows.
+// passes over walls stop at 4 steps and 32 rows.  Two-step passes stop at 8 rows: the
+// traffic of their halo rows, which the model charges to memory, stays in the caches,
+// and more tiles hide more of the loads (8 rows against the 32 to 128 that the model
+// would take: 4096^2 with full-way walls float32 316 and 428 us, 1024^2 periodic float64
+// 47 and 66).
 void march_plans(const KParams& p, int mode, MarchPlan (&plans)[4]) {
   const bool walls = p.scheme != kNoWall;
   const double c = mode == kFP64 ? 0.115 : mode == kFP32 ? 0.172 : 0.177;
   const double node_bytes = mode == kFP64 ? 72.0 : mode == kFP32 ? 36.0 : 44.0;
   const int simds = 4 * device_cus();
-  MarchPlan best{1, 0};
+  MarchPlan best{1, 0, false};
   double best_t = 0.0;
   plans[0] = best;
   for (int i = 1; i < 4; ++i, plans[i - 1] = best) {
@@ -97,7 +123,8 @@ void march_plans(const KParams& p, int mode, MarchPlan (&plans)[4]) {
     if (nl > (walls ? kMarchMaxWallSteps : kMarchMaxSteps)) continue;
     const int w = march_width(nl);
     const long long gx = (p.n[0] + w - 1) / w;
-    for (int yc = 1; yc <= (walls ? 32 : 128); ++yc) {
+    const int most = nl == 2 ? 8 : (walls ? 32 : 128);
+    for (int yc = 1; yc <= most; ++yc) {
       const long long tiles = gx * ((p.n[1] + yc - 1) / yc);
       if (tiles > (1LL << 28)) continue;
       const double rows = nl * yc + nl * (nl - 1);
@@ -107,10 +134,22 @@ void march_plans(const KParams& p, int mode, MarchPlan (&plans)[4]) {
       const double t = (4.0 + std::max(std::max(alone, issue), bytes / 5.2e6)) / nl;
       if (best.nl == 1 || t < best_t) {
         best_t = t;
-        best = MarchPlan{nl, yc};
+        best = MarchPlan{nl, yc, false};
       }
       if (yc >= p.n[1]) break;
     }
+  }
+  // Two steps of a large periodic lattice whose blocks of columns are at least four
+  // fifths full: us of one call, in blocks and in wavefront tiles, 1000^2 float64 35 and
+  // 41, 700^2 31 and 24; float32 2048^2 67 and 85, 1280^2 36 and 32; 300 x 14000 float64
+  // 161 and 147.  The rows per block: 64, halved (down to 8) while the grid has fewer
+  // than four blocks per CU.
+  const long long gx = (p.n[0] + kPairWidth - 1) / kPairWidth;
+  const long long full = mode == kFP64 ? 900000 : 1900000;
+  if (!walls && mode != kSplit && p.nodes >= full && 5LL * p.n[0] >= 4 * gx * kPairWidth) {
+    int yc = 64;
+    while (yc > 8 && gx * ((p.n[1] + yc - 1) / yc) < 4 * device_cus()) yc /= 2;
+    plans[1] = MarchPlan{2, yc, true};
   }
 }
 
@@ -128,6 +167,12 @@ static hipError_t march2_m(const MarchParams& p, int scheme, int nl, const March
 hipError_t launch_march2(const MarchParams& p, int scheme, int mode, const MarchPlan& plan,
                          const MarchBufs& b, long long n, hipStream_t stream) {
   if (plan.yc < 1) return hipErrorInvalidValue;
+  if (plan.block) {
+    if (scheme != kNoWall || plan.nl != 2) return hipErrorInvalidValue;
+    if (mode == kFP64) return pair2_t<double>(p, b, plan.yc, stream);
+    if (mode == kFP32) return pair2_t<float>(p, b, plan.yc, stream);
+    return hipErrorInvalidValue;
+  }
   switch (mode) {
     case kFP64: return march2_m<kFP64>(p, scheme, plan.nl, b, n, plan.yc, stream);
     case kFP32: return march2_m<kFP32>(p, scheme, plan.nl, b, n, plan.yc, stream);
