@@ -62,6 +62,7 @@ struct lbm_handle {
   int wall_ws_steps = 0;
   void* fuse_buf = nullptr;     // state_bytes: populations (+ phi in split mode)
   void* fuse_buf2 = nullptr;    // the same after the second step (three-step passes)
+  bool tri = false, tri_last = false;  // three-step passes (tri_applies, tri_last)
   bool fuse_buf2_refused = false;  // no room for it: not asked for again
   double* xdata2 = nullptr;     // split mode: x_1-face data of the second step
   int device = 0;               // current device at lbm_create
@@ -494,6 +495,8 @@ int lbm_create(int d, const int64_t* dims, double tau, const lbm_params* p, lbm_
   }
 
   if (use_march(h) && d == 2) march_plans(kp, h->precision, h->plans);
+  h->tri = h->multi && tri_applies(kp, h->precision);
+  h->tri_last = tri_last(kp, h->precision);
 
   // device buffers
   const size_t pb = pop_bytes(h);
@@ -668,16 +671,10 @@ int64_t pass_limit(const lbm_handle* h, int64_t left) {
   return left;
 }
 
-// Three-step passes, where the lattice takes them and (with wall rows) the second
-// scratch state is there.
-bool use_tri(const lbm_handle* h) {
-  return h->multi && h->d == 3 && tri_applies(h->kp, h->precision);
-}
-
 int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2, double* wall_ws,
               int wall_cap) {
   const bool pairs = h->steps_per_pass == 2 && h->d == 3;
-  const bool tri = use_tri(h) && (h->kp.wall_rows == 0 || cbuf2);
+  const bool tri = h->tri && (h->kp.wall_rows == 0 || cbuf2);
   const bool march = use_march(h);
   const int64_t wx_len = wall_x(h), wy_len = wall_y(h);
   int64_t wall0 = 0, wall_n = 0;  // steps whose wall data the workspace holds
@@ -693,7 +690,8 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2, do
     if (pairs) {
       // threes, but four steps as two pairs
       const int64_t lim = pass_limit(h, n - i);
-      todo = tri && lim >= 3 && lim != 4 ? 3 : std::min<int64_t>(lim, 2);
+      const bool three = lim >= 6 || (h->tri_last && (lim == 3 || lim == 5));
+      todo = tri && three ? 3 : std::min<int64_t>(lim, 2);
     }
     MarchPlan plan{1, 0, false};
     if (march) {
@@ -794,7 +792,7 @@ int lbm_step(lbm_handle* h, int64_t n) {
       if (!h->fuse_buf) return fail(h, LBM_ENOMEM, "scratch state for two-step passes");
     }
     // without room for the second scratch state the pairs go on
-    if (use_tri(h) && n >= 3 && pair_state_bytes(h) > 0 && !h->fuse_buf2 &&
+    if (h->tri && n >= 3 && pair_state_bytes(h) > 0 && !h->fuse_buf2 &&
         !h->fuse_buf2_refused) {
       h->fuse_buf2 = dev_alloc(h, pair_state_bytes(h));
       h->fuse_buf2_refused = !h->fuse_buf2;

@@ -216,10 +216,11 @@ struct TriBufs {
   void* C2;
 };
 // Three steps of a d = 3 lattice in one pass (tri.hpp); bitwise three
-// launch_step calls.  tri_applies: whether the pass takes the lattice (a plane of
-// x_3 under 4 GiB; x_1 walls only together with wall rows, whose scratch state
-// holds their data).
+// launch_step calls.  tri_applies: whether the pass takes the lattice and pays on it (a
+// plane of x_3 under 4 GiB; x_1 walls only together with wall rows, whose scratch state
+// holds their data); tri_last: whether also for the last three or five steps of a call.
 bool tri_applies(const KParams& p, int mode);
+bool tri_last(const KParams& p, int mode);
 hipError_t launch_tri(const KParams& p, int mode, const TriBufs& tb, long long n,
                       hipStream_t stream, hipEvent_t* ev = nullptr);
 

@@ -31,20 +31,22 @@ inline int device_cus() {
 // ceil(n2 / zc): the chunk is the zc <= 64 that minimises that (the largest
 // on ties).  Large lattices get 64; small ones trade a little recomputation
 // for a last round of blocks that is not nearly empty.
-inline int fuse_zchunk(int tiles_xy, int n2) {
+// The cost is that many iterations; passes of three steps take zc + 4 and zc <= 128.
+struct ZChunk {
+  int zc;
+  long long cost;
+};
+inline ZChunk pass_zchunk(int tiles_xy, int n2, int most, int halo) {
   const long long cus = device_cus();
-  int best = 64;
-  long long best_cost = -1;
-  for (int zc = 64; zc >= 4; --zc) {
+  ZChunk best{most, -1};
+  for (int zc = most; zc >= 4; --zc) {
     const long long blocks = static_cast<long long>(tiles_xy) * ((n2 + zc - 1) / zc);
-    const long long cost = (blocks + cus - 1) / cus * ((zc < n2 ? zc : n2) + 2);
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
-      best = zc;
-    }
+    const long long cost = (blocks + cus - 1) / cus * ((zc < n2 ? zc : n2) + halo);
+    if (best.cost < 0 || cost < best.cost) best = ZChunk{zc, cost};
   }
   return best;
 }
+inline int fuse_zchunk(int tiles_xy, int n2) { return pass_zchunk(tiles_xy, n2, 64, 2).zc; }
 
 // Tiles fill most of the 160 KB of LDS with one block per CU: SLOTS planes of
 // (TX + 2) (TY + 2) values; a row of a tile is 256 B of one population plane.

@@ -39,21 +39,9 @@ __global__ void __launch_bounds__(256)
   step_row<3, T>(src, dst, p, iz * n1 + iy);
 }
 
-// x_3 planes per block, as fuse_zchunk chooses them: a block of zc planes takes
-// zc + 4 iterations, one block per CU at a time.
-static int tri_zchunk(int tiles_xy, int n2) {
-  const long long cus = device_cus();
-  int best = 64;
-  long long best_cost = -1;
-  for (int zc = 128; zc >= 4; --zc) {
-    const long long blocks = static_cast<long long>(tiles_xy) * ((n2 + zc - 1) / zc);
-    const long long cost = (blocks + cus - 1) / cus * ((zc < n2 ? zc : n2) + 4);
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
-      best = zc;
-    }
-  }
-  return best;
+template <class S>
+static int tiles_of(const KParams& p) {
+  return ((p.n[0] + S::TX - 1) / S::TX) * ((p.n[1] + S::TY - 1) / S::TY);
 }
 
 template <class T, bool TAN, bool HALF>
@@ -88,8 +76,8 @@ static hipError_t tri_t(const KParams& p, const TriBufs& tb, long long n, hipStr
                        p);
     launch_wall<3, T, TAN>(wgrid, block, stream, C1, C2, p, t(1));
   }
-  const int tiles_xy = ((p.n[0] + S::TX - 1) / S::TX) * ((p.n[1] + S::TY - 1) / S::TY);
-  const int zc = tri_zchunk(tiles_xy, p.n[2]);
+  const int tiles_xy = tiles_of<S>(p);
+  const int zc = pass_zchunk(tiles_xy, p.n[2], 128, 4).zc;
   const dim3 grid(static_cast<unsigned>(tiles_xy * ((p.n[2] + zc - 1) / zc)));
   if (ev) (void)hipEventRecord(ev[0], stream);
   hipLaunchKernelGGL((k_tri<T, HALF>), grid, dim3(S::NT), lds, stream, A, B, C1, C2, p, zc);
@@ -110,26 +98,59 @@ static hipError_t tri_m(const KParams& p, const TriBufs& tb, long long n, hipStr
               : tri_t<T, false, false>(p, tb, n, stream, ev);
 }
 
-// Periodic lattices gain at every size (24^3: 11.7 against 12.7 us per step in
-// float32, 160^3: 72 against 92).  With wall rows the pass has six launches for
-// three steps against four for two, and small lattices are bound by those: 64^3
-// full-way 27.9 against 27.4 us, 112^3 45.8 against 45.6 (float64 71.9 against 79.2);
-// with the x_1-face data in a launch per step, 128^3 61.6 against 65.2 (109 against 126).
+// Three steps in one pass or 3/2 passes of two, by the iterations that either takes
+// (pass_zchunk) and what one of three steps takes of one of two (`weight`, hundredths,
+// fitted to the passes of 200 lattices): float64 0.80, float32 0.87, its half-way
+// tiles, which are smaller, 0.65, and 0.84 below 3 million nodes without x_1 walls,
+// where the wall launches weigh more.  So lattices that fill their tiles or the last
+// round of blocks worse go on in pairs: us for two and three steps, 300 x 300 x 8
+// periodic float64 66 and 119, 130 x 120 x 110 with half-way x_2 walls float32 125 and
+// 205; 160^3 full-way 205 and 277.
+//
+// Thin lattices go in pairs too: the pass recomputes four planes, keeps the rows next to
+// walls, and has three wall launches (1000 x 700 x 16 full-way float64 1115 and 1691,
+// x 24 1701 and 2302), as do lattices with wall rows below 1.4 million nodes, which are
+// bound by its launches (64^3 full-way 27.9 us per step in threes, 27.4 in pairs; 112^3
+// 45.8 and 45.6).
 //
 // The split mode keeps its two-step pass: in this layout (32 x 14 columns, rings of
 // three planes of t in LDS) three steps of 512^3 took 9.2 ms full-way and 8.4 ms periodic,
 // against 5.95 ms for two.
+template <class T, bool HALF>
+static bool tri_pays(const KParams& p, int weight) {
+  const long long three = pass_zchunk(tiles_of<TriShape<T, HALF>>(p), p.n[2], 128, 4).cost;
+  const long long two = pass_zchunk(tiles_of<FuseFwdShape<T, HALF>>(p), p.n[2], 64, 2).cost;
+  return 2 * weight * three < 300 * two;
+}
+
 bool tri_applies(const KParams& p, int mode) {
   if (p.d != 3 || (mode != kFP64 && mode != kFP32)) return false;
-  if (p.wall_rows > 0 && p.nodes < 1400000) return false;
   const long long plane = static_cast<long long>(p.n[0]) * p.n[1];
   if (plane * 8 >= (1LL << 32)) return false;
-  return p.bc[0] == 0 || p.wall_rows > 0;
+  if (p.bc[0] != 0 && p.wall_rows == 0) return false;
+  const bool dbl = mode == kFP64, half = p.scheme == kHalfWay;
+  if (p.wall_rows > 0) {
+    if (p.nodes < 1400000 || p.n[2] < 8) return false;
+    if (static_cast<long long>(p.wall_rows) * (dbl ? 8 : 5) > p.rows) return false;
+  } else if (p.n[2] < (dbl ? (p.nodes < 100000 ? 16 : 4) : 3)) {
+    return false;
+  }
+  if (dbl) return half ? tri_pays<double, true>(p, 80) : tri_pays<double, false>(p, 80);
+  if (!half) return tri_pays<float, false>(p, 87);
+  return tri_pays<float, true>(p, p.bc[0] == 0 && p.nodes < 3000000 ? 84 : 65);
+}
+
+// A pass of three steps for the last three or five of a call: on small lattices two steps
+// and one are faster (48^3 float32 32 against 36 us, 64^3 39 and 37; 40^3 float64 32 and
+// 33, 16 x 16 x 300, whose single step takes a wavefront per row, 35 and 30).
+bool tri_last(const KParams& p, int mode) {
+  if (mode != kFP64) return p.nodes >= 200000;
+  return static_cast<long long>(p.rows) * ((p.n[0] + 63) / 64 * 64) >= 120000;
 }
 
 hipError_t launch_tri(const KParams& p, int mode, const TriBufs& tb, long long n,
                       hipStream_t stream, hipEvent_t* ev) {
-  if (!tri_applies(p, mode)) return hipErrorInvalidValue;
+  if (p.d != 3 || (mode != kFP64 && mode != kFP32)) return hipErrorInvalidValue;
   if (p.wall_rows > 0 && (!tb.C1 || !tb.C2)) return hipErrorInvalidValue;
   return mode == kFP64 ? tri_m<double>(p, tb, n, stream, ev) : tri_m<float>(p, tb, n, stream, ev);
 }
