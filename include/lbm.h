@@ -216,18 +216,19 @@ int lbm_set_initial(lbm_handle* h, const double* phi0_dev, const double* grad_ph
    a scratch state (lbm_state_bytes) when the lattice has Dirichlet walls on x_2
    or x_3 (LBM_ENOMEM if that fails), and a second one if passes of three steps
    pay on the lattice (without room for it, two steps go per pass); in split mode
-   with x_1 walls the x_1-face data of a second step; for d = 1 and 2 the wall
-   data of coming steps.  Asynchronous on the stream. */
+   with x_1 walls the x_1-face data of a second step.  For d = 1 and 2 it allocates
+   nothing (the wall data of coming steps have room from lbm_create; where that was
+   refused, one step goes per pass).  Asynchronous on the stream. */
 int lbm_step(lbm_handle* h, int64_t n);
 
 /* lbm_step for callers that cannot allocate device memory (code under HIP
    graph capture, tight serving loops, hosts that forbid hipMalloc): the same
    kernels and bitwise the same result as lbm_step, but the scratch of the
-   passes (the scratch states of lattices with walls on x_2 or x_3, the second
-   x_1-face array in split mode, wall data) lives in a fixed device array of
+   passes of d = 3 (the scratch states of lattices with walls on x_2 or x_3, the
+   second x_1-face array in split mode) lives in a fixed device array of
    the library, 128 MiB per GPU, held from the first lbm_create on that GPU
    until the process ends.  This call allocates nothing and calls no
-   allocator.  Every lbm_step_static on one GPU uses that same array and
+   allocator.  Every lbm_step_static of d = 3 on one GPU uses that same array and
    leaves its contents behind (nothing in it has to start at zero): calls
    whose work overlaps on one GPU (lattices stepped concurrently on
    different streams) race, and must be serialised by the caller.

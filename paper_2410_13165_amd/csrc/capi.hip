@@ -58,7 +58,7 @@ struct lbm_handle {
   int steps_per_pass = 1;
   bool multi = false;           // passes of several steps wanted (lbm_params.steps_per_pass == 2)
   MarchPlan plans[4] = {};      // passes of at most 1, 2, 4, 8 steps (d = 2)
-  double* wall_ws = nullptr;    // wall data of wall_ws_steps steps (marching passes)
+  double* wall_ws = nullptr;    // wall data of wall_ws_steps steps (passes of d <= 2)
   int wall_ws_steps = 0;
   void* fuse_buf = nullptr;     // state_bytes: populations (+ phi in split mode)
   void* fuse_buf2 = nullptr;    // the same after the second step (three-step passes)
@@ -305,6 +305,27 @@ bool use_march(const lbm_handle* h) {
   return h->multi && h->d <= 2 && h->precision != LBM_FP32_HILO;
 }
 
+// Wall data of such passes: doubles per step (x_1 faces, x_2 faces), and the
+// steps the workspace holds: the longest pass (d = 1) or 64 (d = 2, one launch of
+// k_wall_data2 serves several passes), fewer, but at least the two of the shortest pass,
+// where that would exceed 1 MB and half the state.
+int64_t wall_x(const lbm_handle* h) {
+  if (!use_march(h) || h->kp.bc[0] == LBM_BC_PERIODIC) return 0;
+  return h->d == 1 ? 2 : wall_data2_x(h->kp);
+}
+int64_t wall_y(const lbm_handle* h) {
+  return use_march(h) && h->d == 2 ? wall_data2_y(h->kp) : 0;
+}
+int64_t wall_doubles(const lbm_handle* h) { return wall_x(h) + wall_y(h); }
+int wall_steps(const lbm_handle* h) {
+  if (h->d == 1) return line_steps(h->kp.n[0]);
+  const int64_t per = wall_doubles(h) * static_cast<int64_t>(sizeof(double));
+  const int64_t cap = std::max<int64_t>(1 << 20, static_cast<int64_t>(state_bytes(h)) / 2);
+  int s = 64;
+  while (s > 2 && s * per > cap) s /= 2;
+  return s;
+}
+
 int tape_push(lbm_handle* h) {
   void* b = dev_alloc(h, state_bytes(h));
   if (!b) return fail(h, LBM_ENOMEM, "checkpoint allocation failed");
@@ -518,6 +539,12 @@ int lbm_create(int d, const int64_t* dims, double tau, const lbm_params* p, lbm_
     delete h;
     return fail(nullptr, LBM_ENOMEM, "device allocation failed");
   }
+  // here, so that stepping allocates nothing; without it one step goes per pass
+  if (wall_doubles(h) > 0) {
+    h->wall_ws_steps = wall_steps(h);
+    h->wall_ws = static_cast<double*>(
+        dev_alloc(h, sizeof(double) * wall_doubles(h) * h->wall_ws_steps));
+  }
   // Deterministic content for the padding between population planes.
   for (int i = 0; i < 2; ++i) {
     hipError_t e = hipMemsetAsync(h->buf[i], 0, pb, h->stream);
@@ -637,27 +664,6 @@ hipError_t check_nonfinite(lbm_handle* h) {
   return e;
 }
 
-// Wall data of such passes: doubles per step (x_1 faces, x_2 faces), and the
-// steps the workspace holds: the longest pass (d = 1) or 64 (d = 2, one launch of
-// k_wall_data2 serves several passes), fewer where that would exceed 1 MB and half
-// the state.
-int64_t wall_x(const lbm_handle* h) {
-  if (!use_march(h) || h->kp.bc[0] == LBM_BC_PERIODIC) return 0;
-  return h->d == 1 ? 2 : wall_data2_x(h->kp);
-}
-int64_t wall_y(const lbm_handle* h) {
-  return use_march(h) && h->d == 2 ? wall_data2_y(h->kp) : 0;
-}
-int64_t wall_doubles(const lbm_handle* h) { return wall_x(h) + wall_y(h); }
-int wall_steps(const lbm_handle* h) {
-  if (h->d == 1) return line_steps(h->kp.n[0]);
-  const int64_t per = wall_doubles(h) * static_cast<int64_t>(sizeof(double));
-  const int64_t cap = std::max<int64_t>(1 << 20, static_cast<int64_t>(state_bytes(h)) / 2);
-  int s = 64;
-  while (s > 1 && s * per > cap) s /= 2;
-  return s;
-}
-
 // Steps of the next pass when `left` remain: none may pass over the tape's next
 // checkpoint, nor (where a pair of steps did not) the next non-finite check.
 int64_t pass_limit(const lbm_handle* h, int64_t left) {
@@ -671,11 +677,13 @@ int64_t pass_limit(const lbm_handle* h, int64_t left) {
   return left;
 }
 
-int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2, double* wall_ws,
-              int wall_cap) {
+int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2) {
   const bool pairs = h->steps_per_pass == 2 && h->d == 3;
   const bool tri = h->tri && (h->kp.wall_rows == 0 || cbuf2);
-  const bool march = use_march(h);
+  const bool walls = wall_doubles(h) > 0;
+  const bool march = use_march(h) && (!walls || h->wall_ws);
+  double* const wall_ws = h->wall_ws;
+  const int wall_cap = walls ? h->wall_ws_steps : wall_steps(h);
   const int64_t wx_len = wall_x(h), wy_len = wall_y(h);
   int64_t wall0 = 0, wall_n = 0;  // steps whose wall data the workspace holds
   bool checked = false;
@@ -780,12 +788,6 @@ extern "C" {
 
 int lbm_step(lbm_handle* h, int64_t n) {
   if (int rc = step_checks(h, n); rc != LBM_OK) return rc;
-  if (wall_doubles(h) > 0 && n >= 2 && !h->wall_ws) {
-    h->wall_ws_steps = wall_steps(h);
-    h->wall_ws = static_cast<double*>(
-        dev_alloc(h, sizeof(double) * wall_doubles(h) * h->wall_ws_steps));
-    if (!h->wall_ws) return fail(h, LBM_ENOMEM, "wall data of the marching passes");
-  }
   if (h->d == 3 && h->steps_per_pass == 2 && n >= 2) {
     if (pair_state_bytes(h) > 0 && !h->fuse_buf) {
       h->fuse_buf = dev_alloc(h, pair_state_bytes(h));
@@ -802,8 +804,7 @@ int lbm_step(lbm_handle* h, int64_t n) {
       if (!h->xdata2) return fail(h, LBM_ENOMEM, "x-face data for two-step passes");
     }
   }
-  return run_steps(h, n, h->fuse_buf, h->fuse_buf2, h->xdata2, h->wall_ws,
-                   wall_doubles(h) > 0 ? h->wall_ws_steps : wall_steps(h));
+  return run_steps(h, n, h->fuse_buf, h->fuse_buf2, h->xdata2);
 }
 
 int lbm_step_static(lbm_handle* h, int64_t n) {
@@ -831,18 +832,7 @@ int lbm_step_static(lbm_handle* h, int64_t n) {
       if (xdata_bytes(h) > 0) xd2 = reinterpret_cast<double*>(static_cast<char*>(base) + cb);
     }
   }
-  // the wall data of marching passes go to the same scratch
-  double* wall_ws = nullptr;
-  int wall_cap = wall_steps(h);
-  if (wall_doubles(h) > 0) {
-    const int64_t per = wall_doubles(h) * static_cast<int64_t>(sizeof(double));
-    wall_cap = static_cast<int>(
-        std::min<int64_t>(wall_steps(h), static_cast<int64_t>(kStaticScratchBytes) / per));
-    hipError_t err = hipSuccess;
-    wall_ws = static_cast<double*>(static_scratch(h->device, &err));
-    if (!wall_ws) return hip_fail(h, err, "address of the static scratch");
-  }
-  return run_steps(h, n, cbuf, cbuf2, xd2, wall_ws, std::max(wall_cap, 1));
+  return run_steps(h, n, cbuf, cbuf2, xd2);
 }
 
 int lbm_moments(lbm_handle* h, uint32_t what, double* phi_out_dev, double* scalars_host) {

@@ -14,20 +14,25 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-def _limited_lattice(limit, d, dims, spec, bc, precision):
+def _limited_lattice(limit, d, dims, spec, bc, precision, refuse_last=False):
     """A lattice whose allocator refuses what would exceed `limit(state_bytes)` bytes
-    in all, and the list of the sizes it refused."""
+    in all (or, refuse_last, the last allocation of lbm_create), and the list of the
+    sizes it refused."""
     from paper_2410_13165_amd import Lattice
     kw = dict(dx=1.0 / (dims[0] - 1), u=spec["u"], R=spec["R"], bc=bc, precision=precision,
               field=spec)
     lat = Lattice(d, dims, 0.5, **kw)
     p, lib = lat._params, lat.lib
-    state = lat.state_bytes()
+    state, count = lat.state_bytes(), len(lat._bufs)
     lib.lbm_destroy(lat._h)
     bufs, refused = {}, []
 
     def alloc(nbytes, ctx):
-        if sum(t.numel() for t in bufs.values()) + nbytes > limit(state):
+        if refuse_last:
+            no = len(bufs) == count - 1
+        else:
+            no = sum(t.numel() for t in bufs.values()) + nbytes > limit(state)
+        if no:
             refused.append(nbytes)
             return None
         t = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
@@ -97,3 +102,49 @@ def test_failed_device_allocation_leaves_no_error():
         torch.cuda.synchronize()
     finally:
         lib.lbm_destroy(h)
+
+
+WALLED = [(1, (40,), ["fullway"], "fp64"), (1, (3000,), ["halfway"], "fp32"),
+          (2, (41, 33), ["fullway"] * 2, "fp32_split"),
+          (2, (41, 33), ["halfway", "periodic"], "fp64"),
+          (2, (300, 41), ["halfway", "halfway"], "fp32"),
+          (2, (20000, 3), ["periodic", "fullway"], "fp32")]
+
+
+@pytest.mark.parametrize("d,dims,bc,precision", WALLED)
+def test_stepping_walled_d1_and_d2_allocates_nothing(d, dims, bc, precision):
+    """From the first call on, and the steps go several to a pass."""
+    spec = inputs.random_cosines(d, [0.05, -0.1][:d], 0.7, seed=82, kmax=1.0)
+    lat = gpu_lattice(d, dims, 1.0 / (dims[0] - 1), spec, bc=bc, precision=precision)
+    try:
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        lat.profile_begin(64)
+        lat.step(20)
+        lat.step_static(7)
+        torch.cuda.synchronize()
+        assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+        assert lat.profile_end()["launches"] < 27
+    finally:
+        lat.close()
+
+
+@pytest.mark.parametrize("d,dims,bc,precision", WALLED)
+def test_wall_data_workspace_refused(d, dims, bc, precision):
+    """Without room for the wall data of several steps the lattice goes on in single
+    steps: the states of a lattice with room."""
+    spec = inputs.random_cosines(d, [0.05, -0.1][:d], 0.7, seed=82, kmax=1.0)
+    lat, refused = _limited_lattice(None, d, dims, spec, bc, precision, refuse_last=True)
+    ref = gpu_lattice(d, dims, 1.0 / (dims[0] - 1), spec, bc=bc, precision=precision)
+    try:
+        assert len(refused) == 1
+        for n in (6, 3):
+            lat.step(n)
+            ref.step(n)
+            assert torch.equal(_node_state(lat), _node_state(ref)), n
+        lat.step_static(5)
+        ref.step_static(5)
+        assert torch.equal(_node_state(lat), _node_state(ref))
+        assert len(refused) == 1
+    finally:
+        lat.close()
+        ref.close()
