@@ -813,7 +813,7 @@ int lbm_step_static(lbm_handle* h, int64_t n) {
     return fail(h, LBM_EINVAL, "lbm_step_static cannot record a tape (checkpoints are allocated)");
   void *cbuf = nullptr, *cbuf2 = nullptr;
   double* xd2 = nullptr;
-  if (h->steps_per_pass == 2 && n >= 2) {
+  if (h->d == 3 && h->steps_per_pass == 2 && n >= 2) {
     const size_t cb = (pair_state_bytes(h) + 255) / 256 * 256;
     const size_t need = cb + xdata_bytes(h);
     if (need > kStaticScratchBytes)
