@@ -341,21 +341,19 @@ hipError_t launch_wall_data1(const KParams& p, double* wx, long long n, int nste
   return hipGetLastError();
 }
 
-// ---- wall data of several steps of d = 2: one thread per (step, face, face node); the
+// ---- wall data of several steps of d = 2: one thread per face node, blockIdx.y = step; the
 // values k_xface and k_wall compute, before their rounding to the storage type.
 template <bool TAN, int V>
 __global__ void __launch_bounds__(256)
     k_wall_data2(double* __restrict__ wx, double* __restrict__ wy, const KParams p,
-                 const long long n, const int nsteps) {
-  const int fx = p.bc[0] != 0 ? 2 * p.n[1] : 0, fy = p.bc[1] != 0 ? 2 * p.n[0] : 0;
-  const int per = fx + fy;
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= per * nsteps) return;
-  const int l = idx / per;
-  int e = idx - l * per;
+                 const long long n) {
+  const unsigned fx = p.bc[0] != 0 ? 2u * p.n[1] : 0, fy = p.bc[1] != 0 ? 2u * p.n[0] : 0;
+  const unsigned idx = blockIdx.x * 256 + threadIdx.x;
+  if (idx >= fx + fy) return;
+  const int l = blockIdx.y;
   const double t_n = step_time(n + l, p.dt);
-  const bool onx = e < fx;
-  if (!onx) e -= fx;
+  const bool onx = idx < fx;
+  const int e = onx ? idx : idx - fx;
   const int len = onx ? p.n[1] : p.n[0];
   const int side = e / len, pos = e - side * len;
   const int ax = onx ? 0 : 1;
@@ -384,26 +382,24 @@ long long wall_data2_x(const KParams& p) { return p.bc[0] != 0 ? 6LL * p.n[1] : 
 long long wall_data2_y(const KParams& p) { return p.bc[1] != 0 ? 6LL * p.n[0] : 0; }
 
 template <bool TAN>
-static void wall_data2_t(unsigned blocks, const KParams& p, double* wx, double* wy, long long n,
-                         int nsteps, hipStream_t stream) {
-  const dim3 g(blocks), b(256);
+static void wall_data2_t(dim3 g, const KParams& p, double* wx, double* wy, long long n,
+                         hipStream_t stream) {
+  const dim3 b(256);
   switch (wall_variant(p)) {
-    case 0: hipLaunchKernelGGL((k_wall_data2<TAN, 0>), g, b, 0, stream, wx, wy, p, n, nsteps); break;
-    case 1: hipLaunchKernelGGL((k_wall_data2<TAN, 1>), g, b, 0, stream, wx, wy, p, n, nsteps); break;
-    case 2: hipLaunchKernelGGL((k_wall_data2<TAN, 2>), g, b, 0, stream, wx, wy, p, n, nsteps); break;
-    default: hipLaunchKernelGGL((k_wall_data2<TAN, 3>), g, b, 0, stream, wx, wy, p, n, nsteps);
+    case 0: hipLaunchKernelGGL((k_wall_data2<TAN, 0>), g, b, 0, stream, wx, wy, p, n); break;
+    case 1: hipLaunchKernelGGL((k_wall_data2<TAN, 1>), g, b, 0, stream, wx, wy, p, n); break;
+    case 2: hipLaunchKernelGGL((k_wall_data2<TAN, 2>), g, b, 0, stream, wx, wy, p, n); break;
+    default: hipLaunchKernelGGL((k_wall_data2<TAN, 3>), g, b, 0, stream, wx, wy, p, n);
   }
 }
 
 hipError_t launch_wall_data2(const KParams& p, double* wx, double* wy, long long n, int nsteps,
                              hipStream_t stream) {
   const long long per = (wall_data2_x(p) + wall_data2_y(p)) / 3;
-  const long long total = per * nsteps;
-  if (total <= 0) return hipSuccess;
-  if (total > (1LL << 30)) return hipErrorInvalidValue;
-  const unsigned blocks = static_cast<unsigned>((total + 255) / 256);
-  if (p.wall_data) wall_data2_t<true>(blocks, p, wx, wy, n, nsteps, stream);
-  else wall_data2_t<false>(blocks, p, wx, wy, n, nsteps, stream);
+  if (per <= 0 || nsteps <= 0) return hipSuccess;
+  const dim3 grid(static_cast<unsigned>((per + 255) / 256), static_cast<unsigned>(nsteps));
+  if (p.wall_data) wall_data2_t<true>(grid, p, wx, wy, n, stream);
+  else wall_data2_t<false>(grid, p, wx, wy, n, stream);
   return hipGetLastError();
 }
 
