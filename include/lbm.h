@@ -232,6 +232,10 @@ int lbm_step(lbm_handle* h, int64_t n);
    leaves its contents behind (nothing in it has to start at zero): calls
    whose work overlaps on one GPU (lattices stepped concurrently on
    different streams) race, and must be serialised by the caller.
+   Under graph capture the steps are cut into passes such that an even number of
+   pairs of steps, an odd last step counting as one (of steps, where lbm_info's
+   steps_per_pass is 1), leaves the state in the buffer it was in: replays of a graph
+   of such a call go on from one another.
    Errors: as lbm_step, plus LBM_EINVAL when the lattice needs more scratch
    than the array holds (the message gives both sizes) or a tape is
    recording (its checkpoints are allocated), LBM_EDEVICE when the array's

@@ -677,13 +677,70 @@ int64_t pass_limit(const lbm_handle* h, int64_t left) {
   return left;
 }
 
+// How the steps of a call are cut into passes.
+struct PassRules {
+  bool pairs, tri, march;
+  int64_t wall_cap;
+};
+MarchPlan next_pass(const lbm_handle* h, const PassRules& r, int64_t lim) {
+  MarchPlan plan{1, 0, false};
+  if (r.pairs) {
+    // threes, but four steps as two pairs
+    const bool three = lim >= 6 || (h->tri_last && (lim == 3 || lim == 5));
+    plan.nl = r.tri && three ? 3 : static_cast<int>(std::min<int64_t>(lim, 2));
+  } else if (r.march) {
+    lim = std::min(lim, r.wall_cap);
+    if (h->d == 2) return h->plans[lim >= 8 ? 3 : lim >= 4 ? 2 : lim >= 2 ? 1 : 0];
+    plan.nl = static_cast<int>(std::max<int64_t>(lim, 1));
+  }
+  return plan;
+}
+
+// Under graph capture: limits on the first passes of n steps such that the number of
+// passes is even where n pairs of steps (n single ones without pairs) would be an even
+// number.  A graph of such a call ends in the buffer it started from, so its replays
+// go on from one another; any other cut would lose that.  next(left): the steps of the
+// pass that follows when left remain.
+bool stream_captures(hipStream_t stream) {
+  if (!stream) return false;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st == hipStreamCaptureStatusActive;
+}
+template <class Next>
+std::vector<int64_t> capture_limits(int64_t n, bool pairs, const Next& next) {
+  const int64_t want = pairs ? n / 2 + n % 2 : n;
+  std::vector<int64_t> limits;
+  auto parity_ok = [&] {
+    int64_t passes = 0;
+    for (int64_t left = n; left > 0; ++passes) {
+      const size_t i = static_cast<size_t>(passes);
+      left -= next(i < limits.size() ? std::min(left, limits[i]) : left);
+    }
+    return (passes - want) % 2 == 0;
+  };
+  if (parity_ok()) return limits;
+  for (int depth = 1; depth <= 3; ++depth) {
+    limits.assign(depth, 0);
+    for (int c = 0; c < 27; ++c) {
+      for (int d = 0, v = c; d < depth; ++d, v /= 3) limits[d] = int64_t(4) >> v % 3;
+      if (parity_ok()) return limits;
+    }
+  }
+  return {};
+}
+
 int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2) {
-  const bool pairs = h->steps_per_pass == 2 && h->d == 3;
-  const bool tri = h->tri && (h->kp.wall_rows == 0 || cbuf2);
   const bool walls = wall_doubles(h) > 0;
-  const bool march = use_march(h) && (!walls || h->wall_ws);
   double* const wall_ws = h->wall_ws;
   const int wall_cap = walls ? h->wall_ws_steps : wall_steps(h);
+  const PassRules rules{h->steps_per_pass == 2 && h->d == 3,
+                        h->tri && (h->kp.wall_rows == 0 || cbuf2),
+                        use_march(h) && (!walls || wall_ws), wall_cap};
+  const bool march = rules.march;
   const int64_t wx_len = wall_x(h), wy_len = wall_y(h);
   int64_t wall0 = 0, wall_n = 0;  // steps whose wall data the workspace holds
   bool checked = false;
@@ -691,34 +748,25 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2) {
     hipError_t e = launch_zero_count(h->nonfinite, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "non-finite counter");
   }
+  std::vector<int64_t> limits;
+  if (n > 1 && (march || rules.tri) && stream_captures(h->stream))
+    limits = capture_limits(n, h->steps_per_pass == 2,
+                            [&](int64_t left) { return next_pass(h, rules, left).nl; });
   int64_t i = 0;
-  while (i < n) {
+  for (size_t pass = 0; i < n; ++pass) {
     const int src = h->cur, dst = 1 - h->cur;
-    int64_t todo = 1;
-    if (pairs) {
-      // threes, but four steps as two pairs
-      const int64_t lim = pass_limit(h, n - i);
-      const bool three = lim >= 6 || (h->tri_last && (lim == 3 || lim == 5));
-      todo = tri && three ? 3 : std::min<int64_t>(lim, 2);
-    }
-    MarchPlan plan{1, 0, false};
-    if (march) {
-      const int64_t lim = std::min<int64_t>(pass_limit(h, n - i), wall_cap);
-      if (h->d == 2) {
-        plan = h->plans[lim >= 8 ? 3 : lim >= 4 ? 2 : lim >= 2 ? 1 : 0];
-        todo = plan.nl;
-      } else {
-        todo = std::max<int64_t>(lim, 1);
-      }
-      if (todo > 1 && h->kp.scheme != kNoWall && h->step + todo > wall0 + wall_n) {
-        wall0 = h->step;
-        wall_n = std::min<int64_t>(n - i, wall_cap);
-        const int m = static_cast<int>(wall_n);
-        hipError_t e = h->d == 1 ? launch_wall_data1(h->kp, wall_ws, wall0, m, h->stream)
-                                 : launch_wall_data2(h->kp, wall_ws, wall_ws + wx_len * wall_cap,
-                                                     wall0, m, h->stream);
-        if (e != hipSuccess) return hip_fail(h, e, "wall data");
-      }
+    int64_t lim = pass_limit(h, n - i);
+    if (pass < limits.size()) lim = std::min(lim, limits[pass]);
+    const MarchPlan plan = next_pass(h, rules, lim);
+    const int64_t todo = plan.nl;
+    if (march && todo > 1 && h->kp.scheme != kNoWall && h->step + todo > wall0 + wall_n) {
+      wall0 = h->step;
+      wall_n = std::min<int64_t>(n - i, wall_cap);
+      const int m = static_cast<int>(wall_n);
+      hipError_t e = h->d == 1 ? launch_wall_data1(h->kp, wall_ws, wall0, m, h->stream)
+                               : launch_wall_data2(h->kp, wall_ws, wall_ws + wx_len * wall_cap,
+                                                   wall0, m, h->stream);
+      if (e != hipSuccess) return hip_fail(h, e, "wall data");
     }
     hipEvent_t* ev = nullptr;
     if (h->profiling && h->prof_used < h->prof_cap) {
@@ -1538,7 +1586,10 @@ void tune_cache_put(const std::string& key, const TuneEntry& e) {
 int batch_run(lbm_batch* b, int64_t n, bool allow_pairs = true) {
   if (n <= 0) return LBM_OK;
   int64_t done = 0;
-  if (allow_pairs && b->pairs && b->form == LBM_BATCH_RESIDENT) {
+  const auto next = [](int64_t left) -> int64_t { return left >= 8 ? 8 : left >= 4 ? 4 : left >= 2 ? 2 : 1; };
+  std::vector<int64_t> limits;
+  if (allow_pairs && b->pairs && stream_captures(b->stream)) limits = capture_limits(n, true, next);
+  if (allow_pairs && b->pairs && b->form == LBM_BATCH_RESIDENT && limits.empty()) {
     // every pass of the call in one launch, one block per instance
     while (n - done >= 2) {
       const int chunk = static_cast<int>(std::min<int64_t>((n - done) / 2 * 2, 1 << 30));
@@ -1551,15 +1602,19 @@ int batch_run(lbm_batch* b, int64_t n, bool allow_pairs = true) {
       done += chunk;
     }
   } else if (allow_pairs && b->pairs) {
-    for (int nl = kMarchMaxSteps; nl >= 2; nl /= 2) {
-      while (n - done >= nl) {
-        hipError_t e = launch_batch_march(b->d_mps, b->d_bufs, b->d_tiles2, b->ntiles2,
-                                          b->precision, nl, b->cur, b->stream);
-        if (e != hipSuccess)
-          return bfail(b, LBM_EDEVICE, std::string("batch marching pass: ") + hipGetErrorString(e));
-        b->cur ^= 1;
-        done += nl;
-      }
+    // one launch per pass (a captured call of another cut than the resident form's too)
+    for (size_t pass = 0; done < n; ++pass) {
+      const int64_t left = n - done;
+      const int64_t nl = next(pass < limits.size() ? std::min(left, limits[pass]) : left);
+      hipError_t e =
+          nl > 1 ? launch_batch_march(b->d_mps, b->d_bufs, b->d_tiles2, b->ntiles2, b->precision,
+                                      static_cast<int>(nl), b->cur, b->stream)
+                 : launch_batch(b->d, b->d_kps, b->d_bufs, b->d_tiles, b->ntiles, b->tx, b->ty,
+                                b->precision, b->cur, 1, b->stream);
+      if (e != hipSuccess)
+        return bfail(b, LBM_EDEVICE, std::string("batch marching pass: ") + hipGetErrorString(e));
+      b->cur ^= 1;
+      done += nl;
     }
   }
   while (done < n) {
