@@ -215,7 +215,8 @@ int lbm_set_initial(lbm_handle* h, const double* phi0_dev, const double* grad_ph
    checkpoint.  The first such call allocates, through the allocator: for d = 3
    a scratch state (lbm_state_bytes) when the lattice has Dirichlet walls on x_2
    or x_3 (LBM_ENOMEM if that fails), and a second one if passes of three steps
-   pay on the lattice (without room for it, two steps go per pass); in split mode
+   pay on the lattice (without room for it, two steps go per pass; it is given back
+   where a tape's buffers need its room); in split mode
    with x_1 walls the x_1-face data of a second step.  For d = 1 and 2 it allocates
    nothing (the wall data of coming steps have room from lbm_create; where that was
    refused, one step goes per pass).  Asynchronous on the stream. */

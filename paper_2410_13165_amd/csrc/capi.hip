@@ -64,6 +64,7 @@ struct lbm_handle {
   void* fuse_buf2 = nullptr;    // the same after the second step (three-step passes)
   bool tri = false, tri_last = false;  // three-step passes (tri_applies, tri_last)
   bool fuse_buf2_refused = false;  // no room for it: not asked for again
+  bool fuse_buf2_captured = false;  // a captured graph uses it: never given back
   double* xdata2 = nullptr;     // split mode: x_1-face data of the second step
   int device = 0;               // current device at lbm_create
   // non-finite checks every check_every steps (0: off)
@@ -145,6 +146,28 @@ void dev_free(lbm_handle* h, void* p) {
     h->free_fn(p, h->alloc_ctx);
   else
     (void)hipFree(p);
+}
+
+bool stream_captures(hipStream_t stream) {
+  if (!stream) return false;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st == hipStreamCaptureStatusActive;
+}
+
+// An allocation that the second scratch state, which the lattice can do without, makes
+// room for if need be (not where a captured graph may still use it).
+void* alloc_or_give_back(lbm_handle* h, size_t bytes) {
+  void* p = dev_alloc(h, bytes);
+  if (p || !h->fuse_buf2 || h->fuse_buf2_captured || stream_captures(h->stream)) return p;
+  if (hipStreamSynchronize(h->stream) != hipSuccess) return nullptr;
+  dev_free(h, h->fuse_buf2);
+  h->fuse_buf2 = nullptr;
+  h->fuse_buf2_refused = true;
+  return dev_alloc(h, bytes);
 }
 
 size_t elem_size(int precision) { return precision == LBM_FP64 ? 8 : 4; }
@@ -327,7 +350,7 @@ int wall_steps(const lbm_handle* h) {
 }
 
 int tape_push(lbm_handle* h) {
-  void* b = dev_alloc(h, state_bytes(h));
+  void* b = alloc_or_give_back(h, state_bytes(h));
   if (!b) return fail(h, LBM_ENOMEM, "checkpoint allocation failed");
   hipError_t e = copy_state_out(h, b);
   if (e != hipSuccess) {
@@ -701,15 +724,6 @@ MarchPlan next_pass(const lbm_handle* h, const PassRules& r, int64_t lim) {
 // number.  A graph of such a call ends in the buffer it started from, so its replays
 // go on from one another; any other cut would lose that.  next(left): the steps of the
 // pass that follows when left remain.
-bool stream_captures(hipStream_t stream) {
-  if (!stream) return false;
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return st == hipStreamCaptureStatusActive;
-}
 template <class Next>
 std::vector<int64_t> capture_limits(int64_t n, bool pairs, const Next& next) {
   const int64_t want = pairs ? n / 2 + n % 2 : n;
@@ -749,9 +763,11 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2) {
     if (e != hipSuccess) return hip_fail(h, e, "non-finite counter");
   }
   std::vector<int64_t> limits;
-  if (n > 1 && (march || rules.tri) && stream_captures(h->stream))
+  if (n > 1 && (march || rules.tri) && stream_captures(h->stream)) {
+    h->fuse_buf2_captured = h->fuse_buf2_captured || (cbuf2 && cbuf2 == h->fuse_buf2);
     limits = capture_limits(n, h->steps_per_pass == 2,
                             [&](int64_t left) { return next_pass(h, rules, left).nl; });
+  }
   int64_t i = 0;
   for (size_t pass = 0; i < n; ++pass) {
     const int src = h->cur, dst = 1 - h->cur;
@@ -842,7 +858,7 @@ int lbm_step(lbm_handle* h, int64_t n) {
       if (!h->fuse_buf) return fail(h, LBM_ENOMEM, "scratch state for two-step passes");
     }
     // without room for the second scratch state the pairs go on
-    if (h->tri && n >= 3 && pair_state_bytes(h) > 0 && !h->fuse_buf2 &&
+    if (h->tri && pair_state_bytes(h) > 0 && !h->fuse_buf2 &&
         !h->fuse_buf2_refused) {
       h->fuse_buf2 = dev_alloc(h, pair_state_bytes(h));
       h->fuse_buf2_refused = !h->fuse_buf2;
@@ -1083,7 +1099,7 @@ int lbm_tape_gradient(lbm_handle* h, const double* dl_dphi_dev, double* dl_dphi0
 
   std::vector<void*> owned;
   auto alloc = [&](size_t bytes) -> void* {
-    void* b = dev_alloc(h, bytes);
+    void* b = alloc_or_give_back(h, bytes);
     if (b) owned.push_back(b);
     return b;
   };

@@ -148,3 +148,39 @@ def test_wall_data_workspace_refused(d, dims, bc, precision):
     finally:
         lat.close()
         ref.close()
+
+
+def test_second_scratch_state_makes_room_for_a_gradient():
+    """Two states, a scratch state, a checkpoint and the two adjoint buffers fit, a second
+    scratch state besides does not: the gradient of a lattice with room."""
+    dims, bc = (120, 113, 112), ["fullway"] * 3
+    spec = inputs.random_cosines(3, [0.05, -0.1, 0.08], 0.7, seed=81, kmax=1.0)
+    lat, refused = _limited_lattice(lambda s: 6.5 * s, 3, dims, spec, bc, "fp32")
+    ref = gpu_lattice(3, dims, 1.0 / 119, spec, bc=bc, precision="fp32")
+    try:
+        out = []
+        for one in (lat, ref):
+            one.tape_begin(100)
+            one.step(6)
+            out.append(one.tape_gradient(one.phi(), want_tau=False)["phi0"])
+            one.tape_end()
+            one.step(6)
+        assert refused
+        assert torch.equal(out[0], out[1])
+        assert torch.equal(_node_state(lat), _node_state(ref))
+    finally:
+        lat.close()
+        ref.close()
+
+
+def test_calls_of_two_steps_allocate_what_longer_ones_need():
+    dims = (120, 113, 112)
+    spec = inputs.random_cosines(3, [0.05, -0.1, 0.08], 0.7, seed=81, kmax=1.0)
+    lat = gpu_lattice(3, dims, 1.0 / 119, spec, bc=["fullway"] * 3, precision="fp32")
+    try:
+        lat.step(2)
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        lat.step(9)
+        assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+    finally:
+        lat.close()
