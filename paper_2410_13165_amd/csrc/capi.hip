@@ -1312,7 +1312,7 @@ struct lbm_batch {
   int form = LBM_BATCH_PER_PAIR;  // launch form of the marching passes
   int* d_first = nullptr;        // resident form: first tile of each instance (count + 1)
   int* d_order = nullptr;        // resident form: instances, largest first
-  // whole-batch initialisation and moments, allocated at their first use
+  // whole-batch initialisation and moments
   BatchBlock* d_blocks = nullptr;
   int nblocks = 0;
   int* d_bfirst = nullptr;       // first block of each instance (count + 1)
@@ -1449,7 +1449,6 @@ int batch_upload(lbm_batch* b) {
 // Tables of the whole-batch initialisation and moments: each instance is cut into
 // the blocks its own reduction uses (at most kRedBlocks of kRedThreads nodes).
 int batch_blocks(lbm_batch* b) {
-  if (b->d_bresult) return LBM_OK;
   const size_t cnt = b->inst.size();
   std::vector<BatchBlock> blocks;
   std::vector<int> first(cnt + 1, 0);
@@ -1464,16 +1463,14 @@ int batch_blocks(lbm_batch* b) {
     for (int k = 0; k < nb; ++k) blocks.push_back(BatchBlock{static_cast<int>(i), k});
   }
   first[cnt] = static_cast<int>(blocks.size());
-  if (!b->d_blocks) {
-    b->d_blocks = static_cast<BatchBlock*>(dev_alloc(b->owner, sizeof(BatchBlock) * blocks.size()));
-    b->nblocks = static_cast<int>(blocks.size());
-  }
-  if (!b->d_bfirst) b->d_bfirst = static_cast<int*>(dev_alloc(b->owner, sizeof(int) * (cnt + 1)));
-  if (!b->d_offset) b->d_offset = static_cast<long long*>(dev_alloc(b->owner, sizeof(long long) * cnt));
-  if (!b->d_bpartial)
-    b->d_bpartial =
-        static_cast<double*>(dev_alloc(b->owner, sizeof(double) * kNumAcc * blocks.size()));
-  if (!b->d_blocks || !b->d_bfirst || !b->d_offset || !b->d_bpartial)
+  b->nblocks = static_cast<int>(blocks.size());
+  b->d_blocks = static_cast<BatchBlock*>(dev_alloc(b->owner, sizeof(BatchBlock) * blocks.size()));
+  b->d_bfirst = static_cast<int*>(dev_alloc(b->owner, sizeof(int) * (cnt + 1)));
+  b->d_offset = static_cast<long long*>(dev_alloc(b->owner, sizeof(long long) * cnt));
+  b->d_bpartial =
+      static_cast<double*>(dev_alloc(b->owner, sizeof(double) * kNumAcc * blocks.size()));
+  b->d_bresult = static_cast<double*>(dev_alloc(b->owner, sizeof(double) * kNumAcc * cnt));
+  if (!b->d_blocks || !b->d_bfirst || !b->d_offset || !b->d_bpartial || !b->d_bresult)
     return bfail(b, LBM_ENOMEM, "batch reduction tables");
   hipError_t e = hipMemcpyAsync(b->d_blocks, blocks.data(), sizeof(BatchBlock) * blocks.size(),
                                 hipMemcpyHostToDevice, b->stream);
@@ -1486,8 +1483,6 @@ int batch_blocks(lbm_batch* b) {
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess)
     return bfail(b, LBM_EDEVICE, std::string("table upload: ") + hipGetErrorString(e));
-  b->d_bresult = static_cast<double*>(dev_alloc(b->owner, sizeof(double) * kNumAcc * cnt));
-  if (!b->d_bresult) return bfail(b, LBM_ENOMEM, "batch reduction tables");
   return LBM_OK;
 }
 
@@ -1700,6 +1695,7 @@ int lbm_batch_create(int count, int d, const int64_t* dims, const double* tau,
   int rc = batch_upload(b);
   if (rc == LBM_OK) rc = batch_tiles(b, 64, 4);
   if (rc == LBM_OK) rc = batch_pair_tiles(b, 0);
+  if (rc == LBM_OK) rc = batch_blocks(b);
   if (rc != LBM_OK) {
     g_create_error = b->err;
     return abort_create(rc);
@@ -1710,8 +1706,7 @@ int lbm_batch_create(int count, int d, const int64_t* dims, const double* tau,
 
 int lbm_batch_set_initial(lbm_batch* b, const double* phi0_dev, const double* grad_dev) {
   if (!b || !phi0_dev) return bfail(b, LBM_EINVAL, "null argument");
-  int rc = batch_blocks(b);
-  if (rc != LBM_OK) return rc;
+  int rc = LBM_OK;
   const int count = static_cast<int>(b->inst.size());
   hipError_t e = hipSuccess;
   if (b->precision == LBM_FP32) {
@@ -1906,8 +1901,6 @@ int lbm_batch_moments(lbm_batch* b, double* scalars_host) {
   }
   // their float32 references
   if (alone && (rc = batch_upload(b)) != LBM_OK) return rc;
-  rc = batch_blocks(b);
-  if (rc != LBM_OK) return rc;
   hipError_t e = launch_batch_moments(b->d, b->d_kps, b->d_bufs, b->d_blocks, b->nblocks,
                                       b->d_bfirst, static_cast<int>(b->inst.size()), b->precision,
                                       b->cur, b->step, b->d_bpartial, b->d_bresult, what,

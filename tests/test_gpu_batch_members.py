@@ -43,3 +43,18 @@ def test_moments_and_steps_after_instance_initialisation(d, before, precision):
             info = lat.info()
             q, ps, nodes = info["q"], info["pstride"], info["nodes"]
             assert torch.equal(own.reshape(q, ps)[:, :nodes], got.reshape(q, ps)[:, :nodes])
+
+
+@pytest.mark.parametrize("d", [1, 2, 3])
+def test_initialisation_and_moments_allocate_nothing(d):
+    """The first ones of a batch included."""
+    from paper_2410_13165_amd import Batch
+    dims = {1: [(40,), (300,)], 2: [(21, 16), (50, 33)], 3: [(8, 7, 6), (9, 5, 4)]}[d]
+    specs = [{"dims": n, "tau": 0.6, "dx": 1.0 / n[0], "u": [0.05] * d} for n in dims]
+    phi0 = torch.randn(sum(int(np.prod(n)) for n in dims), dtype=torch.float64, device="cuda")
+    with Batch(d, specs, precision="fp32") as b:
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        b.set_initial(phi0)
+        b.step(3)
+        b.moments()
+        assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
