@@ -84,9 +84,9 @@ __global__ void __launch_bounds__(kRedThreads)
   __shared__ double sh[kNumAcc * kRedThreads];
   double acc[kNumAcc] = {0, 0, 0, 0, 0, 0};
   const BatchBlock b = blocks[blockIdx.x];
-  const int nodes = kps[b.inst].nodes;
+  const unsigned nodes = kps[b.inst].nodes;
   const double* arr = phi0 + offset[b.inst];
-  for (int node = b.block * kRedThreads + threadIdx.x; node < nodes;
+  for (unsigned node = b.block * kRedThreads + threadIdx.x; node < nodes;
        node += kRedBlocks * kRedThreads)
     acc[0] += arr[node];
   block_reduce(acc, sh);

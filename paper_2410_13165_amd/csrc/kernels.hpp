@@ -1632,6 +1632,9 @@ __global__ void __launch_bounds__(256)
 }
 
 // ------------------------------------------------------------ node helpers --
+//
+// The loops over the nodes of a lattice (up to 2^31 - 1) count without sign: the last
+// thread's stride past the end does not fit an int.
 
 template <int D>
 __device__ __forceinline__ void node_index(const KParams& p, int node, int (&i)[D]) {
@@ -1691,7 +1694,7 @@ __global__ void __launch_bounds__(256, D == 3 && !BATCH ? 2 : 1)
     if constexpr (BATCH) return pb.kps[pb.blocks[blockIdx.x].inst];
     else return pb;
   }();
-  int first = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+  unsigned first = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
   if constexpr (BATCH) {
     const BatchBlock b = pb.blocks[blockIdx.x];
     dst = static_cast<T*>(pb.bufs[2 * b.inst]);
@@ -1702,8 +1705,8 @@ __global__ void __launch_bounds__(256, D == 3 && !BATCH ? 2 : 1)
   }
   constexpr int Q = q_of(D);
   const long long ps = p.pstride;
-  for (int node = first; node < p.nodes;
-       node += stride) {
+  for (unsigned at = first; at < static_cast<unsigned>(p.nodes); at += stride) {
+    const int node = static_cast<int>(at);
     int i[D];
     node_index<D>(p, node, i);
     double phi, grad[D];
@@ -1788,7 +1791,8 @@ __device__ __forceinline__ void moments_block(const T* __restrict__ f,
                                               const int mode, const double t_n,
                                               double* __restrict__ phi_out,
                                               double* __restrict__ partial, const unsigned what,
-                                              const int block, const int stride, double* sh) {
+                                              const int block, const unsigned stride,
+                                              double* sh) {
 #pragma clang fp contract(off)
   constexpr int Q = q_of(D);
   double acc[kNumAcc] = {0, 0, 0, 0, 0, 0};
@@ -1796,7 +1800,9 @@ __device__ __forceinline__ void moments_block(const T* __restrict__ f,
   const bool want_err = (what & kMomRmse) && p.field.kind != kFieldNone;
   const bool want_ent = (what & kMomEntropy) != 0;
   const double ref = (mode == kFP32) ? p.phi_ref + p.R * (t_n + p.dt) : 0.0;
-  for (int node = block * kRedThreads + threadIdx.x; node < p.nodes; node += stride) {
+  for (unsigned at = block * kRedThreads + threadIdx.x; at < static_cast<unsigned>(p.nodes);
+       at += stride) {
+    const int node = static_cast<int>(at);
     double fk[Q];
     double phi;
     if (split_layout(mode)) {
@@ -1884,7 +1890,8 @@ __global__ void __launch_bounds__(256)
 #pragma clang fp contract(off)
   const long long ps = p.pstride;
   const double ref = (mode == kFP32) ? p.phi_ref + p.R * (t_n + p.dt) : 0.0;
-  for (int node = blockIdx.x * 256 + threadIdx.x; node < p.nodes; node += gridDim.x * 256) {
+  for (unsigned node = blockIdx.x * 256 + threadIdx.x; node < static_cast<unsigned>(p.nodes);
+       node += gridDim.x * 256) {
     double phi;
     if (split_layout(mode)) {
       phi = mode == kHiLo ? phi_get(reinterpret_cast<const float2*>(phis), node) : phis[node];
@@ -1904,8 +1911,9 @@ __global__ void __launch_bounds__(kRedThreads)
     k_sum_phi0(const double* __restrict__ arr, const KParams p, double* __restrict__ partial) {
   __shared__ double sh[kNumAcc * kRedThreads];
   double acc[kNumAcc] = {0, 0, 0, 0, 0, 0};
-  for (int node = blockIdx.x * blockDim.x + threadIdx.x; node < p.nodes;
-       node += gridDim.x * blockDim.x) {
+  for (unsigned at = blockIdx.x * blockDim.x + threadIdx.x; at < static_cast<unsigned>(p.nodes);
+       at += gridDim.x * blockDim.x) {
+    const int node = static_cast<int>(at);
     double v;
     if (arr) {
       v = arr[node];

@@ -34,3 +34,28 @@ def test_wall_data_of_a_long_lattice():
         torch.cuda.empty_cache()
     assert torch.equal(out[0], out[1])
     assert bool(torch.isfinite(out[0]).all())
+
+
+def test_initialisation_and_moments_near_the_node_limit():
+    """65535 x 32768 nodes, 32767 short of 2^31 - 1: initial state from a device field,
+    phi, and the sums.  float32 stores deviations from the mean, nine of them per node,
+    each rounded once and summed in float64."""
+    from paper_2410_13165_amd import Lattice
+    dims = (65535, 32768)
+    nodes = dims[0] * dims[1]
+    phi0 = torch.empty(nodes, dtype=torch.float64, device="cuda")
+    phi0.uniform_(-1.0, 1.0, generator=torch.Generator(device="cuda").manual_seed(5))
+    with Lattice(2, dims, 0.7, dx=1.0, u=[0.1, -0.2], precision="fp32", K=1) as lat:
+        print(f"[large] {dims} initialisation", flush=True)
+        lat.set_initial(phi0)
+        phi = lat.phi().reshape(-1)
+        diag = lat.diagnostics(2)  # the sums
+        # |sum of 9 roundings| <= 9 eps max |f|, |f| <= 2 max |phi0|
+        worst = max(float((phi[i:i + (1 << 28)] - phi0[i:i + (1 << 28)]).abs().max())
+                    for i in range(0, nodes, 1 << 28))
+        assert worst <= 18 * 2.0 ** -24, worst
+        del phi
+        total = sum(float(phi0[i:i + (1 << 28)].sum()) for i in range(0, nodes, 1 << 28))
+        assert abs(diag["sum_phi"] - total) <= 18 * 2.0 ** -24 * nodes
+        assert 0.9 <= diag["max_abs_phi"] <= 1.0 + 18 * 2.0 ** -24
+        assert diag["nonfinite"] == 0
