@@ -282,10 +282,11 @@ int lbm_set_state(lbm_handle* h, const void* src_dev, int64_t step);
 /* Kernel timing with HIP events recorded on the lattice's stream, for
    benchmarks.  After lbm_profile_begin, each of the next max_launches bulk
    passes (one step, or several with steps_per_pass = 2) records events before the
-   bulk kernel, after it, and after the wall kernel of its last step.
+   bulk kernel, after it, and after the wall kernel of its last step (d <= 2 passes of
+   several steps: before and after the launch that forms their wall data, which serves
+   several passes, and after the bulk kernel).
    lbm_profile_end synchronises the stream and returns the summed durations in
-   milliseconds of the bulk passes (bulk_ms) and of the wall kernels after them
-   (wall_ms, 0 without Dirichlet axes >= 2), the number of time steps those
+   milliseconds of the bulk passes (bulk_ms) and of those wall kernels (wall_ms, 0 without Dirichlet axes >= 2), the number of time steps those
    passes covered (steps) and the number of passes (launches), and releases the
    events.  All outputs are nullable.  Errors: LBM_EINVAL (max_launches < 1 or
    > 2^20, profiling already active / not active), LBM_EDEVICE. */

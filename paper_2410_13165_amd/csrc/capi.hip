@@ -50,8 +50,10 @@ struct lbm_handle {
   bool tape_active = false;
   int64_t tape_start = 0, tape_every = 0;
   std::vector<void*> tape_ckpt;
-  // kernel timing (lbm_profile_begin / lbm_profile_end): 3 events per step
+  // kernel timing (lbm_profile_begin / lbm_profile_end): 3 events per pass, around the
+  // bulk kernel and then around the wall kernel, or (prof_wall_first) the other way
   std::vector<hipEvent_t> prof_ev;
+  std::vector<char> prof_wall_first;
   int64_t prof_cap = 0, prof_used = 0, prof_steps = 0;
   bool profiling = false;
   // two steps per bulk pass (float32, d = 3): scratch state for the wall rows
@@ -775,7 +777,19 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2) {
     if (pass < limits.size()) lim = std::min(lim, limits[pass]);
     const MarchPlan plan = next_pass(h, rules, lim);
     const int64_t todo = plan.nl;
-    if (march && todo > 1 && h->kp.scheme != kNoWall && h->step + todo > wall0 + wall_n) {
+    hipEvent_t* ev = nullptr;
+    if (h->profiling && h->prof_used < h->prof_cap) {
+      ev = &h->prof_ev[3 * h->prof_used];
+      ++h->prof_used;
+      h->prof_steps += todo;
+    }
+    const bool data = march && todo > 1 && h->kp.scheme != kNoWall &&
+                      h->step + todo > wall0 + wall_n;
+    if (data) {
+      if (ev) {
+        h->prof_wall_first[h->prof_used - 1] = 1;
+        (void)hipEventRecord(ev[0], h->stream);
+      }
       wall0 = h->step;
       wall_n = std::min<int64_t>(n - i, wall_cap);
       const int m = static_cast<int>(wall_n);
@@ -783,12 +797,6 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2) {
                                : launch_wall_data2(h->kp, wall_ws, wall_ws + wx_len * wall_cap,
                                                    wall0, m, h->stream);
       if (e != hipSuccess) return hip_fail(h, e, "wall data");
-    }
-    hipEvent_t* ev = nullptr;
-    if (h->profiling && h->prof_used < h->prof_cap) {
-      ev = &h->prof_ev[3 * h->prof_used];
-      ++h->prof_used;
-      h->prof_steps += todo;
     }
     hipError_t e;
     if (march && todo > 1) {
@@ -798,14 +806,12 @@ int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2) {
         mp.wy = wall_ws + wx_len * wall_cap + wy_len * (h->step - wall0);
       }
       const MarchBufs mb{h->buf[src], h->buf[dst], h->phib[src], h->phib[dst]};
-      if (ev) (void)hipEventRecord(ev[0], h->stream);
+      if (ev) (void)hipEventRecord(ev[data ? 1 : 0], h->stream);
       e = h->d == 1 ? launch_line(mp, h->kp.scheme, h->precision, static_cast<int>(todo), mb,
                                   h->step, h->stream)
                     : launch_march2(mp, h->kp.scheme, h->precision, plan, mb, h->step, h->stream);
-      if (ev) {
-        (void)hipEventRecord(ev[1], h->stream);
-        (void)hipEventRecord(ev[2], h->stream);
-      }
+      if (ev && !data) (void)hipEventRecord(ev[1], h->stream);
+      if (ev) (void)hipEventRecord(ev[2], h->stream);
     } else if (todo == 3) {
       const TriBufs tb{h->buf[src], h->buf[dst], cbuf, cbuf2};
       e = launch_tri(h->kp, h->precision, tb, h->step, h->stream, ev);
@@ -991,6 +997,7 @@ int set_state_impl(lbm_handle* h, const void* src_dev, int64_t step) {
 void destroy_events(lbm_handle* h) {
   for (hipEvent_t e : h->prof_ev) (void)hipEventDestroy(e);
   h->prof_ev.clear();
+  h->prof_wall_first.clear();
   h->prof_cap = h->prof_used = h->prof_steps = 0;
   h->profiling = false;
 }
@@ -1004,6 +1011,7 @@ int lbm_profile_begin(lbm_handle* h, int64_t max_launches) {
   if (max_launches < 1 || max_launches > (int64_t(1) << 20))
     return fail(h, LBM_EINVAL, "max_launches must be in 1..2^20");
   h->prof_ev.assign(static_cast<size_t>(3 * max_launches), nullptr);
+  h->prof_wall_first.assign(static_cast<size_t>(max_launches), 0);
   for (auto& e : h->prof_ev) {
     hipError_t rc = hipEventCreate(&e);
     if (rc != hipSuccess) {
@@ -1036,8 +1044,8 @@ int lbm_profile_end(lbm_handle* h, double* bulk_ms, double* wall_ms, int64_t* st
       destroy_events(h);
       return hip_fail(h, e, "hipEventElapsedTime");
     }
-    b += t01;
-    w += t12;
+    b += h->prof_wall_first[i] ? t12 : t01;
+    w += h->prof_wall_first[i] ? t01 : t12;
   }
   if (bulk_ms) *bulk_ms = b;
   if (wall_ms) *wall_ms = h->kp.wall_rows > 0 ? w : 0.0;

@@ -25,6 +25,7 @@ def _limited_lattice(limit, d, dims, spec, bc, precision, refuse_last=False):
     p, lib = lat._params, lat.lib
     state, count = lat.state_bytes(), len(lat._bufs)
     lib.lbm_destroy(lat._h)
+    lat._h = None
     bufs, refused = {}, []
 
     def alloc(nbytes, ctx):
