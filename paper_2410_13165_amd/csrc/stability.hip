@@ -40,11 +40,11 @@
 // The kernel is bound by float64 arithmetic: per sweep two complex reciprocals for
 // each pair of groups.  No array that a run-time index walks is private: the roots
 // lie in LDS, and the groups in registers or LDS (kStabListed), where the scratch
-// traffic of private arrays bound the kernel before.  A reciprocal is the hardware's
-// estimate with two Newton steps.  Calls at s = 2, before and after: 61^2 points of
-// D2Q9, m = 16, 6.2 and 1.3 ms; 9^2, m = 8, 400 and 210 us; 13^3 of D3Q19, m = 12,
-// 57 and 20.6 ms; 300000 of D1Q3, m = 16, 10.7 and 0.9 ms; 1 point of D2Q9, m = 256,
-// 120 and 0.24 ms (there for the split over blocks).
+// traffic of private arrays bound the kernel before.  The divisions share a refined
+// reciprocal (cinv).  Calls at s = 2, with private arrays and divisions, and now: 61^2
+// points of D2Q9, m = 16, 5.9 and 1.4 ms; 9^2, m = 8, 366 and 206 us; 13^3 of D3Q19, m =
+// 12, 56 and 22 ms; 300000 of D1Q3, m = 16, 10.3 and 0.67 ms; 1 point of D2Q9, m = 256,
+// 130 and 0.24 ms (there for the split over blocks).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -66,16 +66,20 @@ __device__ __forceinline__ cplx cmul(cplx a, cplx b) {
   return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
 __device__ __forceinline__ cplx cscale(cplx a, double r) { return {a.re * r, a.im * r}; }
-// 1 / x: the estimate refined to rounding (0 gives a non-finite value, which the
-// iteration catches)
-__device__ __forceinline__ double recip(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
-}
+// 1 / a = conj(a) / |a|^2.  The two quotients share the reciprocal of |a|^2, the hardware's
+// estimate after two Newton steps, and each is corrected by its remainder (Markstein, IBM
+// J. Res. Dev. 34 (1990)), which rounds as a division does; div_fixup gives a division's
+// results for zero, infinite and undefined |a|^2.
 __device__ __forceinline__ cplx cinv(cplx a) {
-  const double r = recip(a.re * a.re + a.im * a.im);
-  return {a.re * r, -a.im * r};
+  const double n = a.re * a.re + a.im * a.im;
+  double r = __builtin_amdgcn_rcp(n);
+  r = fma(r, fma(-n, r, 1.0), r);
+  r = fma(r, fma(-n, r, 1.0), r);
+  const auto quotient = [&](double x) {
+    const double q = x * r;
+    return __builtin_amdgcn_div_fixup(fma(fma(-n, q, x), r, q), n, x);
+  };
+  return {quotient(a.re), quotient(-a.im)};
 }
 __device__ __forceinline__ cplx cdiv(cplx a, cplx b) { return cmul(a, cinv(b)); }
 __device__ __forceinline__ double cabs2(cplx a) { return a.re * a.re + a.im * a.im; }
@@ -227,16 +231,16 @@ __device__ double rho_at(const double (&w)[q_of(D)], double s, const int (&j)[kM
       each([&](auto g_) {
       const int g = g_;
         const bool on = is_on(g);
-        cplx inv = cinv(csub(z, pole(g)));
         const bool keep = on && g != h;
+        cplx inv = cinv(csub(z, pole(g)));
         inv.re = keep ? inv.re : 0.0;
         inv.im = keep ? inv.im : 0.0;
         const cplx vi = cmul(v(g), inv);
         f = csub(f, vi);
         fp = cadd(fp, cmul(vi, inv));
         S = cadd(S, inv);
-        const cplx il = cinv(csub(z, roots[64 * g]));
         const bool other = on && g != i;
+        const cplx il = cinv(csub(z, roots[64 * g]));
         ab.re += other ? il.re : 0.0;
         ab.im += other ? il.im : 0.0;
       });
@@ -272,7 +276,7 @@ __device__ double rho_at(const double (&w)[q_of(D)], double s, const int (&j)[kM
 
 // How the wave numbers (nh per point) are dealt to blocks of one wavefront: `points` whole
 // points to a block, or, if the call is too small to fill the chip so, one point to `parts`
-// blocks.  81 points of D2Q9, m = 8, and 300 of D3Q19, m = 8, take 210 and 485 us in parts.
+// blocks.  81 points of D2Q9, m = 8, and 343 of D3Q19, m = 8, take 206 and 521 us in parts.
 struct StabSplit {
   int points, parts;
 };
