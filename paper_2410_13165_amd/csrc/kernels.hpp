@@ -265,20 +265,20 @@ inline int wall_variant(const KParams& p) {
 // wall_mode gives mode j's factor at the wall point (cos and sin of its phase,
 // or its exponential in C), wall_term the mode's contribution to population k,
 // wall_close the terms outside the mode sum.
-// Products that a kernel's loops may leave inside or outside the basic block of
-// the sum they enter are rounded by themselves where several kernels must agree
-// on them (d <= 2, whose wall data of several steps come from a kernel of their
-// own): floating-point contraction works within one block, so left to itself it
-// would make the last bit of a wall value depend on the kernel.
+// Sums of a product that a kernel's loops may leave inside or outside one basic block
+// are fused explicitly where several kernels must agree on them (d <= 2, whose wall data
+// of several steps come from a kernel of their own): floating-point contraction works
+// within one block, so left to itself it would make the last bit of a wall value depend
+// on the kernel.
 template <int D>
-__device__ __forceinline__ double wall_product(double a, double b) {
-  if constexpr (D <= 2) {
-#pragma clang fp contract(off)
-    const double r = a * b;
-    return r;
-  } else {
-    return a * b;
-  }
+__device__ __forceinline__ double wall_fma(double a, double b, double c) {
+  if constexpr (D <= 2) return fma(a, b, c);
+  else return c + a * b;
+}
+template <int D>
+__device__ __forceinline__ double wall_fnma(double a, double b, double c) {
+  if constexpr (D <= 2) return fma(-a, b, c);
+  else return c - a * b;
 }
 
 // t: t_{n+1} full-way, t_n half-way
@@ -288,7 +288,7 @@ __device__ __forceinline__ void wall_mode(const KParams& p, const double (&x)[kM
   const FieldDev& F = p.field;
   double ph = 0.0;
 #pragma unroll
-  for (int a = 0; a < D; ++a) ph += F.kvec[j][a] * (x[a] - wall_product<D>(p.u[a], t));
+  for (int a = 0; a < D; ++a) ph += F.kvec[j][a] * wall_fnma<D>(p.u[a], t, x[a]);
   if (wall_cos<V>(p)) {
     sincos(ph + F.phase[j], &S, &C);
   } else {
@@ -363,11 +363,11 @@ __device__ __forceinline__ double wall_term(const KParams& p, int j, double C, d
 
 template <int D, int V, int k>
 __device__ __forceinline__ double wall_close(const KParams& p, double v, double t_n) {
-  if (wall_full<V>(p)) return p.omega[k] * (v + wall_product<D>(p.R, t_n + p.dt));
+  if (wall_full<V>(p)) return p.omega[k] * wall_fma<D>(p.R, t_n + p.dt, v);
   constexpr int kb = opp_index(D, k);
   const double o2 = p.P >= 2 ? 1.0 : 0.0;
   const double wp = p.omega[k] + p.omega[kb];
-  return v + wall_product<D>(wp * p.R, t_n) + wall_product<D>(o2 * wp * p.R, p.dt);
+  return wall_fma<D>(o2 * wp * p.R, p.dt, wall_fma<D>(wp * p.R, t_n, v));
 }
 
 // Only the populations K0 <= k < K1 are evaluated; each val[k] is the same sum
@@ -402,20 +402,20 @@ __device__ __forceinline__ void wall_analytic(const KParams& p, const double (&x
 // coordinate of axis a at index i
 template <int D>
 __device__ __forceinline__ double wall_coord(const KParams& p, int a, int i) {
-  return p.origin[a] + wall_product<D>(i + p.shift[a], p.dx);
+  return wall_fma<D>(i + p.shift[a], p.dx, p.origin[a]);
 }
 
 // absolute post-collision population of a stored value: the float32 deviations
 // are taken from omega_k ref
 template <int D>
 __device__ __forceinline__ double wall_absolute(double stored, double omega, double ref) {
-  return stored + wall_product<D>(omega, ref);
+  return wall_fma<D>(omega, ref, stored);
 }
 
 // deviation of an absolute value v from weight * ref
 template <int D>
 __device__ __forceinline__ double wall_deviation(double v, double weight, double ref) {
-  return v - wall_product<D>(weight, ref);
+  return wall_fnma<D>(weight, ref, v);
 }
 
 // Modes whose factors the half-way wall path of d = 3 keeps in registers
