@@ -1777,6 +1777,14 @@ __device__ __forceinline__ void block_reduce(double (&v)[kNumAcc], double* sh) {
   for (int m = 0; m < kNumAcc; ++m) v[m] = sh[m * kRedThreads];
 }
 
+// Reference of the float32 deviations at step t_n (phi_mean + R t_{n+1})
+template <int D>
+__device__ __forceinline__ double moments_reference(const KParams& p, double t_n) {
+#pragma clang fp contract(off)
+  if constexpr (D <= 2) return p.phi_ref + p.R * (t_n + p.dt);
+  else return fma(p.R, t_n + p.dt, p.phi_ref);
+}
+
 // accumulators: 0 sum phi, 1 sum phi^2, 2 sum (phi - phi*)^2,
 // 3 sum_k f_k^2 / (2 omega_k), 4 max |phi|, 5 non-finite count
 // `what` selects the work (kMom* bits of engine.hpp): without kMomRmse the
@@ -1784,7 +1792,8 @@ __device__ __forceinline__ void block_reduce(double (&v)[kNumAcc], double* sh) {
 // pre-collision populations are not rebuilt, and without any scalar bit no
 // partial sums are written.
 // One block's share of the reduction: nodes block * kRedThreads + thread, then
-// every `stride`; its sums go to partial[0 .. kNumAcc).
+// every `stride`; its sums go to partial[0 .. kNumAcc).  Nothing is left to the compiler's
+// contraction, so that a batch's moments, a lattice's and k_phi are the same numbers.
 template <int D, class T>
 __device__ __forceinline__ void moments_block(const T* __restrict__ f,
                                               const double* __restrict__ phis, const KParams& p,
@@ -1799,7 +1808,7 @@ __device__ __forceinline__ void moments_block(const T* __restrict__ f,
   const long long ps = p.pstride;
   const bool want_err = (what & kMomRmse) && p.field.kind != kFieldNone;
   const bool want_ent = (what & kMomEntropy) != 0;
-  const double ref = (mode == kFP32) ? p.phi_ref + p.R * (t_n + p.dt) : 0.0;
+  const double ref = (mode == kFP32) ? moments_reference<D>(p, t_n) : 0.0;
   for (unsigned at = block * kRedThreads + threadIdx.x; at < static_cast<unsigned>(p.nodes);
        at += stride) {
     const int node = static_cast<int>(at);
@@ -1809,7 +1818,8 @@ __device__ __forceinline__ void moments_block(const T* __restrict__ f,
       phi = mode == kHiLo ? phi_get(reinterpret_cast<const float2*>(phis), node) : phis[node];
       const float* g = reinterpret_cast<const float*>(f);
 #pragma unroll
-      for (int k = 0; k < Q; ++k) fk[k] = static_cast<double>(g[k * ps + node]) + p.omega[k] * phi;
+      for (int k = 0; k < Q; ++k)
+        fk[k] = fma(p.omega[k], phi, static_cast<double>(g[k * ps + node]));
     } else {
       double sum = 0.0;
 #pragma unroll
@@ -1823,7 +1833,7 @@ __device__ __forceinline__ void moments_block(const T* __restrict__ f,
         const double inv = 1.0 / (1.0 - p.s);
 #pragma unroll
         for (int k = 0; k < Q; ++k)
-          fk[k] = (fk[k] - p.dt * p.omega[k] * p.R - p.s * p.omega[k] * phi) * inv;
+          fk[k] = fma(-(p.s * p.omega[k]), phi, fk[k] - p.dt * p.omega[k] * p.R) * inv;
       }
     }
     if (phi_out) phi_out[node] = phi;
@@ -1834,14 +1844,14 @@ __device__ __forceinline__ void moments_block(const T* __restrict__ f,
       acc[3] += ent;
     }
     acc[0] += phi;
-    acc[1] += phi * phi;
+    acc[1] = fma(phi, phi, acc[1]);
     if (want_err) {
       int i[D];
       double x[D];
       node_index<D>(p, node, i);
       node_coords<D>(p, i, x);
       const double e = phi - field_value<D>(p.field, p, x, t_n);
-      acc[2] += e * e;
+      acc[2] = fma(e, e, acc[2]);
     }
     acc[4] = fmax(acc[4], fabs(phi));
     acc[5] += isfinite(phi) ? 0.0 : 1.0;
@@ -1889,7 +1899,7 @@ __global__ void __launch_bounds__(256)
           const int mode, const double t_n, double* __restrict__ phi_out) {
 #pragma clang fp contract(off)
   const long long ps = p.pstride;
-  const double ref = (mode == kFP32) ? p.phi_ref + p.R * (t_n + p.dt) : 0.0;
+  const double ref = (mode == kFP32) ? moments_reference<D>(p, t_n) : 0.0;
   for (unsigned node = blockIdx.x * 256 + threadIdx.x; node < static_cast<unsigned>(p.nodes);
        node += gridDim.x * 256) {
     double phi;
