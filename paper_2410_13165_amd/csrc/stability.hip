@@ -306,9 +306,9 @@ __global__ void k_stability_clear(long long count, double* __restrict__ rho_out,
 
 template <int D>
 __global__ void __launch_bounds__(64)
-    k_stability(const double* __restrict__ sigma, const double* __restrict__ s_arr, double gm4,
-                int m, long long nh, long long count, StabSplit split, int groups,
-                double* __restrict__ rho_out, double* __restrict__ min_omega_out, int32_t* __restrict__ unconv_out) {
+    k_stability(const double* sigma, const double* s_arr, double gm4, int m, long long nh,
+                long long count, StabSplit split, int groups, double* rho_out,
+                double* min_omega_out, int32_t* unconv_out) {
   constexpr int Q = q_of(D);
   extern __shared__ __align__(16) unsigned char stab_lds[];  // kStabBytes<D> x 64 x groups
   cplx* const roots = reinterpret_cast<cplx*>(stab_lds);
@@ -353,6 +353,18 @@ __global__ void __launch_bounds__(64)
   __syncthreads();
   if (lane < here) {
     const long long pt = p0 + lane;
+    // from the inputs before an output is written: they may share memory
+    double mw = 0.0;
+    if (min_omega_out && part == 0) {
+      double u[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int a = 0; a < D; ++a) u[a] = sigma[pt * D + a];
+      double w[Q];
+      omega_closed_form(D, u, (D >= 2) ? m4_interpolated(D, u, gm4) : 0.0, w);
+      mw = w[0];
+#pragma unroll
+      for (int k = 1; k < Q; ++k) mw = fmin(mw, w[k]);
+    }
     if (split.parts > 1) {
       atomicMax(reinterpret_cast<unsigned long long*>(rho_out) + pt, best[lane]);
       if (unconv_out && bad[lane]) atomicAdd(unconv_out + pt, bad[lane]);
@@ -360,17 +372,7 @@ __global__ void __launch_bounds__(64)
       rho_out[pt] = __longlong_as_double(static_cast<long long>(best[lane]));
       if (unconv_out) unconv_out[pt] = bad[lane];
     }
-    if (min_omega_out && part == 0) {
-      double u[kMaxDim] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int a = 0; a < D; ++a) u[a] = sigma[pt * D + a];
-      double w[Q];
-      omega_closed_form(D, u, (D >= 2) ? m4_interpolated(D, u, gm4) : 0.0, w);
-      double mw = w[0];
-#pragma unroll
-      for (int k = 1; k < Q; ++k) mw = fmin(mw, w[k]);
-      min_omega_out[pt] = mw;
-    }
+    if (min_omega_out && part == 0) min_omega_out[pt] = mw;
   }
 }
 
@@ -379,7 +381,11 @@ hipError_t stability_pass(long long count, const double* sigma, const double* s,
                           long long nxi, double* rho, double* min_omega, int32_t* unconverged,
                           hipStream_t stream) {
   const long long nh = nxi / m * (m / 2 + 1);
-  const StabSplit split = stab_split(nh, count);
+  StabSplit split = stab_split(nh, count);
+  // outputs in the memory of s (or, d = 1, of sigma): one block reads a point's inputs
+  // before it writes them
+  for (const double* out : {rho, min_omega})
+    if (out && (out == s || out == sigma)) split = StabSplit{1, 1};
   // no wave number has more groups than phases or velocities
   const int groups = kStabListed<D> && m < q_of(D) ? m : q_of(D);
   constexpr int most = kStabBytes<D> * 64 * q_of(D);
