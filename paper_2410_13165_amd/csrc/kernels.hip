@@ -372,10 +372,13 @@ static hipError_t moments_d(const KParams& p, int mode, const void* f, const dou
   }
   const dim3 block(kRedThreads), grid(kRedBlocks);
   if (mode == kFP64)
-    hipLaunchKernelGGL((k_moments<D, double>), grid, block, 0, stream,
+    hipLaunchKernelGGL((k_moments<D, double, false>), grid, block, 0, stream,
                        static_cast<const double*>(f), phi, p, mode, t_n, phi_out, partial, what);
+  else if (D == 3 && (split_layout(mode) || !(what & kMomEntropy) || (what & kMomRmse)))
+    hipLaunchKernelGGL((k_moments<D, float, D == 3>), grid, block, 0, stream,
+                       static_cast<const float*>(f), phi, p, mode, t_n, phi_out, partial, what);
   else
-    hipLaunchKernelGGL((k_moments<D, float>), grid, block, 0, stream,
+    hipLaunchKernelGGL((k_moments<D, float, false>), grid, block, 0, stream,
                        static_cast<const float*>(f), phi, p, mode, t_n, phi_out, partial, what);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -1863,11 +1863,12 @@ __device__ __forceinline__ void moments_block(const T* __restrict__ f,
   }
 }
 
-// (d = 3 in float32 storage: two wavefronts per SIMD, as for k_init; 512^3 with the
-// entropy 19.0 -> 10.1 ms in split storage, 7.0 -> 6.9 in float32.  Float64 loses: 256^3
-// 0.96 against 1.06.)
-template <int D, class T>
-__global__ void __launch_bounds__(kRedThreads, D == 3 && sizeof(T) == 4 ? 2 : 1)
+// TWO: two wavefronts per SIMD, for d = 3 in float32 storage (as for k_init), us at 256^3:
+// sums 385 -> 267 in float32 and 405 -> 272 in split storage, with the RMSE 739 -> 433 and
+// 726 -> 428, all 919 -> 755 and 873 -> 543.  The entropy without the RMSE loses in plain
+// float32 (128^3 89 against 100 us), as does float64 (256^3 0.96 against 1.06 ms).
+template <int D, class T, bool TWO>
+__global__ void __launch_bounds__(kRedThreads, TWO ? 2 : 1)
     k_moments(const T* __restrict__ f, const double* __restrict__ phis, const KParams p,
               const int mode, const double t_n, double* __restrict__ phi_out,
               double* __restrict__ partial, const unsigned what) {
