@@ -1733,6 +1733,13 @@ int lbm_batch_set_initial(lbm_batch* b, const double* phi0_dev, const double* gr
   }
   e = launch_batch_init(b->d, b->d_kps, b->d_bufs, b->d_blocks, b->nblocks, b->d_offset,
                         b->precision, phi0_dev, grad_dev, b->stream);
+  int64_t off = 0;
+  for (lbm_handle* h : b->inst) {
+    if (e == hipSuccess && b->precision == LBM_FP64 && h->nodes > kBatchInitNodes)
+      e = launch_init(h->kp, h->precision, h->buf[0], nullptr, phi0_dev + off,
+                      grad_dev ? grad_dev + off * b->d : nullptr, b->stream);
+    off += h->nodes;
+  }
   if (e != hipSuccess)
     return bfail(b, LBM_EDEVICE, std::string("initialisation kernel: ") + hipGetErrorString(e));
   for (lbm_handle* h : b->inst) {

@@ -1697,6 +1697,7 @@ __global__ void __launch_bounds__(256, D == 3 && !BATCH ? 2 : 1)
   unsigned first = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
   if constexpr (BATCH) {
     const BatchBlock b = pb.blocks[blockIdx.x];
+    if (sizeof(T) == 8 && p.nodes > kBatchInitNodes) return;
     dst = static_cast<T*>(pb.bufs[2 * b.inst]);
     phi0 += pb.offset[b.inst];
     if (grad0) grad0 += pb.offset[b.inst] * D;

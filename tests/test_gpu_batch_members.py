@@ -58,3 +58,31 @@ def test_initialisation_and_moments_allocate_nothing(d):
         b.step(3)
         b.moments()
         assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("given", [False, True])
+def test_initial_states_of_large_and_small_instances(given, precision):
+    """A batch that mixes instances at the size (1024 blocks of 256 nodes), above and below
+    it from which they are initialised by a launch of their own, with and without given
+    gradients: phi of lattices of their own.  Bounds as for whole-batch initialisation."""
+    from paper_2410_13165_amd import Batch, Lattice
+    dims = [(20, 30), (512, 512), (513, 512), (700, 900)]
+    u = [0.05, -0.1]
+    specs = [{"dims": n, "tau": 0.6, "dx": 1.0 / n[0], "u": u, "R": 0.3, "K": 3} for n in dims]
+    g = torch.Generator(device="cuda").manual_seed(22)
+    phi0 = [torch.randn(*reversed(n), generator=g, dtype=torch.float64, device="cuda") for n in dims]
+    grad = [torch.randn(2, *reversed(n), generator=g, dtype=torch.float64, device="cuda")
+            for n in dims] if given else None
+    eps = 2.0 ** -53 if precision == "fp64" else 2.0 ** -24
+    with Batch(2, specs, precision=precision) as b:
+        b.set_initial(torch.cat([p.reshape(-1) for p in phi0]),
+                      torch.cat([p.reshape(-1) for p in grad]) if given else None)
+        b.step(3)
+        for i, sp in enumerate(specs):
+            with Lattice(2, sp["dims"], 0.6, dx=sp["dx"], u=u, R=0.3, K=3,
+                         precision=precision) as lat:
+                lat.set_initial(phi0[i], grad[i] if given else None)
+                lat.step(3)
+                bound = 8 * 32 * eps * float(phi0[i].abs().max() + 1.0)
+                assert float((lat.phi() - b.instance(i).phi()).abs().max()) <= bound, i
