@@ -1316,6 +1316,8 @@ struct lbm_batch {
   bool pairs = false;
   BatchTile2* d_tiles2 = nullptr;
   int ntiles2 = 0, tiles2_cap = 0;
+  BatchTile2* d_tilesp = nullptr;  // tiles of two-step passes (per-pair form)
+  int ntilesp = 0;
   int ychunk = 0;                // rows per tile of the marching passes
   int form = LBM_BATCH_PER_PAIR;  // launch form of the marching passes
   int* d_first = nullptr;        // resident form: first tile of each instance (count + 1)
@@ -1336,7 +1338,7 @@ namespace {
 
 void batch_free_tables(lbm_batch* b) {
   if (!b->owner) return;
-  void* tables[] = {b->d_kps,    b->d_mps,    b->d_bufs,     b->d_tiles,   b->d_tiles2, b->d_first,
+  void* tables[] = {b->d_kps,    b->d_mps,    b->d_bufs,     b->d_tiles,   b->d_tiles2, b->d_first, b->d_tilesp,
                     b->d_order,  b->d_blocks, b->d_bfirst,   b->d_offset,  b->d_bpartial,
                     b->d_bresult};
   for (void* t : tables) dev_free(b->owner, t);
@@ -1363,6 +1365,46 @@ int batch_tiles(lbm_batch* b, int tx, int ty) {
   b->tx = tx;
   b->ty = ty;
   return LBM_OK;
+}
+
+// Tiles of the two-step passes of the per-pair form: columns as wide as that pass has them
+// and at most 8 rows, as march_plans gives them to single lattices (twenty of 600 x 500
+// float32 145 -> 112 us against the tiles of longer passes).  Instances of at least two
+// million nodes whose own two-step passes go in blocks launch those instead: two of 2048^2
+// float32 148 -> 134 us, but six of 1000^2 float64 185 in one launch and 211 in six.
+bool batch_blocks_pair(const lbm_handle* h) { return h->plans[1].block && h->nodes >= 2000000; }
+int batch_two_step_tiles(lbm_batch* b) {
+  std::vector<BatchTile2> t;
+  for (size_t i = 0; i < b->inst.size(); ++i) {
+    const lbm_handle* h = b->inst[i];
+    if (batch_blocks_pair(h)) continue;
+    for (int y = 0; y < h->kp.n[1]; y += 8)
+      for (int x = 0; x < h->kp.n[0]; x += march_width(2))
+        t.push_back(BatchTile2{static_cast<int>(i), x, y, std::min(y + 8, h->kp.n[1])});
+  }
+  b->ntilesp = static_cast<int>(t.size());
+  if (t.empty()) return LBM_OK;
+  b->d_tilesp = static_cast<BatchTile2*>(dev_alloc(b->owner, sizeof(BatchTile2) * t.size()));
+  if (!b->d_tilesp) return bfail(b, LBM_ENOMEM, "batch tables");
+  hipError_t e = hipMemcpyAsync(b->d_tilesp, t.data(), sizeof(BatchTile2) * t.size(),
+                                hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+  if (e != hipSuccess) return bfail(b, LBM_EDEVICE, std::string("tile upload: ") + hipGetErrorString(e));
+  return LBM_OK;
+}
+
+// Two steps of every instance
+hipError_t batch_two_steps(lbm_batch* b) {
+  hipError_t e = hipSuccess;
+  if (b->ntilesp > 0)
+    e = launch_batch_march(b->d_mps, b->d_bufs, b->d_tilesp, b->ntilesp, b->precision, 2, b->cur,
+                           b->stream);
+  for (lbm_handle* h : b->inst) {
+    if (e != hipSuccess || !batch_blocks_pair(h)) continue;
+    const MarchBufs mb{h->buf[b->cur], h->buf[1 - b->cur], nullptr, nullptr};
+    e = launch_march2(march_params(h->kp), kNoWall, b->precision, h->plans[1], mb, 0, b->stream);
+  }
+  return e;
 }
 
 // Tile table of the marching passes (d = 2): every instance cut into x_1
@@ -1398,6 +1440,7 @@ int batch_pair_tiles(lbm_batch* b, int yc) {
     b->d_order = static_cast<int*>(dev_alloc(b->owner, sizeof(int) * cnt));
     if (!b->d_tiles2 || !b->d_first || !b->d_order) return bfail(b, LBM_ENOMEM, "batch tables");
     b->tiles2_cap = static_cast<int>(cap);
+    if (int rc = batch_two_step_tiles(b); rc != LBM_OK) return rc;
   }
   std::vector<BatchTile2> t;
   std::vector<int> first(b->inst.size() + 1, 0), order(b->inst.size());
@@ -1626,7 +1669,8 @@ int batch_run(lbm_batch* b, int64_t n, bool allow_pairs = true) {
       const int64_t left = n - done;
       const int64_t nl = next(pass < limits.size() ? std::min(left, limits[pass]) : left);
       hipError_t e =
-          nl > 1 ? launch_batch_march(b->d_mps, b->d_bufs, b->d_tiles2, b->ntiles2, b->precision,
+          nl == 2 ? batch_two_steps(b)
+          : nl > 1 ? launch_batch_march(b->d_mps, b->d_bufs, b->d_tiles2, b->ntiles2, b->precision,
                                       static_cast<int>(nl), b->cur, b->stream)
                  : launch_batch(b->d, b->d_kps, b->d_bufs, b->d_tiles, b->ntiles, b->tx, b->ty,
                                 b->precision, b->cur, 1, b->stream);

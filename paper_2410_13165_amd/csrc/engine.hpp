@@ -276,7 +276,7 @@ hipError_t launch_batch(int d, const KParams* kps, void* const* bufs, const Batc
 
 // One marching pass of nl (2, 4 or 8) steps of every instance of a d = 2 batch
 // (float32 or float64) over the BatchTile2 table, whose tiles are kBatchTileWidth
-// wide.
+// wide (march_width(2) for two steps).
 constexpr int kBatchTileWidth = march_width(kMarchMaxSteps);
 hipError_t launch_batch_march(const MarchParams* mps, void* const* bufs, const BatchTile2* tiles,
                               int ntiles, int mode, int nl, int cur, hipStream_t stream);

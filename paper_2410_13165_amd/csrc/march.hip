@@ -190,7 +190,8 @@ __global__ void __launch_bounds__(256)
   if (w >= ntiles) return;
   const BatchTile2 t = tiles[__builtin_amdgcn_readfirstlane(w)];
   const MarchBufs b{bufs[2 * t.inst + cur], bufs[2 * t.inst + 1 - cur], nullptr, nullptr};
-  march2_tile<MODE, NL, 0, 2>(mps[t.inst], b, t.x0, kBatchTileWidth, t.y0, t.y1, 0, nullptr);
+  constexpr int W = NL == 2 ? march_width(2) : kBatchTileWidth;
+  march2_tile<MODE, NL, 0, 2>(mps[t.inst], b, t.x0, W, t.y0, t.y1, 0, nullptr);
 }
 
 template <int MODE>

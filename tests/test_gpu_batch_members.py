@@ -86,3 +86,28 @@ def test_initial_states_of_large_and_small_instances(given, precision):
                 lat.step(3)
                 bound = 8 * 32 * eps * float(phi0[i].abs().max() + 1.0)
                 assert float((lat.phi() - b.instance(i).phi()).abs().max()) <= bound, i
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_two_step_passes_of_large_and_small_instances(precision):
+    """Two-step passes in blocks (large instances) and in wavefront tiles, alone and mixed in
+    one batch: bitwise the states of single lattices in single steps."""
+    from paper_2410_13165_amd import Batch, Lattice
+    from tests.test_zz_no_alloc import _node_state
+    for dims in ([(1500, 1401)], [(57, 9), (1500, 1401), (1, 1), (112, 300)], [(113, 17), (20, 300)]):
+        specs = [{"dims": n, "tau": 0.6, "dx": 0.01, "u": [0.05, -0.1], "R": 0.3} for n in dims]
+        g = torch.Generator(device="cuda").manual_seed(23)
+        phi0 = [torch.randn(*reversed(n), generator=g, dtype=torch.float64, device="cuda")
+                for n in dims]
+        print(f"[two steps] {dims} {precision}", flush=True)
+        with Batch(2, specs, precision=precision) as b:
+            for i in range(len(dims)):
+                b.instance(i).set_initial(phi0[i])
+            for n in (2, 3, 6):
+                b.step(n)
+            for i, sp in enumerate(specs):
+                with Lattice(2, sp["dims"], 0.6, dx=0.01, u=sp["u"], R=0.3, K=1,
+                             precision=precision, steps_per_pass=1) as lat:
+                    lat.set_initial(phi0[i])
+                    lat.step(11)
+                    assert torch.equal(_node_state(lat), _node_state(b.instance(i))), (dims, i)
