@@ -46,3 +46,24 @@ def test_steps_per_pass_and_states(dims, bc, precision, launches):
     finally:
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("dims,precision,every,launches", [
+    ((20, 20, 20), "fp32_split", 5, 12), ((20, 20, 20), "fp64", 5, 12),
+    ((20, 20, 20), "fp32_split", 4, 6), ((90, 90, 90), "fp32_split", 5, 7),
+    ((90, 90, 90), "fp64", 5, 5), ((90, 90, 90), "fp32", 5, 5),
+])
+def test_passes_between_odd_checkpoints(dims, precision, every, launches):
+    """Twelve steps of a tape: small lattices go in single steps between odd checkpoints."""
+    from paper_2410_13165_amd import Lattice
+    lat = Lattice(3, dims, 0.7, dx=1.0 / dims[0], u=[0.05, -0.1, 0.08], precision=precision, K=1)
+    try:
+        lat.set_initial(torch.randn(*reversed(dims), dtype=torch.float64, device="cuda"))
+        lat.tape_begin(every)
+        lat.profile_begin(16)
+        lat.step(12)
+        prof = lat.profile_end()
+        assert prof["steps"] == 12 and prof["launches"] == launches, prof
+        lat.tape_end()
+    finally:
+        lat.close()
