@@ -105,11 +105,11 @@ static hipError_t march2_w(const MarchParams& p, int scheme, const MarchBufs& b,
 // second (2048^2: 8 steps, 152 us), float64 ones by the third (149 us), small
 // ones by the first and the launch (64^2: 4 steps of one row per tile, 7.5 us).
 // 16 wall rows and columns per wavefront are more registers and instructions:
-// passes over walls stop at 4 steps and 32 rows.  Two-step passes stop at 8 rows: the
-// traffic of their halo rows, which the model charges to memory, stays in the caches,
-// and more tiles hide more of the loads (8 rows against the 32 to 128 that the model
-// would take: 4096^2 with full-way walls float32 316 and 428 us, 1024^2 periodic float64
-// 47 and 66).
+// passes over walls stop at 4 steps and 32 rows.  Two-step passes that the third binds
+// stop at 8 rows: the traffic of their halo rows, which the model charges to memory,
+// stays in the caches, and more tiles hide more of the loads (8 rows against the 32 to
+// 128 that the model would take: 4096^2 with full-way walls float32 316 and 428 us, 1024^2
+// periodic float64 47 and 66; 3 x 100000, bound by the second, 48 and 44).
 void march_plans(const KParams& p, int mode, MarchPlan (&plans)[4]) {
   const bool walls = p.scheme != kNoWall;
   const double c = mode == kFP64 ? 0.115 : mode == kFP32 ? 0.172 : 0.177;
@@ -123,18 +123,19 @@ void march_plans(const KParams& p, int mode, MarchPlan (&plans)[4]) {
     if (nl > (walls ? kMarchMaxWallSteps : kMarchMaxSteps)) continue;
     const int w = march_width(nl);
     const long long gx = (p.n[0] + w - 1) / w;
-    const int most = nl == 2 ? 8 : (walls ? 32 : 128);
-    for (int yc = 1; yc <= most; ++yc) {
+    for (int yc = 1; yc <= (walls ? 32 : 128); ++yc) {
       const long long tiles = gx * ((p.n[1] + yc - 1) / yc);
       if (tiles > (1LL << 28)) continue;
       const double rows = nl * yc + nl * (nl - 1);
       const double alone = rows * c + (yc + 2 * nl) * 0.35;
       const double issue = static_cast<double>((tiles + simds - 1) / simds) * rows * c;
       const double bytes = p.nodes * node_bytes * ((1.0 + 2.0 * nl / yc) * 64.0 / w + 1.0);
-      const double t = (4.0 + std::max(std::max(alone, issue), bytes / 5.2e6)) / nl;
+      const double work = std::max(alone, issue), traffic = bytes / 5.2e6;
+      const double t = (4.0 + std::max(work, traffic)) / nl;
       if (best.nl == 1 || t < best_t) {
         best_t = t;
         best = MarchPlan{nl, yc, false};
+        if (nl == 2 && traffic > work) best.yc = std::min(yc, 8);
       }
       if (yc >= p.n[1]) break;
     }
