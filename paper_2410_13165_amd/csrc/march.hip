@@ -343,16 +343,21 @@ hipError_t launch_wall_data1(const KParams& p, double* wx, long long n, int nste
   return hipGetLastError();
 }
 
-// ---- wall data of several steps of d = 2: one thread per face node, blockIdx.y = step; the
+// ---- wall data of several steps of d = 2: one thread per step and face node (of the step
+// blockIdx.y where all of them are too many for one index); the
 // values k_xface and k_wall compute, before their rounding to the storage type.
 template <bool TAN, int V>
 __global__ void __launch_bounds__(256)
     k_wall_data2(double* __restrict__ wx, double* __restrict__ wy, const KParams p,
-                 const long long n) {
+                 const long long n, const int nsteps) {
   const unsigned fx = p.bc[0] != 0 ? 2u * p.n[1] : 0, fy = p.bc[1] != 0 ? 2u * p.n[0] : 0;
-  const unsigned idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= fx + fy) return;
-  const int l = blockIdx.y;
+  unsigned idx = blockIdx.x * 256 + threadIdx.x;
+  int l = blockIdx.y;
+  if (gridDim.y == 1) {
+    l = static_cast<int>(idx / (fx + fy));
+    idx -= l * (fx + fy);
+  }
+  if (l >= nsteps || idx >= fx + fy) return;
   const double t_n = step_time(n + l, p.dt);
   const bool onx = idx < fx;
   const int e = onx ? idx : idx - fx;
@@ -385,13 +390,13 @@ long long wall_data2_y(const KParams& p) { return p.bc[1] != 0 ? 6LL * p.n[0] : 
 
 template <bool TAN>
 static void wall_data2_t(dim3 g, const KParams& p, double* wx, double* wy, long long n,
-                         hipStream_t stream) {
+                         int nsteps, hipStream_t stream) {
   const dim3 b(256);
   switch (wall_variant(p)) {
-    case 0: hipLaunchKernelGGL((k_wall_data2<TAN, 0>), g, b, 0, stream, wx, wy, p, n); break;
-    case 1: hipLaunchKernelGGL((k_wall_data2<TAN, 1>), g, b, 0, stream, wx, wy, p, n); break;
-    case 2: hipLaunchKernelGGL((k_wall_data2<TAN, 2>), g, b, 0, stream, wx, wy, p, n); break;
-    default: hipLaunchKernelGGL((k_wall_data2<TAN, 3>), g, b, 0, stream, wx, wy, p, n);
+    case 0: hipLaunchKernelGGL((k_wall_data2<TAN, 0>), g, b, 0, stream, wx, wy, p, n, nsteps); break;
+    case 1: hipLaunchKernelGGL((k_wall_data2<TAN, 1>), g, b, 0, stream, wx, wy, p, n, nsteps); break;
+    case 2: hipLaunchKernelGGL((k_wall_data2<TAN, 2>), g, b, 0, stream, wx, wy, p, n, nsteps); break;
+    default: hipLaunchKernelGGL((k_wall_data2<TAN, 3>), g, b, 0, stream, wx, wy, p, n, nsteps);
   }
 }
 
@@ -399,9 +404,11 @@ hipError_t launch_wall_data2(const KParams& p, double* wx, double* wy, long long
                              hipStream_t stream) {
   const long long per = (wall_data2_x(p) + wall_data2_y(p)) / 3;
   if (per <= 0 || nsteps <= 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>((per + 255) / 256), static_cast<unsigned>(nsteps));
-  if (p.wall_data) wall_data2_t<true>(grid, p, wx, wy, n, stream);
-  else wall_data2_t<false>(grid, p, wx, wy, n, stream);
+  const bool flat = per * nsteps <= 1LL << 30;
+  const dim3 grid(static_cast<unsigned>(((flat ? per * nsteps : per) + 255) / 256),
+                  static_cast<unsigned>(flat ? 1 : nsteps));
+  if (p.wall_data) wall_data2_t<true>(grid, p, wx, wy, n, nsteps, stream);
+  else wall_data2_t<false>(grid, p, wx, wy, n, nsteps, stream);
   return hipGetLastError();
 }
 
