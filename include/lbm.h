@@ -176,7 +176,10 @@ typedef struct {
   double s, dt;
   double phi_ref;               /* LBM_FP32: phi_mean of the deviation reference      */
   int32_t bytes_per_lu;         /* algorithmic HBM bytes per lattice update of a step */
-  int32_t steps_per_pass;       /* 2: lbm_step pairs steps (d = 2 and 3), 1: it does not */
+  int32_t steps_per_pass;       /* with params.steps_per_pass = 2: 2 for d = 3 and for
+                                   LBM_FP64 and LBM_FP32 of d = 2, 1 otherwise (d = 1
+                                   and the split mode of d = 2 take several steps per
+                                   pass as well); with 1: 1 */
   int64_t pstride;              /* elements between population planes in the state
                                    blob of lbm_get_state (nodes first, then padding) */
 } lbm_info_t;
@@ -391,7 +394,8 @@ int lbm_stability_map(int d, int64_t count, const double* sigma_dev, const doubl
    table of (instance, row) tiles.  Both forms give bitwise the same states.
    lbm_batch_set_launch(b, form, ychunk) selects the form and the rows per tile
    (8..64, 0 = 64 halved down to 8 while there are fewer than eight tiles per
-   CU); LBM_EUNSUPPORTED for batches without pairs.
+   CU; two-step passes of the per-pair form have tiles of their own, 8 rows, and
+   large instances launches of their own); LBM_EUNSUPPORTED for batches without pairs.
    lbm_batch_tune times every launch the batch can use over trial_steps steps
    (the single-step block shapes 64x4, 128x2, 256x1; with pairs both forms at
    8, 16, 32 and 64 rows per tile), restores the states, keeps the fastest and

@@ -56,8 +56,8 @@ struct lbm_handle {
   std::vector<char> prof_wall_first;
   int64_t prof_cap = 0, prof_used = 0, prof_steps = 0;
   bool profiling = false;
-  // two steps per bulk pass (float32, d = 3): scratch state for the wall rows
-  int steps_per_pass = 1;
+  // passes of several steps; d = 3: scratch states for the wall rows
+  int steps_per_pass = 1;       // 2: d = 3, and float32 and float64 of d = 2 (lbm_info)
   bool multi = false;           // passes of several steps wanted (lbm_params.steps_per_pass == 2)
   MarchPlan plans[4] = {};      // passes of at most 1, 2, 4, 8 steps (d = 2)
   double* wall_ws = nullptr;    // wall data of wall_ws_steps steps (passes of d <= 2)
@@ -668,8 +668,6 @@ size_t pair_state_bytes(const lbm_handle* h) {
   return h->kp.wall_rows > 0 ? state_bytes(h) : 0;
 }
 
-// n steps with the two-step scratch at cbuf (pair_state_bytes) and the split
-// mode's second x_1-face array at xd2 (xdata_bytes).
 // Count the non-finite values of population plane 0 of the stored state
 // (split mode: phi).  Post-collision, f*_0 = (1 - s) f_0 + omega_0 (s phi + dt R)
 // carries every population of its node through phi; with omega_0 = 0 plane 1
@@ -749,6 +747,8 @@ std::vector<int64_t> capture_limits(int64_t n, bool pairs, const Next& next) {
   return {};
 }
 
+// n steps with the scratch states of d = 3 at cbuf and cbuf2 (pair_state_bytes each, or
+// null) and the split mode's second x_1-face array at xd2 (xdata_bytes).
 int run_steps(lbm_handle* h, int64_t n, void* cbuf, void* cbuf2, double* xd2) {
   const bool walls = wall_doubles(h) > 0;
   double* const wall_ws = h->wall_ws;
@@ -1817,7 +1817,7 @@ int lbm_batch_set_launch(lbm_batch* b, int form, int ychunk) {
     return bfail(b, LBM_EINVAL, "unknown launch form");
   if (ychunk != 0 && (ychunk < 8 || ychunk > 64))
     return bfail(b, LBM_EINVAL, "row chunk must be 0 or in 8..64");
-  if (!b->pairs) return bfail(b, LBM_EUNSUPPORTED, "the batch does not use two-step passes");
+  if (!b->pairs) return bfail(b, LBM_EUNSUPPORTED, "the batch does not use passes of several steps");
   int rc = batch_pair_tiles(b, ychunk);
   if (rc != LBM_OK) return rc;
   b->form = form;
@@ -1887,7 +1887,7 @@ int lbm_batch_tune(lbm_batch* b, int trial_steps, int32_t* config_out, double* m
         best.ms = ms;
       }
     }
-    // launch forms and row chunks of the two-step passes
+    // launch forms and row chunks of the marching passes
     if (rc == LBM_OK && b->pairs) {
       const int64_t steps2 = std::max<int64_t>(2, trial_steps + (trial_steps & 1));
       double best_pair = 1e300;

@@ -101,9 +101,12 @@ static hipError_t march2_w(const MarchParams& p, int scheme, const MarchBufs& b,
 //     split) and 0.35 per source row (its load);
 //   * a SIMD's tiles one after another: c per row and stage of each;
 //   * the traffic at 5.2 TB/s, halo columns and rows read again.
-// The minimum is over time per step.  Large float32 lattices are bound by the
-// second (2048^2: 8 steps, 152 us), float64 ones by the third (149 us), small
-// ones by the first and the launch (64^2: 4 steps of one row per tile, 7.5 us).
+// The minimum is over time per step.  Large lattices are bound by the third (2048^2
+// float64: 8 steps, 106 rows, 157 us) or, in float32, nearly as much by the second (4
+// steps, 46 rows, 89 us), small ones by the first and the launch (64^2 float64: 8 steps of
+// one row per tile, 16 us).  The second term charges every tile a lone wavefront's time,
+// which several on one SIMD hide in part: 8 steps of 44 rows, which it rules out for
+// float32, take 140 us at 2048^2 against the 178 of twice 4.
 // 16 wall rows and columns per wavefront are more registers and instructions:
 // passes over walls stop at 4 steps and 32 rows.  Two-step passes that the third binds
 // stop at 8 rows: the traffic of their halo rows, which the model charges to memory,

@@ -1,6 +1,6 @@
-// Several time steps of a d = 2 lattice in one pass (k_march2) and of a d = 1
-// lattice (k_line), with the data of the Dirichlet walls for the steps of a pass
-// formed beforehand (k_wall_data2, k_wall_data1).
+// Several time steps of a d = 2 lattice in one pass (k_march2, and k_pair2 for two steps
+// of large periodic lattices) and of a d = 1 lattice (k_line), with the data of the
+// Dirichlet walls for the steps of a pass formed beforehand (k_wall_data2, k_wall_data1).
 //
 // d = 2.
 // One wavefront owns 64 consecutive columns of x_1 and marches along x_2.  Per
@@ -12,7 +12,7 @@
 // along x_2 by waiting in a register: c_2 = -1 values complete the row behind
 // at once, c_2 = 0 values wait one row and c_2 = +1 values two.  Nothing is
 // exchanged between wavefronts, so there is no LDS and no barrier; the price is
-// a halo of NL columns on either side, computed twice.
+// a halo of NL columns on either side and NL rows above and below a tile, computed twice.
 //
 // Every node goes through the arithmetic of k_step (k_step_split, k_wall and
 // k_wall_split on the walls), so a pass is bitwise NL single steps.

@@ -3,10 +3,11 @@ steps.
 
 The single-step kernels are the reference (they are held to the oracle
 elsewhere), so no tolerance enters.  Sizes sit at the edges of the passes' tiles:
-output widths of 48 (8 steps) and 56 (2 and 4 steps) columns, one row, one
-column, row chunks that end unevenly; step counts take every pass length and the
-single-step remainder.  d = 1: one node, the largest lattice held by one block
-(1024 nodes) and the first two cut into windows."""
+output widths of 48 (8 steps, taken in float64) and 56 (2 and 4 steps) columns, one
+row, one column; at these sizes every tile has one row (test_gpu_march_rows.py has the
+larger ones).  Step counts take several pass lengths and the single-step remainder.
+d = 1: one node, the largest lattice held by one block (1024 nodes) and the first two
+cut into windows."""
 import pytest
 
 from paper_2410_13165_amd import inputs

@@ -3,8 +3,9 @@
 The single-step kernels are the reference, so no tolerance enters.  Sizes sit at
 the edges of the passes' tiles (64 x 11, 64 x 7 and 32 x 10 columns), at the fewest
 planes a march can have, and at walls two and three rows apart (lattices with walls
-are as large as the passes take them, 1.5 million nodes); the step counts take 3, 3 + 1 as 2 + 2, 3 + 2, 3 + 3 + 1 as 3 + 2 + 2,
-and several passes in a row."""
+are as large as the passes take them, 1.4 million nodes; the thin ones go in pairs);
+the step counts take 3, 3 + 1 as 2 + 2, 3 + 2, 3 + 3 + 1 as 3 + 2 + 2, and several
+passes in a row."""
 import pytest
 
 from paper_2410_13165_amd import inputs
